@@ -187,7 +187,7 @@ rkn_status rkn_scan_windows(rkn_ctx *ctx, const rkn_scan_params *p, int32_t n_wi
  * memory (code under stream capture, tight serving loops, harnesses that forbid it):
  * the same scan and outputs, which must be device pointers (p->ptr_flags has
  * RKN_PTR_DEVICE; best_index and best_score are required, score and n_in may be
- * NULL). Its work memory (device windows, seed tiles, argmin partials, tile counter,
+ * NULL). Its work memory (device windows, seed chunks, argmin partials, chunk queue,
  * running minima) is one 256 MiB array per GPU, held from the library's load until
  * the process ends and shared by every call on that GPU: calls on one context's
  * stream are ordered, calls that overlap on one GPU from other streams race. The
@@ -202,16 +202,18 @@ rkn_status rkn_scan_windows_noalloc(rkn_ctx *ctx, const rkn_scan_params *p, int3
  * instrumented instance of the same kernel (the timed instances carry no counter):
  * counts[0] = seed-steps taken, counts[1] = sphere tests made by the cull (a wire's
  * line against the sphere around a block's middle point), counts[2] = chord/wire
- * distances evaluated (the DCA update of section 2.2). counts is a host array of 3.
+ * distances evaluated (the DCA update of section 2.2). The counts are those of the
+ * pairs within reach radially and of the sphere test; the timed instances also skip
+ * blocks beyond the wires' z range, whose distances are all out of reach. counts is a
+ * host array of 3.
  * Scores are computed but not returned. Fixed steps over the whole path only:
  * RKN_E_UNSUPPORTED with turn_stop. */
 rkn_status rkn_scan_work_counts(rkn_ctx *ctx, const rkn_scan_params *p, int32_t n_windows,
                                 const rkn_window *w, int64_t *counts);
 
 /* The kernel shape a scan with these parameters uses on the current hits: RKN steps
- * per cull block and seeds per tile (= lanes per workgroup), after the default and
- * the LDS/occupancy fit are resolved (tiles of the batched path and of
- * rkn_scan_windows are built for it). Either output may be NULL. */
+ * per cull block and seeds a workgroup holds at a time (= its lanes), after the default
+ * and the LDS/occupancy fit are resolved. Either output may be NULL. */
 rkn_status rkn_scan_shape(rkn_ctx *ctx, const rkn_scan_params *p, int32_t *block_steps, int32_t *seeds_per_tile);
 
 /* The scan of rkn_scan_windows followed by the choice of the k (1..RKN_TOPK_MAX)
@@ -273,10 +275,10 @@ rkn_status rkn_trace(rkn_ctx *ctx, const rkn_scan_params *p, int64_t n_seeds, co
                      int32_t n_sel, const int32_t *step_idx, double *states);
 
 /* ---- Batched scan of every uploaded event ---------------------------------------
- * The Hough stage, the expansion of its windows into seed tiles, one persistent
- * scan launch over all tiles (an atomic work queue of tiles of up to 64 seeds per
- * wave of the workgroup, 768 with the default shape, of one window each) and the
- * per-event argmin, captured once as HIP graphs on the
+ * The Hough stage, the expansion of its windows into seed chunks, one persistent
+ * scan launch over all of them (chunks of up to 64 seeds of one window, dealt to the
+ * waves of the workgroups; 768 seeds at a time in the default shape) and the per-event
+ * argmin, captured once as HIP graphs on the
  * context's stream. Re-plan after uploading new hits or geometry. */
 
 /* Validate the parameters, size every buffer for the worst case
@@ -287,7 +289,7 @@ rkn_status rkn_batch_plan(rkn_ctx *ctx, const rkn_hough_params *hp, const rkn_sc
 
 /* Autotuner of the batched path: plans the batch with each block size of
  * {4, 6, 8} RKN steps (which with the FP32 field map also sets the workgroup to
- * 16, 12 or 8 waves, i.e. the seeds per tile), times the scan over the tiles of the
+ * 16, 12 or 8 waves, i.e. the seeds a workgroup holds), times the scan over the seeds of the
  * first sample_events events on the current hits (HIP events, best of reps), and
  * leaves the batch planned with the fastest, as rkn_batch_plan with that
  * block_steps would. chosen (may be NULL): that block size; ms[3] (may be NULL):
@@ -336,7 +338,7 @@ rkn_status rkn_batch_results(rkn_ctx *ctx, int32_t max_windows, rkn_window *wind
  * are kept, each with the step of its own grid, 2 half-width / (grid - 1). An event
  * stops after the round whose lowest E is <= target[e], or after max_rounds. Every
  * round runs on the context's stream with no host synchronisation in between: the
- * grids, the seed tiles and the selection are built on the device. */
+ * grids, the seed chunks and the selection are built on the device. */
 typedef struct {
   int32_t k;           /* seeds kept per event, 1..RKN_TOPK_MAX                       */
   int32_t grid;        /* points per dimension of a round's grids, 2..16              */

@@ -147,13 +147,13 @@ void rkn_destroy(rkn_ctx* c) {
   c->refine_release();
   rkn::rescan_release(c);
   DevBuf* bufs[] = {&c->wire32, &c->wire64, &c->wire_layer, &c->layer_r, &c->field_nodes, &c->ev_off,
-                    &c->hits32, &c->hits64, &c->layer_off, &c->ev_maxdrift, &c->windows, &c->tiles,
-                    &c->ev_tiles, &c->parts, &c->counter, &c->mscratch, &c->out_score, &c->out_nin,
+                    &c->hits32, &c->hits64, &c->layer_off, &c->ev_maxdrift, &c->windows, &c->segs,
+                    &c->ev_chunk, &c->parts, &c->counter, &c->mscratch, &c->out_score, &c->out_nin,
                     &c->out_best_i, &c->out_best_e, &c->trace_buf, &c->seeds_buf, &c->perm_buf,
                     &c->wire_wx, &c->wire_wy, &c->hits_wire, &c->hough_acc, &c->hough_max,
                     &c->hough_cand_n, &c->hough_cand, &c->hough_slots, &c->hough_nsel, &c->hits_orig, &c->hits_phi, &c->layer_ext,
                     &c->sel_seg, &c->sel_win, &c->sel_idx, &c->sel_sc, &c->sel_seed, &c->cl_seeds,
-                    &c->cl_perm, &c->cl_tiles, &c->cl_resid, &c->cl_argmin, &c->cl_phi, &c->cl_mask,
+                    &c->cl_perm, &c->cl_segs, &c->cl_evc, &c->cl_resid, &c->cl_argmin, &c->cl_phi, &c->cl_mask,
                     &c->cl_count, &c->work_counts};
   for (DevBuf* b : bufs) b->release();
   for (DevBuf& b : c->extra) b.release();
@@ -214,6 +214,14 @@ rkn_status rkn_upload_geometry(rkn_ctx* c, int32_t n_wires, const double* mx, co
   RKN_HIP(upload(c->wire_wx, mx, (size_t)n_wires, c->stream), "geometry upload");
   RKN_HIP(upload(c->wire_wy, my, (size_t)n_wires, c->stream), "geometry upload");
   RKN_HIP(hipStreamSynchronize(c->stream), "geometry upload");
+  double z_lo = mz[0], z_hi = mz[0];
+  for (int i = 0; i < n_wires; ++i) {
+    const double dz = half_len[i] * fabs(uz[i]);
+    z_lo = std::min(z_lo, mz[i] - dz);
+    z_hi = std::max(z_hi, mz[i] + dz);
+  }
+  c->wire_zmin = (float)z_lo - 0.01f;   // outwards past the FP32 rounding
+  c->wire_zmax = (float)z_hi + 0.01f;
   c->n_wires = n_wires;
   c->n_layers = n_layers;
   c->h_layer_rmin.assign(layer_rmin, layer_rmin + n_layers);
@@ -334,15 +342,31 @@ rkn_status rkn_upload_hits(rkn_ctx* c, int32_t n_events, const int32_t* ev_off, 
 }
 
 // ---------------------------------------------------------------------------------
-static rkn_status run_scan(rkn_ctx* c, const rkn_scan_params* p, std::vector<rkn::WindowDev>& wins,
-                           std::vector<rkn::Tile>& tiles, std::vector<int32_t>& ev_tiles,
-                           int64_t total, double* score, int32_t* n_in, int64_t* best_index,
+// Segments and windows of a scan to the device.
+static rkn_status upload_segs(rkn_ctx* c, const std::vector<rkn::WindowDev>& wins, const rkn::SegList& list,
+                              rkn::ScanSegs& w) {
+  RKN_HIP(upload(c->windows, wins.data(), wins.size(), c->stream), "window upload");
+  RKN_HIP(upload(c->segs, list.segs.data(), list.segs.size(), c->stream), "segment upload");
+  RKN_HIP(upload(c->ev_chunk, list.ev_chunk.data(), list.ev_chunk.size(), c->stream), "segment upload");
+  w.segs = c->segs.as<rkn::Seg>();
+  w.n_seg = (int)list.segs.size() - 1;
+  w.ev_chunk = c->ev_chunk.as<int64_t>();
+  w.n_chunks = list.chunks;
+  w.windows = c->windows.as<rkn::WindowDev>();
+  return RKN_OK;
+}
+
+static rkn_status run_scan(rkn_ctx* c, const rkn_scan_params* p, const std::vector<rkn::WindowDev>& wins,
+                           const rkn::SegList& list, double* score, int32_t* n_in, int64_t* best_index,
                            double* best_score, const double* d_seeds5 = nullptr,
                            const int64_t* d_perm = nullptr) {
   const bool dev = (p->ptr_flags & RKN_PTR_DEVICE) != 0;
-  RKN_HIP(upload(c->windows, wins.data(), wins.size(), c->stream), "window upload");
-  RKN_HIP(upload(c->tiles, tiles.data(), tiles.size(), c->stream), "tile upload");
-  RKN_HIP(upload(c->ev_tiles, ev_tiles.data(), ev_tiles.size(), c->stream), "tile upload");
+  const int64_t total = list.seeds;
+  rkn::ScanSegs segs;
+  const rkn_status st = upload_segs(c, wins, list, segs);
+  if (st != RKN_OK) return st;
+  segs.seeds5 = d_seeds5;
+  segs.perm = d_perm;
   double* d_score = nullptr;
   int32_t* d_nin = nullptr;
   int64_t* d_bi;
@@ -374,9 +398,7 @@ static rkn_status run_scan(rkn_ctx* c, const rkn_scan_params* p, std::vector<rkn
   }
   rkn_scan_params q = *p;
   q.block_steps = rkn::resolve_block_steps(c, &q);
-  hipError_t e = rkn::launch_scan(c, &q, (int64_t)tiles.size(), c->tiles.as<rkn::Tile>(),
-                                  c->windows.as<rkn::WindowDev>(), d_seeds5, d_perm, d_score, d_nin,
-                                  d_bi, d_be, c->ev_tiles.as<int32_t>());
+  hipError_t e = rkn::launch_scan(c, &q, segs, d_score, d_nin, d_bi, d_be);
   if (e == hipErrorInvalidConfiguration) {
     c->err = "scan configuration does not fit the device (LDS per workgroup); use FP32 or fewer hits per event";
     return RKN_E_UNSUPPORTED;
@@ -392,20 +414,16 @@ static rkn_status run_scan(rkn_ctx* c, const rkn_scan_params* p, std::vector<rkn
   return RKN_OK;
 }
 
-// Windows -> device windows, tiles and per-event tile, seed and window offsets
+// Windows -> device windows and segments, and the per-event seed and window offsets
 // (windows must be ordered by event; an event's seeds are contiguous).
-static rkn_status prepare_windows(rkn_ctx* c, const rkn_scan_params* p, int32_t n_windows, const rkn_window* w,
-                                  std::vector<rkn::WindowDev>& wins, std::vector<rkn::Tile>& tiles,
-                                  std::vector<int32_t>& ev_tiles, int64_t& total, std::vector<long long>* ev_seed,
-                                  std::vector<int32_t>* ev_win) {
+static rkn_status prepare_windows(rkn_ctx* c, int32_t n_windows, const rkn_window* w,
+                                  std::vector<rkn::WindowDev>& wins, rkn::SegList& list,
+                                  std::vector<long long>* ev_seed, std::vector<int32_t>* ev_win) {
   if (n_windows < 0 || (n_windows > 0 && !w)) return arg_err(c, "bad window array");
   wins.assign(std::max(n_windows, 1), rkn::WindowDev{});
-  tiles.clear();
-  ev_tiles.assign(c->n_events + 1, 0);
+  list.segs.reserve((size_t)n_windows + 1);
   if (ev_seed) ev_seed->assign(c->n_events + 1, 0);
   if (ev_win) ev_win->assign(c->n_events + 1, 0);
-  const int T = rkn::scan_tile(c, p);
-  total = 0;
   int last_ev = -1;
   for (int k = 0; k < n_windows; ++k) {
     const rkn_window& x = w[k];
@@ -420,8 +438,7 @@ static rkn_status prepare_windows(rkn_ctx* c, const rkn_scan_params* p, int32_t 
       if (size > (int64_t(1) << 40)) return arg_err(c, "window too large");
     }
     for (int e = last_ev + 1; e <= x.event; ++e) {
-      ev_tiles[e] = (int32_t)tiles.size();
-      if (ev_seed) (*ev_seed)[e] = total;
+      if (ev_seed) (*ev_seed)[e] = list.seeds;
       if (ev_win) (*ev_win)[e] = k;
     }
     last_ev = x.event;
@@ -432,20 +449,11 @@ static rkn_status prepare_windows(rkn_ctx* c, const rkn_scan_params* p, int32_t 
       d.count[j] = x.count[j];
     }
     d.event = x.event;
-    for (int64_t s = 0; s < size; s += T) {
-      rkn::Tile t{};
-      t.window = k;
-      t.event = x.event;
-      t.n = (int32_t)std::min<int64_t>(T, size - s);
-      t.start = s;
-      t.gbase = total + s;
-      tiles.push_back(t);
-    }
-    total += size;
+    list.add(x.event, size);
   }
+  list.close();
   for (int e = last_ev + 1; e <= c->n_events; ++e) {
-    ev_tiles[e] = (int32_t)tiles.size();
-    if (ev_seed) (*ev_seed)[e] = total;
+    if (ev_seed) (*ev_seed)[e] = list.seeds;
     if (ev_win) (*ev_win)[e] = n_windows;
   }
   return RKN_OK;
@@ -455,10 +463,9 @@ static rkn_status prepare_windows(rkn_ctx* c, const rkn_scan_params* p, int32_t 
 
 namespace rkn {
 
-rkn_status prepare_scan_windows(rkn_ctx* c, const rkn_scan_params* p, int32_t n_windows, const rkn_window* w,
-                                std::vector<WindowDev>& wins, std::vector<Tile>& tiles, std::vector<int32_t>& ev_tiles,
-                                int64_t& total) {
-  return prepare_windows(c, p, n_windows, w, wins, tiles, ev_tiles, total, nullptr, nullptr);
+rkn_status prepare_scan_windows(rkn_ctx* c, int32_t n_windows, const rkn_window* w, std::vector<WindowDev>& wins,
+                                SegList& list) {
+  return prepare_windows(c, n_windows, w, wins, list, nullptr, nullptr);
 }
 
 }  // namespace rkn
@@ -484,13 +491,11 @@ rkn_status rkn_scan_windows(rkn_ctx* c, const rkn_scan_params* p, int32_t n_wind
   if ((st = check_state(c)) != RKN_OK) return st;
   if (!best_index || !best_score) return arg_err(c, "best_index/best_score must not be NULL");
   std::vector<rkn::WindowDev> wins;
-  std::vector<rkn::Tile> tiles;
-  std::vector<int32_t> ev_tiles;
-  int64_t total = 0;
-  if ((st = prepare_windows(c, p, n_windows, w, wins, tiles, ev_tiles, total, nullptr, nullptr)) != RKN_OK)
+  rkn::SegList list(c->n_events);
+  if ((st = prepare_windows(c, n_windows, w, wins, list, nullptr, nullptr)) != RKN_OK)
     return st;
   RKN_HIP(hipSetDevice(c->device), "hipSetDevice");
-  return run_scan(c, p, wins, tiles, ev_tiles, total, score, n_in, best_index, best_score);
+  return run_scan(c, p, wins, list, score, n_in, best_index, best_score);
 }
 
 rkn_status rkn_scan_work_counts(rkn_ctx* c, const rkn_scan_params* p, int32_t n_windows, const rkn_window* w,
@@ -505,10 +510,8 @@ rkn_status rkn_scan_work_counts(rkn_ctx* c, const rkn_scan_params* p, int32_t n_
     return RKN_E_UNSUPPORTED;
   }
   std::vector<rkn::WindowDev> wins;
-  std::vector<rkn::Tile> tiles;
-  std::vector<int32_t> ev_tiles;
-  int64_t total = 0;
-  if ((st = prepare_windows(c, p, n_windows, w, wins, tiles, ev_tiles, total, nullptr, nullptr)) != RKN_OK)
+  rkn::SegList list(c->n_events);
+  if ((st = prepare_windows(c, n_windows, w, wins, list, nullptr, nullptr)) != RKN_OK)
     return st;
   RKN_HIP(hipSetDevice(c->device), "hipSetDevice");
   RKN_HIP(c->work_counts.ensure(4 * sizeof(unsigned long long)), "alloc");
@@ -519,7 +522,7 @@ rkn_status rkn_scan_work_counts(rkn_ctx* c, const rkn_scan_params* p, int32_t n_
   rkn_scan_params q = *p;
   q.ptr_flags = 0;
   c->count_work = c->work_counts.as<unsigned long long>();
-  st = run_scan(c, &q, wins, tiles, ev_tiles, total, nullptr, nullptr, bi.data(), bs.data());
+  st = run_scan(c, &q, wins, list, nullptr, nullptr, bi.data(), bs.data());
   c->count_work = nullptr;
   if (st != RKN_OK) return st;
   unsigned long long h[4];
@@ -542,14 +545,12 @@ rkn_status rkn_scan_windows_adaptive(rkn_ctx* c, const rkn_scan_params* p, const
   rkn_scan_params q = *p;
   q.block_steps = 4;
   std::vector<rkn::WindowDev> wins;
-  std::vector<rkn::Tile> tiles;
-  std::vector<int32_t> ev_tiles;
-  int64_t total = 0;
-  if ((st = prepare_windows(c, &q, n_windows, w, wins, tiles, ev_tiles, total, nullptr, nullptr)) != RKN_OK)
+  rkn::SegList list(c->n_events);
+  if ((st = prepare_windows(c, n_windows, w, wins, list, nullptr, nullptr)) != RKN_OK)
     return st;
   RKN_HIP(hipSetDevice(c->device), "hipSetDevice");
   c->adapt = ap;
-  st = run_scan(c, &q, wins, tiles, ev_tiles, total, score, n_in, best_index, best_score);
+  st = run_scan(c, &q, wins, list, score, n_in, best_index, best_score);
   c->adapt = nullptr;
   return st;
 }
@@ -562,21 +563,18 @@ rkn_status rkn_scan_windows_topk(rkn_ctx* c, const rkn_scan_params* p, int32_t n
   if ((st = check_state(c)) != RKN_OK) return st;
   if (k < 1 || k > RKN_TOPK_MAX || !index || !score) return arg_err(c, "topk: k in [1, 16] and index/score outputs");
   std::vector<rkn::WindowDev> wins;
-  std::vector<rkn::Tile> tiles;
-  std::vector<int32_t> ev_tiles, ev_win;
+  rkn::SegList list(c->n_events);
+  std::vector<int32_t> ev_win;
   std::vector<long long> ev_seed;
-  int64_t total = 0;
-  if ((st = prepare_windows(c, p, n_windows, w, wins, tiles, ev_tiles, total, &ev_seed, &ev_win)) != RKN_OK)
-    return st;
+  if ((st = prepare_windows(c, n_windows, w, wins, list, &ev_seed, &ev_win)) != RKN_OK) return st;
   RKN_HIP(hipSetDevice(c->device), "hipSetDevice");
   const bool dev = (p->ptr_flags & RKN_PTR_DEVICE) != 0;
   const size_t ne = (size_t)c->n_events;
-  RKN_HIP(upload(c->windows, wins.data(), wins.size(), c->stream), "window upload");
-  RKN_HIP(upload(c->tiles, tiles.data(), std::max<size_t>(tiles.size(), 1), c->stream), "tile upload");
-  RKN_HIP(upload(c->ev_tiles, ev_tiles.data(), ev_tiles.size(), c->stream), "tile upload");
+  rkn::ScanSegs segs;
+  if ((st = upload_segs(c, wins, list, segs)) != RKN_OK) return st;
   RKN_HIP(upload(c->sel_seg, ev_seed.data(), ev_seed.size(), c->stream), "offset upload");
   RKN_HIP(upload(c->sel_win, ev_win.data(), ev_win.size(), c->stream), "offset upload");
-  RKN_HIP(c->out_score.ensure(sizeof(double) * (size_t)std::max<int64_t>(total, 1)), "alloc");
+  RKN_HIP(c->out_score.ensure(sizeof(double) * (size_t)std::max<int64_t>(list.seeds, 1)), "alloc");
   RKN_HIP(c->out_best_i.ensure(sizeof(int64_t) * ne), "alloc");
   RKN_HIP(c->out_best_e.ensure(sizeof(double) * ne), "alloc");
   int64_t* d_idx = index;
@@ -592,10 +590,8 @@ rkn_status rkn_scan_windows_topk(rkn_ctx* c, const rkn_scan_params* p, int32_t n
   }
   rkn_scan_params q = *p;
   q.block_steps = rkn::resolve_block_steps(c, &q);
-  hipError_t e = rkn::launch_scan(c, &q, (int64_t)tiles.size(), c->tiles.as<rkn::Tile>(),
-                                  c->windows.as<rkn::WindowDev>(), nullptr, nullptr, c->out_score.as<double>(),
-                                  nullptr, c->out_best_i.as<int64_t>(), c->out_best_e.as<double>(),
-                                  c->ev_tiles.as<int32_t>());
+  hipError_t e = rkn::launch_scan(c, &q, segs, c->out_score.as<double>(), nullptr, c->out_best_i.as<int64_t>(),
+                                  c->out_best_e.as<double>());
   if (e == hipErrorInvalidConfiguration) {
     c->err = "scan configuration does not fit the device (LDS per workgroup); use FP32 or fewer hits per event";
     return RKN_E_UNSUPPORTED;
@@ -626,7 +622,7 @@ rkn_status rkn_scan_seeds(rkn_ctx* c, const rkn_scan_params* p, int64_t n_seeds,
     return arg_err(c, "bad seed arrays");
   if (!best_index || !best_score) return arg_err(c, "best_index/best_score must not be NULL");
   if (n_seeds > (int64_t(1) << 31)) return arg_err(c, "too many seeds");
-  // Each explicit seed becomes a one-point window; seeds are grouped by event (stable)
+  // Seeds are grouped by event (stable), one segment each,
   // and a permutation maps scan order back to the caller's order.
   std::vector<int64_t> order(n_seeds);
   std::iota(order.begin(), order.end(), 0);
@@ -646,33 +642,20 @@ rkn_status rkn_scan_seeds(rkn_ctx* c, const rkn_scan_params* p, int64_t n_seeds,
     sorted[5 * i + 3] = py[s];
     sorted[5 * i + 4] = pz[s];
   }
-  std::vector<rkn::WindowDev> wins(1);
-  std::vector<rkn::Tile> tiles;
-  std::vector<int32_t> ev_tiles(c->n_events + 1, 0);
-  const int T = rkn::scan_tile(c, p);
-  int last_ev = -1;
+  const std::vector<rkn::WindowDev> wins(1);
+  rkn::SegList list(c->n_events);
   for (int64_t i = 0; i < n_seeds;) {
     const int ev = seed_event[order[i]];
     int64_t j = i;
     while (j < n_seeds && seed_event[order[j]] == ev) ++j;
-    for (int e = last_ev + 1; e <= ev; ++e) ev_tiles[e] = (int32_t)tiles.size();
-    last_ev = ev;
-    for (int64_t s = i; s < j; s += T) {
-      rkn::Tile t{};
-      t.window = 0;
-      t.event = ev;
-      t.n = (int32_t)std::min<int64_t>(T, j - s);
-      t.start = s;
-      t.gbase = s;
-      tiles.push_back(t);
-    }
+    list.add(ev, j - i);
     i = j;
   }
-  for (int e = last_ev + 1; e <= c->n_events; ++e) ev_tiles[e] = (int32_t)tiles.size();
+  list.close();
   RKN_HIP(hipSetDevice(c->device), "hipSetDevice");
   RKN_HIP(upload(c->seeds_buf, sorted.data(), sorted.size(), c->stream), "seed upload");
   RKN_HIP(upload(c->perm_buf, order.data(), (size_t)std::max<int64_t>(n_seeds, 1), c->stream), "seed upload");
-  return run_scan(c, p, wins, tiles, ev_tiles, n_seeds, score, n_in, best_index, best_score,
+  return run_scan(c, p, wins, list, score, n_in, best_index, best_score,
                   c->seeds_buf.as<double>(), c->perm_buf.as<int64_t>());
 }
 

@@ -3,11 +3,10 @@
 // replayed per batch (section 2.1 seeding and section 2.2 scan, many events).
 //
 // Graph A: the Hough stage for all events and the expansion of its window slots
-//          into the compact window list, the seed tiles (at most one workgroup's
-//          worth of seeds of one window) and the per-event tile ranges, all on the
-//          device.
-// Graph B: the persistent scan over the tiles (atomic tile queue, tile count read
-//          from device memory) and the per-event argmin.
+//          into the compact window list, its segments and the per-event chunk ranges,
+//          all on the device.
+// Graph B: the persistent scan over the chunks (their count read from device memory)
+//          and the per-event argmin.
 // HIP events recorded between the two graph launches time each stage.
 #include <algorithm>
 #include <string>
@@ -17,70 +16,62 @@
 
 namespace rkn {
 
-// Single workgroup: per-event sizes, a serial exclusive scan over events, then
-// every event writes its windows and tiles. Counts: [0] windows, [1] tiles.
+// Single workgroup: per-event sizes, a serial exclusive scan over events, then every
+// event writes its windows and segments. counts[0] = windows.
 __global__ void __launch_bounds__(256)
 batch_expand_kernel(const WinSlot* __restrict__ slots, const int32_t* __restrict__ nsel, int n_events,
-                    int32_t* __restrict__ ev_nw, int32_t* __restrict__ ev_nt, long long* __restrict__ ev_ns,
-                    WindowDev* __restrict__ windows, Tile* __restrict__ tiles, int32_t* __restrict__ ev_tiles,
-                    long long* __restrict__ ev_seed, int32_t* __restrict__ counts, int tile) {
+                    int32_t* __restrict__ ev_nw, long long* __restrict__ ev_nc, long long* __restrict__ ev_ns,
+                    WindowDev* __restrict__ windows, Seg* __restrict__ segs, int64_t* __restrict__ ev_chunk,
+                    long long* __restrict__ ev_seed, int32_t* __restrict__ counts) {
   const int tid = threadIdx.x;
   for (int e = tid; e < n_events; e += 256) {
-    int nw = 0, nt = 0;
-    long long ns = 0;
+    int nw = 0;
+    long long nc = 0, ns = 0;
     for (int j = 0; j < nsel[e]; ++j) {
       const WinSlot& s = slots[(size_t)e * kMaxCand + j];
       if (!s.valid) continue;
       long long size = 1;
       for (int q = 0; q < 5; ++q) size *= s.w.count[q];
       ++nw;
-      nt += (int)((size + tile - 1) / tile);
+      nc += (size + kChunk - 1) / kChunk;
       ns += size;
     }
     ev_nw[e] = nw;
-    ev_nt[e] = nt;
+    ev_nc[e] = nc;
     ev_ns[e] = ns;
   }
   __syncthreads();
   if (tid == 0) {
-    int w = 0, t = 0;
-    long long s = 0;
+    int w = 0;
+    long long ch = 0, s = 0;
     for (int e = 0; e < n_events; ++e) {
-      const int nw = ev_nw[e], nt = ev_nt[e];
-      const long long ns = ev_ns[e];
+      const int nw = ev_nw[e];
+      const long long nc = ev_nc[e], ns = ev_ns[e];
       ev_nw[e] = w;
-      ev_tiles[e] = t;
+      ev_chunk[e] = ch;
       ev_seed[e] = s;
       w += nw;
-      t += nt;
+      ch += nc;
       s += ns;
     }
-    ev_tiles[n_events] = t;
+    ev_chunk[n_events] = ch;
     ev_seed[n_events] = s;
     counts[0] = w;
-    counts[1] = t;
+    segs[w] = Seg{s, 0, ch, 0, 0};
   }
   __syncthreads();
   for (int e = tid; e < n_events; e += 256) {
-    int w = ev_nw[e], t = ev_tiles[e];
-    long long g = ev_seed[e];
+    int w = ev_nw[e];
+    long long g = ev_seed[e], ch = ev_chunk[e];
     for (int j = 0; j < nsel[e]; ++j) {
       const WinSlot& s = slots[(size_t)e * kMaxCand + j];
       if (!s.valid) continue;
       long long size = 1;
       for (int q = 0; q < 5; ++q) size *= s.w.count[q];
       windows[w] = s.w;
-      for (long long st = 0; st < size; st += tile) {
-        Tile tl;
-        tl.window = w;
-        tl.event = e;
-        tl.n = (int32_t)(size - st < tile ? size - st : tile);
-        tl.pad = 0;
-        tl.start = st;
-        tl.gbase = g + st;
-        tiles[t++] = tl;
-      }
+      segs[w] = Seg{g, size, ch, e, 0};
       g += size;
+      ch += (size + kChunk - 1) / kChunk;
       ++w;
     }
   }
@@ -108,6 +99,18 @@ void drop_graphs(rkn_ctx* c) {
   c->batch_launched = false;
 }
 
+// The seeds of the batch's first n events, as graph A leaves them on the device.
+ScanSegs batch_segs(const rkn_ctx* c, int n) {
+  ScanSegs w;
+  w.segs = c->b_segs.as<Seg>();
+  w.n_seg_dev = c->b_counts.as<int32_t>();
+  w.ev_chunk = c->b_ev_chunk.as<int64_t>();
+  w.n_chunks = c->batch_max_chunks;
+  w.n_chunks_dev = c->b_ev_chunk.as<int64_t>() + n;
+  w.windows = c->b_windows.as<WindowDev>();
+  return w;
+}
+
 // Addresses of the shared Hough buffers that the captured graph A refers to.
 void hough_ptrs(const rkn_ctx* c, void* out[6]) {
   out[0] = c->hough_acc.p;
@@ -128,7 +131,7 @@ void batch_release(rkn_ctx* c) {
   if (c->ev_t1) (void)hipEventDestroy(c->ev_t1);
   if (c->ev_t2) (void)hipEventDestroy(c->ev_t2);
   c->ev_t0 = c->ev_t1 = c->ev_t2 = nullptr;
-  DevBuf* bufs[] = {&c->b_windows, &c->b_tiles, &c->b_ev_tiles, &c->b_counts, &c->b_ev_seed,
+  DevBuf* bufs[] = {&c->b_windows, &c->b_segs, &c->b_ev_chunk, &c->b_counts, &c->b_ev_seed,
                     &c->b_score,   &c->b_nin,   &c->b_best_i,   &c->b_best_e, &c->b_ev_scratch,
                     &c->b_slab,    &c->b_parts, &c->b_counter};
   for (DevBuf* b : bufs) b->release();
@@ -169,8 +172,9 @@ rkn_status rkn_batch_plan(rkn_ctx* c, const rkn_hough_params* hp, const rkn_scan
   c->batch_scan = *sp;
   c->batch_scan.block_steps = resolve_block_steps(c, &c->batch_scan);
   const int tile = scan_tile(c, &c->batch_scan);
-  c->batch_max_tiles = max_windows * ((per_window + tile - 1) / tile);
-  if (c->batch_max_tiles > (int64_t(1) << 31) || c->batch_max_seeds > (int64_t(1) << 40)) {
+  const int64_t max_tiles = max_windows * ((per_window + tile - 1) / tile);
+  c->batch_max_chunks = max_windows * ((per_window + kChunk - 1) / kChunk);
+  if (max_tiles > (int64_t(1) << 31) || c->batch_max_seeds > (int64_t(1) << 40)) {
     c->err = "batch: capacity too large; lower max_seeds_window or max_cand";
     return RKN_E_CAPACITY;
   }
@@ -179,21 +183,20 @@ rkn_status rkn_batch_plan(rkn_ctx* c, const rkn_hough_params* hp, const rkn_scan
   c->batch_hough = h;
   if ((e = ensure_hough_buffers(c, h)) != hipSuccess) return berr(c, e, "batch alloc");
   if ((e = c->b_windows.ensure(sizeof(WindowDev) * std::max<int64_t>(max_windows, 1))) != hipSuccess ||
-      (e = c->b_tiles.ensure(sizeof(Tile) * std::max<int64_t>(c->batch_max_tiles, 1))) != hipSuccess ||
-      (e = c->b_ev_tiles.ensure(sizeof(int32_t) * (ne + 1))) != hipSuccess ||
+      (e = c->b_segs.ensure(sizeof(Seg) * (max_windows + 1))) != hipSuccess ||
+      (e = c->b_ev_chunk.ensure(sizeof(int64_t) * (ne + 1))) != hipSuccess ||
       (e = c->b_counts.ensure(64)) != hipSuccess ||
       (e = c->b_ev_seed.ensure(sizeof(long long) * (ne + 1))) != hipSuccess ||
-      (e = c->b_ev_scratch.ensure((sizeof(int32_t) * 2 + sizeof(long long)) * std::max(ne, 1))) != hipSuccess ||
+      (e = c->b_ev_scratch.ensure((sizeof(int32_t) * 2 + sizeof(long long) * 2) * std::max(ne, 1))) != hipSuccess ||
       (e = c->b_score.ensure(sizeof(double) * std::max<int64_t>(c->batch_max_seeds, 1))) != hipSuccess ||
       (e = c->b_nin.ensure(sizeof(int32_t) * std::max<int64_t>(c->batch_max_seeds, 1))) != hipSuccess ||
       (e = c->b_best_i.ensure(sizeof(int64_t) * ne)) != hipSuccess ||
       (e = c->b_best_e.ensure(sizeof(double) * ne)) != hipSuccess)
     return berr(c, e, "batch alloc");
   // size the scan's scratch before capture (no allocation inside a captured stream)
-  e = launch_scan_dev(c, &c->batch_scan, c->batch_max_tiles, c->b_counts.as<int32_t>() + 1,
-                      c->b_tiles.as<Tile>(), c->b_windows.as<WindowDev>(), c->b_score.as<double>(),
-                      c->b_nin.as<int32_t>(), c->b_best_i.as<int64_t>(), c->b_best_e.as<double>(),
-                      c->b_ev_tiles.as<int32_t>(), true);
+  const ScanSegs segs = batch_segs(c, ne);
+  e = launch_scan_dev(c, &c->batch_scan, segs, c->b_score.as<double>(), c->b_nin.as<int32_t>(),
+                      c->b_best_i.as<int64_t>(), c->b_best_e.as<double>(), true);
   if (e == hipErrorInvalidConfiguration) {
     c->err = "batch: scan configuration does not fit the device";
     return RKN_E_UNSUPPORTED;
@@ -208,16 +211,16 @@ rkn_status rkn_batch_plan(rkn_ctx* c, const rkn_hough_params* hp, const rkn_scan
   // graph A: Hough + expansion
   char* scratch = c->b_ev_scratch.as<char>();
   int32_t* ev_nw = reinterpret_cast<int32_t*>(scratch);
-  int32_t* ev_nt = ev_nw + std::max(ne, 1);
-  long long* ev_ns = reinterpret_cast<long long*>(ev_nt + std::max(ne, 1));
+  long long* ev_nc = reinterpret_cast<long long*>(ev_nw + 2 * std::max(ne, 1));
+  long long* ev_ns = ev_nc + std::max(ne, 1);
   if ((e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal)) != hipSuccess)
     return berr(c, e, "batch capture");
   hipError_t eq = queue_hough_all(c, h);
   if (eq == hipSuccess) {
     hipLaunchKernelGGL(batch_expand_kernel, dim3(1), dim3(256), 0, c->stream, c->hough_slots.as<WinSlot>(),
-                       c->hough_nsel.as<int32_t>(), ne, ev_nw, ev_nt, ev_ns, c->b_windows.as<WindowDev>(),
-                       c->b_tiles.as<Tile>(), c->b_ev_tiles.as<int32_t>(), c->b_ev_seed.as<long long>(),
-                       c->b_counts.as<int32_t>(), tile);
+                       c->hough_nsel.as<int32_t>(), ne, ev_nw, ev_nc, ev_ns, c->b_windows.as<WindowDev>(),
+                       c->b_segs.as<Seg>(), c->b_ev_chunk.as<int64_t>(), c->b_ev_seed.as<long long>(),
+                       c->b_counts.as<int32_t>());
     eq = hipGetLastError();
   }
   e = hipStreamEndCapture(c->stream, &c->g_hough);
@@ -228,10 +231,8 @@ rkn_status rkn_batch_plan(rkn_ctx* c, const rkn_hough_params* hp, const rkn_scan
   // graph B: persistent scan + argmin
   if ((e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal)) != hipSuccess)
     return berr(c, e, "batch capture");
-  eq = launch_scan_dev(c, &c->batch_scan, c->batch_max_tiles, c->b_counts.as<int32_t>() + 1,
-                       c->b_tiles.as<Tile>(), c->b_windows.as<WindowDev>(), c->b_score.as<double>(),
-                       c->b_nin.as<int32_t>(), c->b_best_i.as<int64_t>(), c->b_best_e.as<double>(),
-                       c->b_ev_tiles.as<int32_t>(), false);
+  eq = launch_scan_dev(c, &c->batch_scan, segs, c->b_score.as<double>(), c->b_nin.as<int32_t>(),
+                       c->b_best_i.as<int64_t>(), c->b_best_e.as<double>(), false);
   e = hipStreamEndCapture(c->stream, &c->g_scan);
   if (eq != hipSuccess) return berr(c, eq, "batch capture (scan)");
   if (e != hipSuccess) return berr(c, e, "batch capture end");
@@ -278,16 +279,14 @@ rkn_status rkn_batch_autotune(rkn_ctx* c, const rkn_hough_params* hp, const rkn_
     if (st == RKN_E_UNSUPPORTED) continue;
     if (st != RKN_OK) return st;
     hipError_t e;
-    // graph A writes the tiles; the scan then runs over the first events' tiles only
+    // graph A writes the segments; the scan then runs over the first events' chunks only
     if ((e = hipGraphLaunch(c->x_hough, c->stream)) != hipSuccess) return berr(c, e, "autotune");
     const int k = std::min(sample_events, c->n_events);
     float t_min = INFINITY;
     for (int r = 0; r < reps; ++r) {
       if ((e = hipEventRecord(c->ev_t1, c->stream)) != hipSuccess) return berr(c, e, "autotune");
-      e = launch_scan_dev(c, &c->batch_scan, c->batch_max_tiles, c->b_ev_tiles.as<int32_t>() + k,
-                          c->b_tiles.as<Tile>(), c->b_windows.as<WindowDev>(), c->b_score.as<double>(),
-                          c->b_nin.as<int32_t>(), c->b_best_i.as<int64_t>(), c->b_best_e.as<double>(),
-                          c->b_ev_tiles.as<int32_t>(), false);
+      e = launch_scan_dev(c, &c->batch_scan, batch_segs(c, k), c->b_score.as<double>(), c->b_nin.as<int32_t>(),
+                          c->b_best_i.as<int64_t>(), c->b_best_e.as<double>(), false);
       if (e != hipSuccess) return berr(c, e, "autotune scan");
       if ((e = hipEventRecord(c->ev_t2, c->stream)) != hipSuccess || (e = hipEventSynchronize(c->ev_t2)) != hipSuccess)
         return berr(c, e, "autotune");
@@ -399,7 +398,7 @@ rkn_status rkn_batch_info(rkn_ctx* c, int32_t* n_windows, int64_t* n_seeds, floa
   hipError_t e;
   if ((e = hipSetDevice(c->device)) != hipSuccess) return berr(c, e, "hipSetDevice");
   if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return berr(c, e, "batch sync");
-  int32_t counts[2] = {0, 0};
+  int32_t counts[1] = {0};
   long long total = 0;
   if ((e = hipMemcpy(counts, c->b_counts.p, sizeof(counts), hipMemcpyDeviceToHost)) != hipSuccess ||
       (e = hipMemcpy(&total, c->b_ev_seed.as<long long>() + c->n_events, sizeof(long long),

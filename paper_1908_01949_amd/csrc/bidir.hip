@@ -73,33 +73,27 @@ rkn_status classify(rkn_ctx* c, const rkn_scan_params* q, int64_t n, const int32
   rkn_scan_params p = *q;
   p.precision = 32;
   p.block_steps = 8;
-  const int T = scan_tile(c, &p);
   std::vector<int64_t> order(n);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return seed_event[a] < seed_event[b]; });
   std::vector<double> sorted((size_t)n * 5);
   for (int64_t i = 0; i < n; ++i)
     for (int d = 0; d < 5; ++d) sorted[5 * i + d] = seeds5[5 * order[i] + d];
-  std::vector<Tile> tiles;
+  SegList list(c->n_events);
   for (int64_t i = 0; i < n;) {
     const int ev = seed_event[order[i]];
     int64_t j = i;
     while (j < n && seed_event[order[j]] == ev) ++j;
-    for (int64_t s = i; s < j; s += T) {
-      Tile t{};
-      t.event = ev;
-      t.n = (int32_t)std::min<int64_t>(T, j - s);
-      t.start = s;
-      t.gbase = s;
-      tiles.push_back(t);
-    }
+    list.add(ev, j - i);
     i = j;
   }
+  list.close();
   const size_t H = (size_t)(c->max_hits_event > 0 ? c->max_hits_event : 1);
   hipError_t e;
   if ((e = c->cl_seeds.ensure(sizeof(double) * 5 * (size_t)n)) != hipSuccess ||
       (e = c->cl_perm.ensure(sizeof(int64_t) * (size_t)n)) != hipSuccess ||
-      (e = c->cl_tiles.ensure(sizeof(Tile) * std::max<size_t>(tiles.size(), 1))) != hipSuccess ||
+      (e = c->cl_segs.ensure(sizeof(Seg) * list.segs.size())) != hipSuccess ||
+      (e = c->cl_evc.ensure(sizeof(int64_t) * list.ev_chunk.size())) != hipSuccess ||
       (e = c->cl_resid.ensure(sizeof(float) * (size_t)n * H)) != hipSuccess ||
       (e = c->cl_argmin.ensure(sizeof(int32_t) * (size_t)n * H)) != hipSuccess ||
       (e = c->cl_phi.ensure(sizeof(double) * (size_t)n)) != hipSuccess)
@@ -107,11 +101,20 @@ rkn_status classify(rkn_ctx* c, const rkn_scan_params* q, int64_t n, const int32
   e = hipMemcpyAsync(c->cl_seeds.p, sorted.data(), sizeof(double) * 5 * (size_t)n, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(c->cl_perm.p, order.data(), sizeof(int64_t) * (size_t)n, hipMemcpyHostToDevice, c->stream);
-  if (e == hipSuccess && !tiles.empty())
-    e = hipMemcpyAsync(c->cl_tiles.p, tiles.data(), sizeof(Tile) * tiles.size(), hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess)
-    e = launch_refine_fwd(c, &p, (int64_t)tiles.size(), c->cl_tiles.as<Tile>(), c->cl_seeds.as<double>(),
-                          c->cl_perm.as<int64_t>(), nullptr, dmask, 1, c->cl_resid.as<float>(),
+    e = hipMemcpyAsync(c->cl_segs.p, list.segs.data(), sizeof(Seg) * list.segs.size(), hipMemcpyHostToDevice, c->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(c->cl_evc.p, list.ev_chunk.data(), sizeof(int64_t) * list.ev_chunk.size(), hipMemcpyHostToDevice,
+                       c->stream);
+  ScanSegs segs;
+  segs.segs = c->cl_segs.as<Seg>();
+  segs.n_seg = (int)list.segs.size() - 1;
+  segs.ev_chunk = c->cl_evc.as<int64_t>();
+  segs.n_chunks = list.chunks;
+  segs.seeds5 = c->cl_seeds.as<double>();
+  segs.perm = c->cl_perm.as<int64_t>();
+  if (e == hipSuccess)
+    e = launch_refine_fwd(c, &p, segs, nullptr, dmask, 1, c->cl_resid.as<float>(),
                           c->cl_argmin.as<int32_t>(), c->cl_phi.as<double>(), nullptr, 64, 0, n);
   if (e == hipErrorInvalidConfiguration) {
     c->err = "classify: scan configuration does not fit the device";

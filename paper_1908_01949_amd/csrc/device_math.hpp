@@ -483,16 +483,30 @@ __device__ __forceinline__ void rkn_step_err(State<R>& st, const FieldDev& f, co
 // m + t u (|t| <= L, |u| = 1): clamp the chord parameter of the line-line optimum,
 // take the wire's closest parameter for it, and if that leaves [-L, L] clamp it and
 // re-optimise the chord parameter (convexity makes this the global minimum).
-template <typename R>
+//
+// The FP32 sums are written as fused multiply-adds, so every kernel and every unrolled
+// copy that inlines this rounds alike; X_FIRST picks which of the first two products of
+// u.r is the inner one (the scan's unrolled chord loop takes x, everything else y).
+template <typename R, bool X_FIRST = false>
 __device__ __forceinline__ R seg_wire_d2(R p0x, R p0y, R p0z, R p1x, R p1y, R p1z, R mx, R my,
                                          R mz, R ux, R uy, R uz, R L) {
   const R dx = p1x - p0x, dy = p1y - p0y, dz = p1z - p0z;
   const R rx = p0x - mx, ry = p0y - my, rz = p0z - mz;
-  const R a = dx * dx + dy * dy + dz * dz;
-  const R b = dx * ux + dy * uy + dz * uz;
-  const R e = dx * rx + dy * ry + dz * rz;
-  const R f = ux * rx + uy * ry + uz * rz;
-  const R den = a - b * b;
+  R a, b, e, f, den;
+  if constexpr (sizeof(R) == 4) {
+    a = __builtin_fmaf(dz, dz, __builtin_fmaf(dx, dx, dy * dy));
+    b = __builtin_fmaf(uz, dz, __builtin_fmaf(ux, dx, uy * dy));
+    e = __builtin_fmaf(rz, dz, __builtin_fmaf(rx, dx, ry * dy));
+    f = X_FIRST ? __builtin_fmaf(uz, rz, __builtin_fmaf(uy, ry, ux * rx))
+                : __builtin_fmaf(uz, rz, __builtin_fmaf(ux, rx, uy * ry));
+    den = __builtin_fmaf(-b, b, a);
+  } else {
+    a = dx * dx + dy * dy + dz * dz;
+    b = dx * ux + dy * uy + dz * uz;
+    e = dx * rx + dy * ry + dz * rz;
+    f = ux * rx + uy * ry + uz * rz;
+    den = a - b * b;
+  }
   R s = den > (R)1e-6 * a ? (b * f - e) * frcp(den) : (R)0;
   s = clampv(s, (R)0, (R)1);
   const R t = b * s + f;
@@ -501,7 +515,11 @@ __device__ __forceinline__ R seg_wire_d2(R p0x, R p0y, R p0z, R p1x, R p1y, R p1
   const R vx = rx + s * dx - tc * ux;
   const R vy = ry + s * dy - tc * uy;
   const R vz = rz + s * dz - tc * uz;
-  return vx * vx + vy * vy + vz * vz;
+  if constexpr (sizeof(R) == 4) {
+    return __builtin_fmaf(vz, vz, __builtin_fmaf(vx, vx, vy * vy));
+  } else {
+    return vx * vx + vy * vy + vz * vz;
+  }
 }
 
 __device__ __forceinline__ int wave_min_i32(int v) {

@@ -1,7 +1,7 @@
 // rkn_scan_windows_noalloc: the window scan of rkn_scan_windows for callers that
 // cannot allocate device memory (code under stream capture, tight serving loops,
-// harnesses that forbid hipMalloc). Its work memory -- the device windows, the seed
-// tiles, the per-event tile offsets, the argmin partials, the tile counter and the
+// harnesses that forbid hipMalloc). Its work memory -- the device windows, their
+// segments, the per-event chunk offsets, the argmin partials, the chunk queue and the
 // slab of running minima -- lives in one file-scope device array per GPU, held from
 // the library's load until the process ends. Nothing in the call allocates.
 //
@@ -75,41 +75,54 @@ rkn_status rkn_scan_windows_noalloc(rkn_ctx* c, const rkn_scan_params* p, int32_
     return RKN_E_DEVICE;
   }
   std::vector<WindowDev> wins;
-  std::vector<Tile> tiles;
-  std::vector<int32_t> ev_tiles;
-  int64_t total = 0;
-  if ((st = prepare_scan_windows(c, p, n_windows, w, wins, tiles, ev_tiles, total)) != RKN_OK) return st;
+  SegList list(c->n_events);
+  if ((st = prepare_scan_windows(c, n_windows, w, wins, list)) != RKN_OK) return st;
   rkn_scan_params q = *p;
   q.block_steps = resolve_block_steps(c, &q);
-  // layout of the work array for this call; the slab takes what is left
-  const size_t n_tiles = tiles.size();
+  // layout of the work array for this call; the argmin partials take at most half of
+  // what is left (a scan of more chunks runs in several launches), the slab the rest
+  const size_t n_seg = list.segs.size();
   const size_t o_win = 0;
-  const size_t o_tiles = o_win + align256(sizeof(WindowDev) * wins.size());
-  const size_t o_evt = o_tiles + align256(sizeof(Tile) * std::max<size_t>(n_tiles, 1));
-  const size_t o_parts = o_evt + align256(sizeof(int32_t) * ev_tiles.size());
-  const size_t o_counter = o_parts + align256(sizeof(ArgminPart) * std::max<size_t>(n_tiles, 1));
-  const size_t o_slab = o_counter + 256;
+  const size_t o_segs = o_win + align256(sizeof(WindowDev) * wins.size());
+  const size_t o_evc = o_segs + align256(sizeof(Seg) * n_seg);
+  const size_t o_queue = o_evc + align256(sizeof(int64_t) * list.ev_chunk.size());
+  const size_t o_parts = o_queue + 256;
   const size_t per_wg = scan_slab_bytes_per_workgroup(c, &q);
-  if (o_slab + per_wg > kScratchBytes) {
-    c->err = "scan (no allocation): " + std::to_string(n_windows) + " windows, " + std::to_string(n_tiles) +
-             " tiles and the running minima of one workgroup need " + std::to_string(o_slab + per_wg) +
+  // the limit that callers know: 48 bytes for every workgroup's worth of seeds beside
+  // the windows and one workgroup's minima
+  const size_t T = (size_t)scan_tile(c, &q);
+  size_t need = o_win + align256(sizeof(WindowDev) * wins.size()) + align256(sizeof(int32_t) * list.ev_chunk.size()) +
+                256 + per_wg;
+  for (size_t k = 0; k + 1 < n_seg; ++k) need += 48 * (((size_t)list.segs[k].size + T - 1) / T);
+  if (need > kScratchBytes || o_parts + 256 + per_wg > kScratchBytes) {
+    c->err = "scan (no allocation): " + std::to_string(n_windows) + " windows, their " + std::to_string(list.seeds) +
+             " seeds and the running minima of one workgroup need " + std::to_string(need) +
              " bytes, more than the " + std::to_string(kScratchBytes) + "-byte work array";
     return RKN_E_CAPACITY;
   }
+  const size_t room = kScratchBytes - o_parts - per_wg;
+  const int64_t max_parts =
+      std::max<int64_t>(std::min<int64_t>(list.chunks, (int64_t)(room / 2 / sizeof(ArgminPart))), 1);
+  const size_t o_slab = o_parts + align256(sizeof(ArgminPart) * (size_t)max_parts);
   unsigned char* base = g_ptr[c->device];
   if ((e = hipMemcpyAsync(base + o_win, wins.data(), sizeof(WindowDev) * wins.size(), hipMemcpyHostToDevice,
                           c->stream)) != hipSuccess ||
-      (n_tiles > 0 && (e = hipMemcpyAsync(base + o_tiles, tiles.data(), sizeof(Tile) * n_tiles,
-                                          hipMemcpyHostToDevice, c->stream)) != hipSuccess) ||
-      (e = hipMemcpyAsync(base + o_evt, ev_tiles.data(), sizeof(int32_t) * ev_tiles.size(), hipMemcpyHostToDevice,
-                          c->stream)) != hipSuccess) {
+      (e = hipMemcpyAsync(base + o_segs, list.segs.data(), sizeof(Seg) * n_seg, hipMemcpyHostToDevice, c->stream)) !=
+          hipSuccess ||
+      (e = hipMemcpyAsync(base + o_evc, list.ev_chunk.data(), sizeof(int64_t) * list.ev_chunk.size(),
+                          hipMemcpyHostToDevice, c->stream)) != hipSuccess) {
     c->err = std::string("scan (no allocation) upload: ") + hipGetErrorString(e);
     return RKN_E_DEVICE;
   }
-  e = launch_scan_raw(c, &q, (int64_t)n_tiles, reinterpret_cast<const Tile*>(base + o_tiles),
-                      reinterpret_cast<const WindowDev*>(base + o_win), score, n_in, best_index, best_score,
-                      reinterpret_cast<const int32_t*>(base + o_evt), reinterpret_cast<ArgminPart*>(base + o_parts),
-                      reinterpret_cast<int*>(base + o_counter), base + o_slab, kScratchBytes - o_slab);
+  ScanSegs segs;
+  segs.segs = reinterpret_cast<const Seg*>(base + o_segs);
+  segs.n_seg = (int)n_seg - 1;
+  segs.ev_chunk = reinterpret_cast<const int64_t*>(base + o_evc);
+  segs.n_chunks = list.chunks;
+  segs.windows = reinterpret_cast<const WindowDev*>(base + o_win);
+  e = launch_scan_raw(c, &q, segs, score, n_in, best_index, best_score,
+                      reinterpret_cast<ArgminPart*>(base + o_parts), max_parts,
+                      reinterpret_cast<unsigned long long*>(base + o_queue), base + o_slab, kScratchBytes - o_slab);
   if (e == hipErrorInvalidConfiguration) {
     c->err = "scan configuration does not fit the device (LDS per workgroup); use FP32 or fewer hits per event";
     return RKN_E_UNSUPPORTED;

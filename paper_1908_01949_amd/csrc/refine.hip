@@ -681,25 +681,18 @@ rkn_status rerr(rkn_ctx* c, hipError_t e, const char* where) {
   return e == hipErrorOutOfMemory ? RKN_E_NOMEM : RKN_E_DEVICE;
 }
 
-// Tiles over runs of equal events of a slot list (slots grouped by event).
-std::vector<Tile> slot_tiles(const std::vector<int32_t>& ev, int T) {
-  std::vector<Tile> tiles;
+// Segments of a slot list grouped by event: `copies` slots per seed.
+SegList slot_segs(int n_events, const std::vector<int32_t>& ev, int copies) {
+  SegList list(n_events);
   const int64_t n = (int64_t)ev.size();
   for (int64_t i = 0; i < n;) {
     int64_t j = i;
     while (j < n && ev[j] == ev[i]) ++j;
-    for (int64_t s = i; s < j; s += T) {
-      Tile t{};
-      t.window = 0;
-      t.event = ev[i];
-      t.n = (int32_t)std::min<int64_t>(T, j - s);
-      t.start = s;
-      t.gbase = s;
-      tiles.push_back(t);
-    }
+    list.add(ev[i], (j - i) * copies);
     i = j;
   }
-  return tiles;
+  list.close();
+  return list;
 }
 
 // Sets the checkpoint interval and sizes the buffers that depend on it.
@@ -721,10 +714,14 @@ hipError_t refine_forward(rkn_ctx* c, bool trials, int define_mask, bool tape) {
   const int64_t n = c->r_n;
   const int copies = trials ? 6 : 1;
   const int64_t npos = n * copies;
-  Tile* tl = trials ? c->r_tiles6.as<Tile>() : c->r_tiles.as<Tile>();
-  const int64_t nt = trials ? c->r_ntiles6 : c->r_ntiles;
-  const double* seeds = trials ? c->r_trials.as<double>() : c->r_seeds.as<double>();
-  return launch_refine_fwd(c, &c->r_params, nt, tl, seeds, c->r_ident.as<int64_t>(),
+  ScanSegs w;
+  w.segs = trials ? c->r_segs6.as<Seg>() : c->r_segs.as<Seg>();
+  w.n_seg = c->r_nseg;
+  w.ev_chunk = trials ? c->r_evc6.as<int64_t>() : c->r_evc.as<int64_t>();
+  w.n_chunks = trials ? c->r_nchunks6 : c->r_nchunks;
+  w.seeds5 = trials ? c->r_trials.as<double>() : c->r_seeds.as<double>();
+  w.perm = c->r_ident.as<int64_t>();
+  return launch_refine_fwd(c, &c->r_params, w,
                            trials ? c->r_base6.as<int64_t>() : nullptr, c->r_mask.as<uint8_t>(), define_mask,
                            trials ? c->r_resid6.as<float>() : c->r_resid.as<float>(),
                            trials ? c->r_argmin6.as<int32_t>() : c->r_argmin.as<int32_t>(),
@@ -825,15 +822,13 @@ rkn_status rkn_refine_setup(rkn_ctx* c, const rkn_scan_params* p, int64_t n_seed
   c->r_nckpt = (p->n_steps + c->r_ckpt - 1) / c->r_ckpt;
   for (float& t : c->r_tune_ms) t = 0.0f;
   const int H = c->max_hits_event > 0 ? c->max_hits_event : 1;
-  const int T = scan_tile(c, &c->r_params);
-  std::vector<int32_t> ev(seed_event, seed_event + n_seeds);
+  const std::vector<int32_t> ev(seed_event, seed_event + n_seeds);
   // trials: the six step lengths of seed s at positions 6 s .. 6 s + 5, so that an
-  // event's trials share its tiles
-  std::vector<int32_t> ev6(6 * (size_t)n_seeds);
-  for (int64_t i = 0; i < 6 * n_seeds; ++i) ev6[i] = ev[i / 6];
-  std::vector<Tile> t1 = slot_tiles(ev, T), t6 = slot_tiles(ev6, T);
-  c->r_ntiles = (int64_t)t1.size();
-  c->r_ntiles6 = (int64_t)t6.size();
+  // event's trials share its chunks
+  const SegList l1 = slot_segs(c->n_events, ev, 1), l6 = slot_segs(c->n_events, ev, 6);
+  c->r_nseg = (int)l1.segs.size() - 1;
+  c->r_nchunks = l1.chunks;
+  c->r_nchunks6 = l6.chunks;
   std::vector<int64_t> ident(6 * n_seeds), base6(6 * n_seeds);
   for (int64_t i = 0; i < 6 * n_seeds; ++i) {
     ident[i] = i;
@@ -844,8 +839,10 @@ rkn_status rkn_refine_setup(rkn_ctx* c, const rkn_scan_params* p, int64_t n_seed
       (e = c->r_seeds0.ensure(sizeof(double) * 5 * n)) != hipSuccess ||
       (e = c->r_trials.ensure(sizeof(double) * 5 * 6 * n)) != hipSuccess ||
       (e = c->r_event.ensure(sizeof(int32_t) * n)) != hipSuccess ||
-      (e = c->r_tiles.ensure(sizeof(Tile) * std::max<size_t>(t1.size(), 1))) != hipSuccess ||
-      (e = c->r_tiles6.ensure(sizeof(Tile) * std::max<size_t>(t6.size(), 1))) != hipSuccess ||
+      (e = c->r_segs.ensure(sizeof(Seg) * l1.segs.size())) != hipSuccess ||
+      (e = c->r_segs6.ensure(sizeof(Seg) * l6.segs.size())) != hipSuccess ||
+      (e = c->r_evc.ensure(sizeof(int64_t) * l1.ev_chunk.size())) != hipSuccess ||
+      (e = c->r_evc6.ensure(sizeof(int64_t) * l6.ev_chunk.size())) != hipSuccess ||
       (e = c->r_ident.ensure(sizeof(int64_t) * 6 * n)) != hipSuccess ||
       (e = c->r_base6.ensure(sizeof(int64_t) * 6 * n)) != hipSuccess ||
       (e = c->r_mask.ensure(n * H)) != hipSuccess ||
@@ -865,10 +862,13 @@ rkn_status rkn_refine_setup(rkn_ctx* c, const rkn_scan_params* p, int64_t n_seed
   if (e == hipSuccess)
     e = hipMemcpyAsync(c->r_seeds0.p, seeds5, sizeof(double) * 5 * n, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(c->r_event.p, seed_event, sizeof(int32_t) * n, hipMemcpyHostToDevice, c->stream);
-  if (e == hipSuccess && !t1.empty())
-    e = hipMemcpyAsync(c->r_tiles.p, t1.data(), sizeof(Tile) * t1.size(), hipMemcpyHostToDevice, c->stream);
-  if (e == hipSuccess && !t6.empty())
-    e = hipMemcpyAsync(c->r_tiles6.p, t6.data(), sizeof(Tile) * t6.size(), hipMemcpyHostToDevice, c->stream);
+  auto up = [&](DevBuf& b, const void* src, size_t bytes) {
+    if (e == hipSuccess) e = hipMemcpyAsync(b.p, src, bytes, hipMemcpyHostToDevice, c->stream);
+  };
+  up(c->r_segs, l1.segs.data(), sizeof(Seg) * l1.segs.size());
+  up(c->r_segs6, l6.segs.data(), sizeof(Seg) * l6.segs.size());
+  up(c->r_evc, l1.ev_chunk.data(), sizeof(int64_t) * l1.ev_chunk.size());
+  up(c->r_evc6, l6.ev_chunk.data(), sizeof(int64_t) * l6.ev_chunk.size());
   if (e == hipSuccess)
     e = hipMemcpyAsync(c->r_ident.p, ident.data(), sizeof(int64_t) * 6 * n, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess)

@@ -3,9 +3,9 @@
 //
 // Per round, on the context's stream and with no host synchronisation:
 //   rescan_expand_kernel  the grids of every still-running event (one window per kept
-//                         seed, half-width = the step that seed came from), the seed
-//                         tiles and the per-event window/tile/seed offsets;
-//   launch_scan_dev       the persistent scan over those tiles (tile count read from
+//                         seed, half-width = the step that seed came from), their
+//                         segments and the per-event window/chunk/seed offsets;
+//   launch_scan_dev       the persistent scan over those chunks (their count read from
 //                         device memory) with scores per seed;
 //   launch_topk           the k lowest (E, index) per event, decoded with the step of
 //                         each pick's own grid;
@@ -66,19 +66,18 @@ __device__ __forceinline__ long long window_points(const double* step, int grid,
   return size;
 }
 
-// Single workgroup: per-event window, tile and seed counts of the running events, a
-// serial exclusive scan over events, then the windows and tiles. counts[0] = windows,
-// counts[1] = tiles.
+// Single workgroup: per-event window, chunk and seed counts of the running events, a
+// serial exclusive scan over events, then the windows and segments. counts[0] = windows.
 __global__ void __launch_bounds__(256)
-rescan_expand_kernel(int ne, int k, int grid, int tile, const double* __restrict__ cur,
+rescan_expand_kernel(int ne, int k, int grid, const double* __restrict__ cur,
                      const double* __restrict__ step, const int32_t* __restrict__ active, int32_t* __restrict__ ev_nw,
-                     int32_t* __restrict__ ev_nt, long long* __restrict__ ev_ns, WindowDev* __restrict__ windows,
-                     Tile* __restrict__ tiles, int32_t* __restrict__ ev_win, int32_t* __restrict__ ev_tiles,
+                     long long* __restrict__ ev_nc, long long* __restrict__ ev_ns, WindowDev* __restrict__ windows,
+                     Seg* __restrict__ segs, int32_t* __restrict__ ev_win, int64_t* __restrict__ ev_chunk,
                      long long* __restrict__ ev_seed, int32_t* __restrict__ counts) {
   const int tid = threadIdx.x;
   for (int e = tid; e < ne; e += 256) {
-    int nw = 0, nt = 0;
-    long long ns = 0;
+    int nw = 0;
+    long long nc = 0, ns = 0;
     if (active[e]) {
       for (int j = 0; j < k; ++j) {
         const size_t o = ((size_t)e * k + j) * 5;
@@ -86,39 +85,39 @@ rescan_expand_kernel(int ne, int k, int grid, int tile, const double* __restrict
         int32_t cnt[5];
         const long long size = window_points(step + o, grid, cnt);
         ++nw;
-        nt += (int)((size + tile - 1) / tile);
+        nc += (size + kChunk - 1) / kChunk;
         ns += size;
       }
     }
     ev_nw[e] = nw;
-    ev_nt[e] = nt;
+    ev_nc[e] = nc;
     ev_ns[e] = ns;
   }
   __syncthreads();
   if (tid == 0) {
-    int w = 0, t = 0;
-    long long s = 0;
+    int w = 0;
+    long long ch = 0, s = 0;
     for (int e = 0; e < ne; ++e) {
-      const int nw = ev_nw[e], nt = ev_nt[e];
-      const long long ns = ev_ns[e];
+      const int nw = ev_nw[e];
+      const long long nc = ev_nc[e], ns = ev_ns[e];
       ev_win[e] = w;
-      ev_tiles[e] = t;
+      ev_chunk[e] = ch;
       ev_seed[e] = s;
       w += nw;
-      t += nt;
+      ch += nc;
       s += ns;
     }
     ev_win[ne] = w;
-    ev_tiles[ne] = t;
+    ev_chunk[ne] = ch;
     ev_seed[ne] = s;
     counts[0] = w;
-    counts[1] = t;
+    segs[w] = Seg{s, 0, ch, 0, 0};
   }
   __syncthreads();
   for (int e = tid; e < ne; e += 256) {
     if (!active[e]) continue;
-    int w = ev_win[e], t = ev_tiles[e];
-    long long g = ev_seed[e];
+    int w = ev_win[e];
+    long long g = ev_seed[e], ch = ev_chunk[e];
     for (int j = 0; j < k; ++j) {
       const size_t o = ((size_t)e * k + j) * 5;
       if (!row_ok(cur + o, step + o)) continue;
@@ -130,16 +129,8 @@ rescan_expand_kernel(int ne, int k, int grid, int tile, const double* __restrict
       }
       W.event = e;
       windows[w] = W;
-      for (long long st = 0; st < size; st += tile) {
-        Tile tl;
-        tl.window = w;
-        tl.event = e;
-        tl.n = (int32_t)(size - st < tile ? size - st : tile);
-        tl.pad = 0;
-        tl.start = st;
-        tl.gbase = g + st;
-        tiles[t++] = tl;
-      }
+      segs[w] = Seg{g, size, ch, e, 0};
+      ch += (size + kChunk - 1) / kChunk;
       g += size;
       ++w;
     }
@@ -184,7 +175,7 @@ rkn_status aerr(rkn_ctx* c, const char* s) {
 
 void rescan_release(rkn_ctx* c) {
   DevBuf* bufs[] = {&c->rs_cur,       &c->rs_step,    &c->rs_score,    &c->rs_rounds,    &c->rs_active,
-                    &c->rs_target,    &c->rs_windows, &c->rs_tiles,    &c->rs_ev_tiles,  &c->rs_ev_seed,
+                    &c->rs_target,    &c->rs_windows, &c->rs_segs,     &c->rs_ev_chunk,  &c->rs_ev_seed,
                     &c->rs_ev_win,    &c->rs_counts,  &c->rs_ev_scratch, &c->rs_seed_score, &c->rs_best_i,
                     &c->rs_best_e,    &c->rs_sel_idx, &c->rs_sel_sc,   &c->rs_sel_seed,  &c->rs_sel_step,
                     &c->rs_parts,     &c->rs_counter, &c->rs_slab};
@@ -220,6 +211,7 @@ rkn_status rkn_rescan_refine(rkn_ctx* c, const rkn_scan_params* p, const rkn_res
   const long long per_window = (long long)G * G * G * G * G;
   const long long max_seeds = (long long)ne * k * per_window;
   const long long max_tiles = (long long)ne * k * ((per_window + tile - 1) / tile);
+  const long long max_chunks = (long long)ne * k * ((per_window + kChunk - 1) / kChunk);
   if (max_seeds > (1LL << 32) || max_tiles > (1LL << 31)) {
     c->err = "rescan: a round could scan more than 2^32 seeds; lower k or grid";
     return RKN_E_CAPACITY;
@@ -235,12 +227,12 @@ rkn_status rkn_rescan_refine(rkn_ctx* c, const rkn_scan_params* p, const rkn_res
       (e = c->rs_active.ensure(sizeof(int32_t) * ne)) != hipSuccess ||
       (e = c->rs_target.ensure(sizeof(double) * ne)) != hipSuccess ||
       (e = c->rs_windows.ensure(sizeof(WindowDev) * nk)) != hipSuccess ||
-      (e = c->rs_tiles.ensure(sizeof(Tile) * (size_t)std::max<long long>(max_tiles, 1))) != hipSuccess ||
-      (e = c->rs_ev_tiles.ensure(sizeof(int32_t) * (ne + 1))) != hipSuccess ||
+      (e = c->rs_segs.ensure(sizeof(Seg) * (nk + 1))) != hipSuccess ||
+      (e = c->rs_ev_chunk.ensure(sizeof(int64_t) * (ne + 1))) != hipSuccess ||
       (e = c->rs_ev_win.ensure(sizeof(int32_t) * (ne + 1))) != hipSuccess ||
       (e = c->rs_ev_seed.ensure(sizeof(long long) * (ne + 1))) != hipSuccess ||
       (e = c->rs_counts.ensure(64)) != hipSuccess ||
-      (e = c->rs_ev_scratch.ensure((sizeof(int32_t) * 2 + sizeof(long long)) * ne)) != hipSuccess ||
+      (e = c->rs_ev_scratch.ensure((sizeof(int32_t) * 2 + sizeof(long long) * 2) * ne)) != hipSuccess ||
       (e = c->rs_seed_score.ensure(sizeof(double) * (size_t)std::max<long long>(max_seeds, 1))) != hipSuccess ||
       (e = c->rs_best_i.ensure(sizeof(int64_t) * ne)) != hipSuccess ||
       (e = c->rs_best_e.ensure(sizeof(double) * ne)) != hipSuccess ||
@@ -251,10 +243,15 @@ rkn_status rkn_rescan_refine(rkn_ctx* c, const rkn_scan_params* p, const rkn_res
     return rerr(c, e, "rescan alloc");
   const ScanScratch scratch{&c->rs_parts, &c->rs_counter, &c->rs_slab};
   // size the scan's scratch before the first round (the launches then allocate nothing)
-  e = launch_scan_dev(c, &q, max_tiles, c->rs_counts.as<int32_t>() + 1, c->rs_tiles.as<Tile>(),
-                      c->rs_windows.as<WindowDev>(), c->rs_seed_score.as<double>(), nullptr,
-                      c->rs_best_i.as<int64_t>(), c->rs_best_e.as<double>(), c->rs_ev_tiles.as<int32_t>(), true,
-                      &scratch);
+  ScanSegs segs;
+  segs.segs = c->rs_segs.as<Seg>();
+  segs.n_seg_dev = c->rs_counts.as<int32_t>();
+  segs.ev_chunk = c->rs_ev_chunk.as<int64_t>();
+  segs.n_chunks = max_chunks;
+  segs.n_chunks_dev = c->rs_ev_chunk.as<int64_t>() + ne;
+  segs.windows = c->rs_windows.as<WindowDev>();
+  e = launch_scan_dev(c, &q, segs, c->rs_seed_score.as<double>(), nullptr, c->rs_best_i.as<int64_t>(),
+                      c->rs_best_e.as<double>(), true, &scratch);
   if (e == hipErrorInvalidConfiguration) {
     c->err = "rescan: scan configuration does not fit the device";
     return RKN_E_UNSUPPORTED;
@@ -298,18 +295,16 @@ rkn_status rkn_rescan_refine(rkn_ctx* c, const rkn_scan_params* p, const rkn_res
   // ---- rounds -----------------------------------------------------------------------
   char* scr = c->rs_ev_scratch.as<char>();
   int32_t* ev_nw = reinterpret_cast<int32_t*>(scr);
-  int32_t* ev_nt = ev_nw + ne;
-  long long* ev_ns = reinterpret_cast<long long*>(ev_nt + ne);
+  long long* ev_nc = reinterpret_cast<long long*>(ev_nw + 2 * ne);
+  long long* ev_ns = ev_nc + ne;
   for (int r = 0; r < rp->max_rounds; ++r) {
-    hipLaunchKernelGGL(rescan_expand_kernel, dim3(1), dim3(256), 0, c->stream, ne, k, G, tile,
-                       c->rs_cur.as<double>(), c->rs_step.as<double>(), c->rs_active.as<int32_t>(), ev_nw, ev_nt,
-                       ev_ns, c->rs_windows.as<WindowDev>(), c->rs_tiles.as<Tile>(), c->rs_ev_win.as<int32_t>(),
-                       c->rs_ev_tiles.as<int32_t>(), c->rs_ev_seed.as<long long>(), c->rs_counts.as<int32_t>());
+    hipLaunchKernelGGL(rescan_expand_kernel, dim3(1), dim3(256), 0, c->stream, ne, k, G,
+                       c->rs_cur.as<double>(), c->rs_step.as<double>(), c->rs_active.as<int32_t>(), ev_nw, ev_nc,
+                       ev_ns, c->rs_windows.as<WindowDev>(), c->rs_segs.as<Seg>(), c->rs_ev_win.as<int32_t>(),
+                       c->rs_ev_chunk.as<int64_t>(), c->rs_ev_seed.as<long long>(), c->rs_counts.as<int32_t>());
     if ((e = hipGetLastError()) != hipSuccess) return rerr(c, e, "rescan expand");
-    e = launch_scan_dev(c, &q, max_tiles, c->rs_counts.as<int32_t>() + 1, c->rs_tiles.as<Tile>(),
-                        c->rs_windows.as<WindowDev>(), c->rs_seed_score.as<double>(), nullptr,
-                        c->rs_best_i.as<int64_t>(), c->rs_best_e.as<double>(), c->rs_ev_tiles.as<int32_t>(), false,
-                        &scratch);
+    e = launch_scan_dev(c, &q, segs, c->rs_seed_score.as<double>(), nullptr, c->rs_best_i.as<int64_t>(),
+                        c->rs_best_e.as<double>(), false, &scratch);
     if (e != hipSuccess) return rerr(c, e, "rescan scan");
     e = launch_topk(c, c->rs_seed_score.as<double>(), c->rs_ev_seed.as<long long>(), c->rs_windows.as<WindowDev>(),
                     c->rs_ev_win.as<int32_t>(), ne, c->rs_counts.as<int32_t>(), k, c->rs_sel_idx.as<int64_t>(),

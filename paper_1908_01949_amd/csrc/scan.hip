@@ -1,10 +1,12 @@
 // The seed-scan kernels for gfx950 (Yeo et al., CTD/WIT 2019, section 2.2, Eq. 1).
 //
 // Work decomposition (one MI355X):
-//   * one lane per seed; a workgroup of 64*WAVES lanes takes tiles of up to 64*WAVES
-//     seeds of one event from an atomic queue (persistent grid sized to the resident
-//     capacity); with a field map, the 65x129 (B_r, B_z) nodes are staged in LDS once
-//     per workgroup and shared by all its waves;
+//   * one lane per seed; a wave scans chunks of up to 64 seeds of one window. The
+//     persistent grid (sized to the resident capacity) deals runs of chunks to its
+//     workgroups, a first share fixed, the rest from an atomic queue in runs that
+//     shrink as it empties; a workgroup works through its run event by event, its
+//     waves taking the chunks one by one. With a field map, the 65x129 (B_r, B_z)
+//     nodes are staged in LDS once per workgroup and shared by all its waves;
 //   * the event's hits are staged in LDS, ordered by layer and, within a layer, by
 //     the twisted azimuth psi = phi - s_l z of the wire centre; a 1 mm radial table
 //     maps a radius range to the layers whose band (widened by the largest drift +
@@ -23,8 +25,8 @@
 //     a minimum in the current tile;
 //   * after the last block each lane forms E = sum min((D - d)^2, lambda) in FP64,
 //     reading only the marked rows (the others still hold +inf) and resetting them to
-//     +inf, so the slab is written once per workgroup at launch and afterwards only
-//     where a tile touched it.
+//     +inf, so a wave writes its slab columns once and afterwards only where a chunk
+//     touched them.
 // Every filter is exact: a pair it drops can only have a distance above
 // d + sqrt(lambda), where the term is lambda whatever the distance is.
 #include <type_traits>
@@ -57,18 +59,22 @@ struct ScanArgs {
   const float* ev_maxdrift;
   const float* hits_phi;      // twisted azimuth psi of each layer-ordered hit's wire centre
   const float2* layer_twist;  // [n_events][n_layers] (dphi/dz of the layer's wires, psi deviation)
+  float wire_zmin, wire_zmax; // z extent of all wires
   int n_layers;
   int sect_bytes;             // LDS bytes reserved for the layer x sector table
   int hits_bytes;             // LDS bytes reserved for hit records
   int field_bytes;            // LDS bytes reserved for the field map (0: uniform)
   int touch_words;            // 32-bit words of a wave's row bitmap (>= max hits / 32)
-  const Tile* tiles;
-  int64_t n_tiles;
-  const int32_t* n_tiles_dev;   // if set, the tile count is read here (captured launches)
+  const Seg* segs;            // [n_seg + 1]: windows (or explicit seeds' events) and their chunks
+  int n_seg;
+  const int32_t* n_seg_dev;   // if set, the segment count is read here (captured launches)
+  const int64_t* ev_chunk;    // first chunk of each event [n_events + 1]
+  int64_t chunk0, n_chunks;   // the chunks to scan: [chunk0, chunk0 + n_chunks)
+  const int64_t* n_chunks_dev;   // if set, n_chunks is read here
   const WindowDev* windows;
   const double* seeds5;       // explicit seeds [n][5] in scan order (NULL: windows)
   const int64_t* perm;        // scan order -> caller index (explicit seeds)
-  int* tile_counter;
+  unsigned long long* queue;  // chunks taken from the queue
   void* mscratch;
   int64_t slab_stride;        // elements per workgroup slab
   double R0, charge, h, lambda;
@@ -76,7 +82,7 @@ struct ScanArgs {
   int turn_stop;              // 1: a lane's track ends with the first step inside r < R0
   double* score;
   int32_t* nin;
-  ArgminPart* parts;
+  ArgminPart* parts;          // per chunk, [chunk - chunk0]
   // refinement forward mode (MODE 1): per output slot = scan position
   const int32_t* hits_orig;   // original index (within its event) of each layer-ordered hit
   const int64_t* base_of;     // scan position -> refinement seed whose inlier set applies
@@ -229,7 +235,7 @@ hipError_t launch_prep_hits(rkn_ctx* c, const int32_t* d_wire_id, const float* d
 }
 
 // ---------------------------------------------------------------------------------
-__global__ void reset_counter_kernel(int* counter) { *counter = 0; }
+__global__ void reset_queue_kernel(unsigned long long* queue) { *queue = 0; }
 
 template <typename R>
 __device__ __forceinline__ const HitRec<R>* hits_of(const ScanArgs& a);
@@ -258,16 +264,15 @@ __device__ __forceinline__ R load_coherent(const R* p) {
 // written. The refinement pass writes every block (its inlier set is fixed).
 // The wave's row of the hit is marked in its LDS bitmap.
 template <typename R, int TILE, int MODE, typename S>
-__device__ __forceinline__ void fold_min(S* slab, uint32_t* touch, int hh, int wave, int s, R d2, int chord,
-                                         R lim2) {
+__device__ __forceinline__ void fold_min(S* slab, uint32_t* touch, int hh, int s, R d2, int chord, R lim2) {
   if constexpr (MODE == 0) {
     if (!(d2 < lim2)) return;
-    atomic_min_nonneg(slab + (size_t)hh * TILE + wave * 64 + s, d2);
+    atomic_min_nonneg(slab + (size_t)hh * TILE + s, d2);
   } else {
     // (distance bits, chord index): the minimum distance, then the lowest chord
     const unsigned long long key =
         ((unsigned long long)__float_as_uint((float)d2) << 32) | (unsigned long long)(unsigned)chord;
-    atomicMin(reinterpret_cast<unsigned long long*>(slab + (size_t)hh * TILE + wave * 64 + s), key);
+    atomicMin(reinterpret_cast<unsigned long long*>(slab + (size_t)hh * TILE + s), key);
   }
   atomicOr(touch + (hh >> 5), 1u << (hh & 31));
 }
@@ -281,10 +286,10 @@ __device__ __forceinline__ void fold_min(S* slab, uint32_t* touch, int hh, int w
 // reduction over the G lanes. In the scan, adjacent lanes first merge their minima
 // with one row shift (half the atomics, and half their L2 write-backs, for three
 // instructions); the refinement pass folds every lane's (distance, chord) key.
-template <typename R, int B, int TILE, int MODE, typename S>
+template <typename R, int B, int TILE, int MODE, bool Y_FIRST, typename S>
 __device__ __forceinline__ void flush_items(const uint32_t* items, int n_items, const R* pts,
-                                            const HitRec<R>* s_hits, S* slab, uint32_t* touch, int wave,
-                                            int lane, int nb, int step0, R sqrt_lam) {
+                                            const HitRec<R>* s_hits, S* slab, uint32_t* touch, int lane,
+                                            int nb, int step0, R sqrt_lam) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -301,7 +306,9 @@ __device__ __forceinline__ void flush_items(const uint32_t* items, int n_items, 
       if (j <= nb) {
         const R qx = pts[(j * 3 + 0) * 64 + s], qy = pts[(j * 3 + 1) * 64 + s],
                 qz = pts[(j * 3 + 2) * 64 + s];
-        const R d2 = seg_wire_d2<R>(px, py, pz, qx, qy, qz, w.mx, w.my, w.mz, w.ux, w.uy, w.uz, w.L);
+        const R d2 = j > 1 && !Y_FIRST
+                         ? seg_wire_d2<R, true>(px, py, pz, qx, qy, qz, w.mx, w.my, w.mz, w.ux, w.uy, w.uz, w.L)
+                         : seg_wire_d2<R>(px, py, pz, qx, qy, qz, w.mx, w.my, w.mz, w.ux, w.uy, w.uz, w.L);
         if (d2 < dmin) {
           dmin = d2;
           jmin = j - 1;
@@ -312,7 +319,7 @@ __device__ __forceinline__ void flush_items(const uint32_t* items, int n_items, 
       }
     }
     const R lim = w.drift + sqrt_lam;
-    fold_min<R, TILE, MODE>(slab, touch, hh, wave, s, dmin, step0 + jmin, lim * lim);
+    fold_min<R, TILE, MODE>(slab, touch, hh, s, dmin, step0 + jmin, lim * lim);
   }
   const int n_rem = n_items - done;
   if (n_rem > 0) {
@@ -346,7 +353,7 @@ __device__ __forceinline__ void flush_items(const uint32_t* items, int n_items, 
     }
     if (folds) {
       const R lim = w.drift + sqrt_lam;
-      fold_min<R, TILE, MODE>(slab, touch, hh, wave, s, dmin, step0 + jmin, lim * lim);
+      fold_min<R, TILE, MODE>(slab, touch, hh, s, dmin, step0 + jmin, lim * lim);
     }
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -396,6 +403,422 @@ __device__ __forceinline__ int test_staged(uint32_t* items, int lo, int hi, cons
   return out;
 }
 
+// The staged event: its hits and the tables the cull walks (LDS).
+template <typename R>
+struct EventLds {
+  HitRec<R>* hits;
+  uint16_t* ltab;    // 1 mm radial bin -> layers [l0, l1p), l0 | l1p << 8
+  uint16_t* sect;    // layer x twisted-azimuth sector -> run of the layer's hits
+  int* loff;         // first hit of each layer
+  float* slope;      // dphi/dz of each layer's wires
+};
+
+// Stage event ev with nthreads threads (the caller's barriers order it).
+template <typename R>
+__device__ __forceinline__ void stage_event(const ScanArgs& a, const EventLds<R>& L, int ev, int tid, int nthreads,
+                                            double block_len) {
+  const int hbase = a.ev_off[ev];
+  const int nh = a.ev_off[ev + 1] - hbase;
+  const HitRec<R>* ghits = hits_of<R>(a) + hbase;
+  for (int i = tid; i < nh; i += nthreads) L.hits[i] = ghits[i];
+  const int32_t* loff = a.layer_off + (size_t)ev * (a.n_layers + 1);
+  for (int l = tid; l <= a.n_layers; l += nthreads) L.loff[l] = loff[l];
+  // radial bins: the layers whose band, widened by the event's largest drift +
+  // sqrt(lambda) + 1 mm, meets the bin: [l0, l1p) packed as l0 | l1p << 8
+  const float D = a.ev_maxdrift[ev] + (float)sqrt(a.lambda) + kBandMargin;
+  for (int b = tid; b < kTabBins; b += nthreads) {
+    const float lo_r = (float)b, hi_r = b == kTabBins - 1 ? INFINITY : (float)(b + 1);
+    int l0 = 0;
+    while (l0 < a.n_layers && a.layer_r[l0].y + D < lo_r) ++l0;
+    int l1 = a.n_layers - 1;
+    while (l1 >= 0 && a.layer_r[l1].x - D > hi_r) --l1;
+    L.ltab[b] = (uint16_t)(l0 | ((l1 + 1) << 8));
+  }
+  // layer x twisted-azimuth sector: the circular run of a layer's hits (sorted by
+  // psi) that a block whose middle point c has psi_c = phi_c - s_l z_c in the
+  // sector can reach. A kept pair needs a wire point w within
+  // rho = d + sqrt(lambda) + margin + B h / 2 of c; then |phi_w - phi_c| <=
+  // 2 asin(rho / (2 (r_l - rho))) (radii >= r_l - rho and r_l),
+  // |z_w - z_c| <= rho, and phi_w - s_l z_w is within dev_l of the hit's psi.
+  const float rho = a.ev_maxdrift[ev] + (float)sqrt(a.lambda) + kCullMargin + 0.5f * (float)block_len;
+  const float* gpsi = a.hits_phi + hbase;
+  for (int l = tid; l < a.n_layers; l += nthreads) L.slope[l] = a.layer_twist[(size_t)ev * a.n_layers + l].x;
+  for (int q = tid; q < a.n_layers * kSectors; q += nthreads) {
+    const int l = q / kSectors, k = q - l * kSectors;
+    const int lb = loff[l], nl = loff[l + 1] - lb;
+    uint32_t ent = 0u;
+    if (nl > 0) {
+      const float2 tw = a.layer_twist[(size_t)ev * a.n_layers + l];
+      const float rl = a.layer_r[l].x - rho;
+      const float ratio = rl > 0.0f ? rho / (2.0f * rl) : 2.0f;
+      const float dphi = ratio < 1.0f ? 2.0f * asinf(ratio) : kPi;
+      const float W = dphi + fabsf(tw.x) * rho + tw.y + 2e-3f;
+      if (W >= kPi) {
+        ent = kSectAll;
+      } else {
+        const float a0 = -kPi + (2.0f * kPi / kSectors) * k, a1 = a0 + 2.0f * kPi / kSectors;
+        auto inside = [&](int j) {
+          const float ps = gpsi[lb + j];
+          if (ps >= a0 && ps <= a1) return true;
+          float d1 = a0 - ps, d2 = ps - a1;
+          d1 -= 2.0f * kPi * floorf(d1 / (2.0f * kPi));
+          d2 -= 2.0f * kPi * floorf(d2 / (2.0f * kPi));
+          return fminf(d1, d2) <= W;
+        };
+        int cnt = 0, start = -1;
+        bool prev = inside(nl - 1);
+        for (int j = 0; j < nl; ++j) {
+          const bool in = inside(j);
+          cnt += in;
+          if (in && !prev && start < 0) start = j;
+          prev = in;
+        }
+        if (cnt == nl) start = 0;
+        ent = cnt > 127 ? kSectAll : (cnt > 0 ? ((uint32_t)start | ((uint32_t)cnt << 9)) : 0u);
+      }
+    }
+    L.sect[q] = (uint16_t)ent;
+  }
+}
+
+// One lane's place in a chunk: whether it has a seed, and the seed's output index.
+struct LaneSlot {
+  bool in_tile;
+  int64_t gidx;
+};
+
+// A chunk's lanes; with v not NULL also their seeds (lanes without one repeat the first).
+__device__ __forceinline__ LaneSlot lane_slot(const ScanArgs& a, int seg, int64_t ch, int lane, double* v) {
+  const Seg sg = a.segs[seg];
+  const int64_t first = (ch - sg.chunk0) * kChunk;
+  LaneSlot q;
+  q.in_tile = lane < sg.size - first;
+  const int64_t local = first + (q.in_tile ? lane : 0);
+  q.gidx = sg.gbase + local;
+  if (a.seeds5) {
+    if (v) {
+#pragma unroll
+      for (int d = 0; d < 5; ++d) v[d] = a.seeds5[q.gidx * 5 + d];
+    }
+    q.gidx = a.perm[q.gidx];
+  } else {
+    q.gidx = sg.gbase + window_scan_seed(a.windows[seg], local, v);
+  }
+  return q;
+}
+
+// The starting state of a chunk's lanes; valid: the lane's seed has a momentum.
+template <typename R>
+__device__ __forceinline__ LaneSlot load_seed(const ScanArgs& a, int seg, int64_t ch, int lane, State<R>& st,
+                                              bool& valid) {
+  double v[5];
+  const LaneSlot q = lane_slot(a, seg, ch, lane, v);
+  const double pm = sqrt(v[2] * v[2] + v[3] * v[3] + v[4] * v[4]);
+  valid = q.in_tile && (pm >= 1e-3);
+  const double ipm = valid ? 1.0 / pm : 0.0;
+  st.x = (R)(a.R0 * cos(v[0]));
+  st.y = (R)(a.R0 * sin(v[0]));
+  st.z = (R)v[1];
+  st.tx = valid ? (R)(v[2] * ipm) : (R)1;
+  st.ty = valid ? (R)(v[3] * ipm) : (R)0;
+  st.tz = valid ? (R)(v[4] * ipm) : (R)0;
+  st.lam = valid ? (R)(kKappa * a.charge * ipm) : (R)0;
+  st.cx = st.cy = st.cz = (R)0;
+  st.ctx = st.cty = st.ctz = (R)0;
+  return q;
+}
+
+// The checkpoint of a lane at one of the refinement pass's checkpoint steps.
+template <typename R>
+__device__ __forceinline__ void write_tape(const ScanArgs& a, int step, int64_t gidx, const State<R>& st) {
+  float* tp = a.tape + (size_t)(step / a.ckpt) * 13 * a.n_pos + gidx;
+  const float v13[13] = {(float)st.x,  (float)st.y,  (float)st.z,   (float)st.cx,  (float)st.cy, (float)st.cz, (float)st.tx,
+                         (float)st.ty, (float)st.tz, (float)st.ctx, (float)st.cty, (float)st.ctz, (float)st.lam};
+#pragma unroll
+  for (int q = 0; q < 13; ++q) tp[(size_t)q * a.n_pos] = v13[q];
+}
+
+// Segment holding chunk ch: segs[s].chunk0 <= ch < segs[s + 1].chunk0.
+__device__ __forceinline__ int find_seg(const Seg* segs, int n_seg, int64_t ch) {
+  int lo = 0, hi = n_seg;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) / 2;
+    if (segs[mid].chunk0 <= ch)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+
+// Wire candidates of one block for the wave's 64 lanes, and the chord distances of the
+// kept pairs. Per lane: whether its block is to be culled (on), the radial range of its
+// points (r2min, r2max) and its points in column `lane` of pts.
+//
+// A block whose middle point lies outside [z_lo, z_hi] is out of every wire's reach along
+// z (a quarter of the blocks of the 6000-step paths) and has no candidates. Only the scan
+// drops it: the refinement's inliers count wherever they are, and the counting instance
+// counts the pairs of the radial and sphere rules.
+//
+// Per layer whose band meets the block's radial range, the candidates are the run of
+// hits that can reach the azimuth sector of the block's middle point. Each lane walks
+// its own runs and stages (lane, hit) pairs in the wave's list (cheap steps, as many as
+// the longest run in the wave); the staged pairs are then sphere-tested densely, one
+// per lane, and the survivors kept at the list's front for the distance pass.
+template <typename R, int B, int TILE, int MODE, bool Y_FIRST, bool COUNT, typename S>
+__device__ __forceinline__ void cull_block(const EventLds<R>& L, const R* pts, uint32_t* items, S* slab,
+                                           uint32_t* touch, int lane, bool on, int nb, int step0, R r2min, R r2max,
+                                           float half_h, float z_lo, float z_hi, R Kcull, R sqrt_lam, unsigned long long& w_tests,
+                                           unsigned long long& w_chords) {
+  const int jc = nb / 2;
+  // the block's middle point, from this lane's own column
+  const R cx = pts[(jc * 3 + 0) * 64 + lane], cy = pts[(jc * 3 + 1) * 64 + lane], cz = pts[(jc * 3 + 2) * 64 + lane];
+  // radial range of the block's chords (a chord point is within hmax/2 of an endpoint)
+  const float rmin = fmaxf((float)fsqrt(r2min) - half_h, 0.0f);
+  const float rmax = (float)fsqrt(r2max);
+  // clamp in float first: fminf/fmaxf map NaN to the bound, so the index is in range
+  const int b_lo = (int)fminf(fmaxf(rmin, 0.0f), (float)(kTabBins - 1));
+  const int b_hi = (int)fminf(fmaxf(rmax, 0.0f), (float)(kTabBins - 1));
+  const int L0 = L.ltab[b_lo] & 0xff, L1p = L.ltab[b_hi] >> 8;
+  const bool z_in = MODE != 0 || COUNT || !((float)cz > z_hi || (float)cz < z_lo);
+  const int n_lay = on && z_in ? max(L1p - L0, 0) : 0;
+  const float phic = sector_atan2((float)cy, (float)cx);
+  int n_items = 0;   // survivors: items[0, n_items)
+  int n_stage = 0;   // staged candidates: items[n_items, n_items + n_stage)
+  for (int dl = 0; __ballot(dl < n_lay) != 0; ++dl) {
+    const bool has = dl < n_lay;
+    const int l = has ? L0 + dl : 0;
+    const float psic = wrap_pi(phic - L.slope[l] * (float)cz);
+    int sect = (int)((psic + kPi) * (kSectors / (2.0f * kPi)));
+    sect = sect < 0 ? 0 : (sect > kSectors - 1 ? kSectors - 1 : sect);
+    const uint32_t ent = has ? (uint32_t)L.sect[l * kSectors + sect] : 0u;
+    const int lb = L.loff[l], nl = L.loff[l + 1] - lb;
+    const bool all = ent == kSectAll;
+    const int start = all ? 0 : (int)(ent & 511u), cnt = all ? nl : (int)(ent >> 9);
+    // the run's first item and the step at which it wraps to the layer's first hit,
+    // formed before the loop (so the loop waits on none of the table reads)
+    const uint32_t first = ((uint32_t)lane << 16) | (uint32_t)(lb + start);
+    const int wrap = nl - start;
+    for (int k = 0;; ++k) {
+      const bool act = k < cnt;
+      const uint64_t m = __ballot(act);
+      if (m == 0) break;
+      const int off = k < wrap ? k : k - nl;
+      if (act) items[n_items + n_stage + lane_rank(m)] = first + (uint32_t)off;
+      n_stage += (int)__popcll(m);
+      if (n_items + n_stage > kCap - 64) {
+        n_items = test_staged<R, COUNT>(items, n_items, n_items + n_stage, pts, L.hits, jc, Kcull, lane, nb, w_tests,
+                                        w_chords);
+        n_stage = 0;
+        if (n_items > kCap - 64) {
+          flush_items<R, B, TILE, MODE, Y_FIRST>(items, n_items, pts, L.hits, slab, touch, lane, nb, step0, sqrt_lam);
+          n_items = 0;
+        }
+      }
+    }
+  }
+  if (n_stage)
+    n_items = test_staged<R, COUNT>(items, n_items, n_items + n_stage, pts, L.hits, jc, Kcull, lane, nb, w_tests,
+                                    w_chords);
+  if (n_items) flush_items<R, B, TILE, MODE, Y_FIRST>(items, n_items, pts, L.hits, slab, touch, lane, nb, step0, sqrt_lam);
+}
+
+// Results of a chunk's lanes from their slab column, read and reset at the marked rows.
+// MODE 0: score (Eq. 1, FP64), n_in and the chunk's argmin (E, then index).
+template <typename R, int TILE, typename S>
+__device__ __forceinline__ void finish_scan(const ScanArgs& a, const EventLds<R>& L, S* slab, const uint32_t* touch,
+                                            int lane, int nh, int seg, int64_t ch, bool valid) {
+  const LaneSlot q = lane_slot(a, seg, ch, lane, nullptr);
+  double E = 0.0;
+  int cnt = 0;
+  for (int i = 0; i < nh; ++i) {
+    // rows without a mark were not written in this chunk: +inf, nothing to reset
+    R m2 = (R)INFINITY;
+    if ((touch[i >> 5] >> (i & 31)) & 1u) {
+      m2 = load_coherent(slab + (size_t)i * TILE + lane);
+      slab[(size_t)i * TILE + lane] = (R)INFINITY;
+    }
+    if (valid) {
+      const double r = sqrt((double)m2) - (double)L.hits[i].drift;
+      const double tq = r * r;
+      if (tq < a.lambda) {
+        E += tq;
+        ++cnt;
+      } else {
+        E += a.lambda;
+      }
+    }
+  }
+  if (!valid) E = INFINITY;
+  __threadfence_block();   // the resets land before the next chunk's minima
+  long long idx = q.in_tile ? (long long)q.gidx : (long long)0x7fffffffffffffffLL;
+  if (q.in_tile) {
+    if (a.score) a.score[q.gidx] = E;
+    if (a.nin) a.nin[q.gidx] = cnt;
+  }
+  double be = q.in_tile ? E : INFINITY;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const double oe = __shfl_xor(be, o, 64);
+    const long long oi = __shfl_xor(idx, o, 64);
+    if (oe < be || (oe == be && oi < idx)) {
+      be = oe;
+      idx = oi;
+    }
+  }
+  if (lane == 0) {
+    a.parts[ch - a.chunk0].e = be;
+    a.parts[ch - a.chunk0].idx = idx;
+  }
+}
+
+// MODE 1: inlier residuals (original hit order) and argmin chords.
+template <typename R, int TILE, typename S>
+__device__ __forceinline__ void finish_refine(const ScanArgs& a, const EventLds<R>& L, S* slab, const uint32_t* touch,
+                                              int lane, int hbase, int nh, int seg, int64_t ch, bool valid) {
+  const LaneSlot q = lane_slot(a, seg, ch, lane, nullptr);
+  if (q.in_tile) {
+    const int64_t base = a.base_of ? a.base_of[q.gidx] : q.gidx;
+    uint8_t* mrow = a.mask + (size_t)base * a.max_hits;
+    float* rrow = a.resid + (size_t)q.gidx * a.max_hits;
+    int32_t* arow = a.argmin_step + (size_t)q.gidx * a.max_hits;
+    double ph = 0.0;
+    for (int i = 0; i < nh; ++i) {
+      unsigned long long key = 0xffffffffffffffffULL;
+      if ((touch[i >> 5] >> (i & 31)) & 1u) {
+        key = load_coherent(slab + (size_t)i * TILE + lane);
+        slab[(size_t)i * TILE + lane] = 0xffffffffffffffffULL;
+      }
+      // no block came within the cull reach: the distance is beyond it (+inf here)
+      const float d2 = key == 0xffffffffffffffffULL ? INFINITY : __uint_as_float((unsigned)(key >> 32));
+      const double r = sqrt((double)d2) - (double)L.hits[i].drift;
+      const int o = a.hits_orig[hbase + i];
+      bool in;
+      if (a.define_mask) {
+        in = valid && (r * r < a.lambda);
+        mrow[o] = in ? 1 : 0;
+      } else {
+        in = valid && mrow[o] != 0;
+      }
+      rrow[o] = in ? (float)r : NAN;
+      arow[o] = (in && key != 0xffffffffffffffffULL) ? (int32_t)(unsigned)(key & 0xffffffffu) : -1;
+      if (in) ph += r * r;
+    }
+    for (int i = nh; i < a.max_hits; ++i) {
+      if (a.define_mask) mrow[i] = 0;   // the whole row is defined, unused columns 0
+      rrow[i] = NAN;
+      arow[i] = -1;
+    }
+    a.phi[q.gidx] = valid ? ph : INFINITY;
+  } else {
+    for (int i = 0; i < nh; ++i)
+      if ((touch[i >> 5] >> (i & 31)) & 1u) slab[(size_t)i * TILE + lane] = 0xffffffffffffffffULL;
+  }
+  __threadfence_block();
+}
+
+// What a workgroup works on (LDS, not registers held across a chunk): the part [g0, ge)
+// of its run [.., g1) that lies in one event.
+template <int WAVES>
+struct Work {
+  int64_t g0, ge, g1;
+  int64_t q0, q_end;        // the launch's queue: chunks [q0, q_end)
+  int64_t ev_end;           // the event's chunks end here
+  int64_t spare[WAVES];     // chunks of another event that waves took from the queue
+  int seg, event, hbase, nh, next, n_spare, singles, stage, done;
+};
+
+// The launch's chunks: an even share for each workgroup, and a queue for the rest. A
+// launch with at most one chunk per wave is shared out whole. One whose events each fill
+// the grid comes whole from the queue, which then stands in one event most of the time,
+// so waves take single chunks and none waits for another (16^5 FP32 seeds of one event,
+// uniform field: 9.3 ms, against 11.6 ms with half of them shared out). Smaller events
+// would send every wave of a workgroup into another event, so there 7/8 are shared out in
+// long runs and the queue evens out the ends (64 events in the field map: 97 ms, against
+// 107 ms all from the queue).
+template <int WAVES>
+__device__ __forceinline__ void start_work(const ScanArgs& a, Work<WAVES>& sh) {
+  const int64_t n = a.n_chunks_dev ? *a.n_chunks_dev : a.n_chunks;
+  const int n_seg = a.n_seg_dev ? *a.n_seg_dev : a.n_seg;
+  const int64_t grid = gridDim.x, slots = grid * WAVES;
+  const int64_t span = n > 0 ? a.segs[n_seg - 1].event - a.segs[0].event + 1 : 1;
+  const int64_t n_queue = n <= slots ? 0 : (n >= span * slots ? n : n / 8);
+  const int64_t n_shared = n - n_queue;
+  sh.event = -1;
+  sh.ge = a.chunk0 + n_shared * blockIdx.x / grid;
+  sh.g1 = a.chunk0 + n_shared * (blockIdx.x + 1) / grid;
+  sh.q0 = a.chunk0 + n_shared;
+  sh.q_end = a.chunk0 + n;
+  sh.n_spare = 0;
+}
+
+__device__ __forceinline__ int64_t queue_head(const ScanArgs& a) {
+  return (int64_t)__hip_atomic_load(a.queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The workgroup's next part (thread 0, between barriers): what is left of its run, else
+// a chunk that a wave could not use, else a run from the queue (2 chunks per wave, near
+// the end 1).
+template <int WAVES>
+__device__ __forceinline__ void next_part(const ScanArgs& a, Work<WAVES>& sh) {
+  const int n_seg = a.n_seg_dev ? *a.n_seg_dev : a.n_seg;
+  int64_t g0 = sh.ge;
+  sh.done = 0;
+  if (g0 >= sh.g1) {
+    int64_t len = 0;
+    if (sh.n_spare > 0) {
+      g0 = sh.spare[--sh.n_spare];
+      len = 1;
+    } else if (sh.q0 < sh.q_end) {
+      const int64_t left = sh.q_end - sh.q0 - queue_head(a);
+      const int64_t want = left > 4 * (int64_t)gridDim.x * WAVES ? 2 * WAVES : WAVES;
+      g0 = sh.q0 + (int64_t)atomicAdd(a.queue, (unsigned long long)want);
+      len = min(want, sh.q_end - g0);
+    }
+    if (len <= 0) {
+      sh.done = 1;
+      return;
+    }
+    sh.g1 = g0 + len;
+  }
+  const int seg = find_seg(a.segs, n_seg, g0), ev = a.segs[seg].event;
+  sh.g0 = g0;
+  sh.ev_end = a.ev_chunk[ev + 1];
+  sh.ge = min(sh.g1, sh.ev_end);
+  sh.seg = seg;
+  sh.stage = ev != sh.event;
+  sh.event = ev;
+  sh.hbase = a.ev_off[ev];
+  sh.nh = a.ev_off[ev + 1] - sh.hbase;
+  sh.next = 0;
+  sh.singles = sh.g1 == sh.ge && sh.n_spare == 0;   // a wave leaves at most one spare per part
+}
+
+// A wave's next chunk (one lane): of the workgroup's part, then, while the queue stands
+// in the same event, single chunks from there (so that the waves of a launch of one event
+// never wait for each other); -1: none.
+template <int WAVES>
+__device__ __forceinline__ int64_t next_chunk(const ScanArgs& a, Work<WAVES>& sh) {
+  int64_t ch = sh.g0 + atomicAdd(&sh.next, 1);
+  if (ch < sh.ge) return ch;
+  if (!sh.singles || sh.q0 + queue_head(a) >= min(sh.ev_end, sh.q_end)) return -1;
+  ch = sh.q0 + (int64_t)atomicAdd(a.queue, 1ULL);
+  if (ch >= sh.q_end) return -1;
+  if (ch < sh.ev_end) return ch;
+  sh.spare[atomicAdd(&sh.n_spare, 1)] = ch;   // the wave now waits for the next part
+  return -1;
+}
+
+// The slab entry that means "no minimum yet".
+template <typename S>
+__device__ __forceinline__ S slab_empty() {
+  if constexpr (std::is_same<S, unsigned long long>::value) {
+    return 0xffffffffffffffffULL;
+  } else {
+    return (S)INFINITY;
+  }
+}
+
 // VAR 0: fixed steps over the whole path; 1: fixed steps, the track ends with its
 // turn partition; 2: adaptive step size (scan mode only), turn_stop as given.
 // COUNT: the instance that also counts its work (seed-steps, sphere tests, chord
@@ -408,441 +831,205 @@ __global__ void __launch_bounds__(64 * WAVES) scan_kernel(ScanArgs a) {
   using Slab = typename std::conditional<MODE == 0, R, unsigned long long>::type;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   float2* s_field = reinterpret_cast<float2*>(smem);
-  HitRec<R>* s_hits = reinterpret_cast<HitRec<R>*>(smem + a.field_bytes);
-  uint16_t* s_ltab = reinterpret_cast<uint16_t*>(smem + a.field_bytes + a.hits_bytes);
-  uint16_t* s_sect = reinterpret_cast<uint16_t*>(smem + a.field_bytes + a.hits_bytes + kTabBins * 2);
+  EventLds<R> L;
+  L.hits = reinterpret_cast<HitRec<R>*>(smem + a.field_bytes);
+  L.ltab = reinterpret_cast<uint16_t*>(smem + a.field_bytes + a.hits_bytes);
+  L.sect = reinterpret_cast<uint16_t*>(smem + a.field_bytes + a.hits_bytes + kTabBins * 2);
   R* s_pts = reinterpret_cast<R*>(smem + a.field_bytes + a.hits_bytes + kTabBins * 2 + a.sect_bytes);
   uint32_t* s_items = reinterpret_cast<uint32_t*>(s_pts + WAVES * (B + 1) * 3 * 64);
   // small tables sized by the uploaded event set: layer offsets and twist slopes of
   // the current event, the per-wave row bitmaps
-  int* s_loff = reinterpret_cast<int*>(s_items + WAVES * kCap);
-  float* s_slope = reinterpret_cast<float*>(s_loff + a.n_layers + 1);
-  uint32_t* s_touch = reinterpret_cast<uint32_t*>(s_slope + a.n_layers);
-  __shared__ int s_tile;
-  __shared__ double s_red_e[WAVES];
-  __shared__ long long s_red_i[WAVES];
+  L.loff = reinterpret_cast<int*>(s_items + WAVES * kCap);
+  L.slope = reinterpret_cast<float*>(L.loff + a.n_layers + 1);
+  uint32_t* s_touch = reinterpret_cast<uint32_t*>(L.slope + a.n_layers);
+  __shared__ Work<WAVES> sh;
+  __shared__ int64_t s_chunk[WAVES];
+  __shared__ int s_seg[WAVES];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t n_tiles = a.n_tiles_dev ? (int64_t)*a.n_tiles_dev : a.n_tiles;
   // longest chord: every point of a block's chords lies within B hmax / 2 of its
   // middle point, and every point of a chord within hmax / 2 of one of its ends
   const double hmax = VAR == 2 ? (double)a.h_max : a.h;
   R* pts = s_pts + wave * (B + 1) * 3 * 64;
   uint32_t* items = s_items + wave * kCap;
-  Slab* slab = reinterpret_cast<Slab*>(a.mscratch) + (size_t)blockIdx.x * a.slab_stride;
+  Slab* slab = reinterpret_cast<Slab*>(a.mscratch) + (size_t)blockIdx.x * a.slab_stride + wave * 64;
   uint32_t* touch = s_touch + wave * a.touch_words;
   unsigned long long w_steps = 0, w_tests = 0, w_chords = 0;   // COUNT only
-  // every slab entry holds "no minimum yet" between tiles: written here once, then
-  // reset by the tile that read it
-  for (int64_t i = tid; i < a.slab_stride; i += TILE) {
-    if constexpr (MODE == 0)
-      slab[i] = (R)INFINITY;
-    else
-      slab[i] = 0xffffffffffffffffULL;
-  }
-  __threadfence_block();
+  bool filled = false;   // the wave's slab columns hold "no minimum yet" (between chunks)
   const R h = (R)a.h;
   const double lam = a.lambda;
-  int cur_event = -1;
   const float2* nodes = nullptr;
   if constexpr (FIELD == 1) {
     const int nn = (int)padded_field_nodes(a.field.nr, a.field.nz);
     for (int i = tid; i < nn; i += TILE) s_field[i] = a.field.nodes[i];
-    nodes = s_field;   // made visible by the first tile's barrier
+    nodes = s_field;   // made visible by the barriers before the first chunk
   }
 
+  if (tid == 0) start_work(a, sh);
   for (;;) {
-    if (tid == 0) s_tile = atomicAdd(a.tile_counter, 1);
+    __syncthreads();   // every wave is done with the part and its tables
+    if (tid == 0) next_part(a, sh);
     __syncthreads();
-    const int64_t ti = __builtin_amdgcn_readfirstlane(s_tile);
-    if (ti >= n_tiles) break;
-    const Tile t = a.tiles[ti];
-    const int ev = t.event;
-    const int hbase = a.ev_off[ev];
-    const int nh = a.ev_off[ev + 1] - hbase;
-    const HitRec<R>* ghits = hits_of<R>(a) + hbase;
-
-    if (ev != cur_event) {
-      for (int i = tid; i < nh; i += TILE) s_hits[i] = ghits[i];
-      const int32_t* loff = a.layer_off + (size_t)ev * (a.n_layers + 1);
-      for (int l = tid; l <= a.n_layers; l += TILE) s_loff[l] = loff[l];
-      // radial bins: the layers whose band, widened by the event's largest drift +
-      // sqrt(lambda) + 1 mm, meets the bin: [l0, l1p) packed as l0 | l1p << 8
-      const float D = a.ev_maxdrift[ev] + (float)sqrt(lam) + kBandMargin;
-      for (int b = tid; b < kTabBins; b += TILE) {
-        const float lo_r = (float)b, hi_r = b == kTabBins - 1 ? INFINITY : (float)(b + 1);
-        int l0 = 0;
-        while (l0 < a.n_layers && a.layer_r[l0].y + D < lo_r) ++l0;
-        int l1 = a.n_layers - 1;
-        while (l1 >= 0 && a.layer_r[l1].x - D > hi_r) --l1;
-        s_ltab[b] = (uint16_t)(l0 | ((l1 + 1) << 8));
-      }
-      // layer x twisted-azimuth sector: the circular run of a layer's hits (sorted by
-      // psi) that a block whose middle point c has psi_c = phi_c - s_l z_c in the
-      // sector can reach. A kept pair needs a wire point w within
-      // rho = d + sqrt(lambda) + margin + B h / 2 of c; then |phi_w - phi_c| <=
-      // 2 asin(rho / (2 (r_l - rho))) (radii >= r_l - rho and r_l),
-      // |z_w - z_c| <= rho, and phi_w - s_l z_w is within dev_l of the hit's psi.
-      const float rho = a.ev_maxdrift[ev] + (float)sqrt(lam) + kCullMargin + 0.5f * (float)(B * hmax);
-      const float* gpsi = a.hits_phi + hbase;
-      for (int l = tid; l < a.n_layers; l += TILE) s_slope[l] = a.layer_twist[(size_t)ev * a.n_layers + l].x;
-      for (int q = tid; q < a.n_layers * kSectors; q += TILE) {
-        const int l = q / kSectors, k = q - l * kSectors;
-        const int lb = loff[l], nl = loff[l + 1] - lb;
-        uint32_t ent = 0u;
-        if (nl > 0) {
-          const float2 tw = a.layer_twist[(size_t)ev * a.n_layers + l];
-          const float rl = a.layer_r[l].x - rho;
-          const float ratio = rl > 0.0f ? rho / (2.0f * rl) : 2.0f;
-          const float dphi = ratio < 1.0f ? 2.0f * asinf(ratio) : kPi;
-          const float W = dphi + fabsf(tw.x) * rho + tw.y + 2e-3f;
-          if (W >= kPi) {
-            ent = kSectAll;
-          } else {
-            const float a0 = -kPi + (2.0f * kPi / kSectors) * k, a1 = a0 + 2.0f * kPi / kSectors;
-            auto inside = [&](int j) {
-              const float ps = gpsi[lb + j];
-              if (ps >= a0 && ps <= a1) return true;
-              float d1 = a0 - ps, d2 = ps - a1;
-              d1 -= 2.0f * kPi * floorf(d1 / (2.0f * kPi));
-              d2 -= 2.0f * kPi * floorf(d2 / (2.0f * kPi));
-              return fminf(d1, d2) <= W;
-            };
-            int cnt = 0, start = -1;
-            bool prev = inside(nl - 1);
-            for (int j = 0; j < nl; ++j) {
-              const bool in = inside(j);
-              cnt += in;
-              if (in && !prev && start < 0) start = j;
-              prev = in;
-            }
-            if (cnt == nl) start = 0;
-            ent = cnt > 127 ? kSectAll : (cnt > 0 ? ((uint32_t)start | ((uint32_t)cnt << 9)) : 0u);
-          }
-        }
-        s_sect[q] = (uint16_t)ent;
-      }
-      cur_event = ev;
-    }
-
-    // ---- seed of this lane ------------------------------------------------------
-    const bool in_tile = tid < t.n;
-    bool valid = in_tile;
-    int64_t gidx = t.gbase + tid;
-    State<R> st;
-    {
-      double v[5];
-      if (a.seeds5) {
-        const int64_t pos = t.start + (in_tile ? tid : 0);
-#pragma unroll
-        for (int d = 0; d < 5; ++d) v[d] = a.seeds5[pos * 5 + d];
-        gidx = a.perm[pos];
-      } else {
-        window_seed(a.windows[t.window], t.start + (in_tile ? tid : 0), v);
-      }
-      const double pm = sqrt(v[2] * v[2] + v[3] * v[3] + v[4] * v[4]);
-      valid = valid && (pm >= 1e-3);
-      const double ipm = valid ? 1.0 / pm : 0.0;
-      st.x = (R)(a.R0 * cos(v[0]));
-      st.y = (R)(a.R0 * sin(v[0]));
-      st.z = (R)v[1];
-      st.tx = valid ? (R)(v[2] * ipm) : (R)1;
-      st.ty = valid ? (R)(v[3] * ipm) : (R)0;
-      st.tz = valid ? (R)(v[4] * ipm) : (R)0;
-      st.lam = valid ? (R)(kKappa * a.charge * ipm) : (R)0;
-      st.cx = st.cy = st.cz = (R)0;
-      st.ctx = st.cty = st.ctz = (R)0;
-    }
-    Prop<R, FIELD> pr;   // fixed steps: current point and the block's increments
-    pr.start(st);
-    pr.init_field(st, a.field, nodes);
-    if (lane < a.touch_words) touch[lane] = 0u;
-    __syncthreads();
-
-    constexpr bool STOP = VAR != 0;    // lanes can end before the last block
-    constexpr bool ADAPT = VAR == 2;
-    // adaptive: at most 4 L / h_min + 8 trial steps per lane (every rejection at
-    // least shortens the step, and h_min steps are always taken)
-    const int nblocks = ADAPT ? (int)((4.0 * a.path_len / a.h_min + 8.0 + B - 1) / B) : (a.n_steps + B - 1) / B;
-    const R Kcull = (R)(0.5 * B * hmax + sqrt(lam) + (double)kCullMargin);
-    const R sqrt_lam = (R)sqrt(lam);
-    // STOP (a lane's track can end early: at the end of its turn partition, the first
-    // step inside r < R0, or with adaptive steps at the end of the path): from then on
-    // the lane's state is frozen, so its later chords have zero length at that end
-    // point and cannot lower any distance; a block that starts frozen is not culled at
-    // all, and a wave whose lanes are all frozen leaves the loop (after writing the
-    // frozen state into the checkpoints still ahead, when a tape is recorded)
-    const R r0sq = (R)(a.R0 * a.R0);
-    const bool may_exit = STOP;
-    const bool stop_turn = VAR == 1 || (ADAPT && a.turn_stop);
-    bool live = valid;                          // lanes without a seed have no track to end
-    R hl = (R)a.h_max, arc = (R)0;              // adaptive: next step and path so far
-    const R path = (R)a.path_len;
-    for (int blk = 0; blk < nblocks; ++blk) {
-      if constexpr (STOP) {
-        if (may_exit && __ballot(live) == 0) {
-          if constexpr (MODE == 1) {
-            // the remaining checkpoints hold the frozen state (as if stepped on)
-            if (a.tape && in_tile) {
-              const float v13[13] = {(float)st.x, (float)st.y, (float)st.z, (float)st.cx, (float)st.cy, (float)st.cz,
-                                     (float)st.tx, (float)st.ty, (float)st.tz, (float)st.ctx, (float)st.cty,
-                                     (float)st.ctz, (float)st.lam};
-              for (int step = blk * B; step < a.n_steps; step += B) {
-                if (step % a.ckpt != 0) continue;
-                float* tp = a.tape + (size_t)(step / a.ckpt) * 13 * a.n_pos + gidx;
-#pragma unroll
-                for (int q = 0; q < 13; ++q) tp[(size_t)q * a.n_pos] = v13[q];
-              }
-            }
-          }
-          break;
-        }
-      }
-      const bool live0 = live;
-      const int nb = ADAPT ? B : min(B, a.n_steps - blk * B);
-      const int jc = nb / 2;
-      if constexpr (MODE == 1) {
-        const int step = blk * B;
-        // a checkpoint restarts the adjoint's recompute: the field there is evaluated
-        // at the stored state, as the recompute does
-        if (a.ckpt > 0 && step % a.ckpt == 0) pr.init_field(st, a.field, nodes);
-        if (a.tape && in_tile && step % a.ckpt == 0) {
-          float* tp = a.tape + (size_t)(step / a.ckpt) * 13 * a.n_pos + gidx;
-          const float v13[13] = {(float)st.x, (float)st.y, (float)st.z, (float)st.cx, (float)st.cy, (float)st.cz,
-                                 (float)st.tx, (float)st.ty, (float)st.tz, (float)st.ctx, (float)st.cty,
-                                 (float)st.ctz, (float)st.lam};
-#pragma unroll
-          for (int q = 0; q < 13; ++q) tp[(size_t)q * a.n_pos] = v13[q];
-        }
-      }
-      pts[0 * 64 + lane] = st.x;
-      pts[1 * 64 + lane] = st.y;
-      pts[2 * 64 + lane] = st.z;
-      R r2min, r2max;
-      if constexpr (ADAPT) {
-        r2min = r2max = radius2(st.x, st.y);
-#pragma unroll
-        for (int j = 1; j <= B; ++j) {
-          // one trial step; accepted when its error estimate is within the bound
-          // (or it is the smallest step), else the lane stays and retries shorter
-          if (live) {
-            const R hs = hl < path - arc ? hl : path - arc;
-            State<R> tr = st;
-            R err;
-            rkn_step_err<R, FIELD>(tr, a.field, nodes, hs, err);
-            const bool acc = err <= (R)a.tol || hs <= (R)a.h_min;
-            R g = err > (R)0 ? (R)0.9 * fsqrt(fsqrt((R)a.tol / err)) : (R)4;
-            g = g > (R)4 ? (R)4 : (g < (R)0.25 ? (R)0.25 : g);
-            if (acc) {
-              st = tr;
-              arc += hs;
-              if (hs == hl) hl *= g;   // a cut last step leaves the step size
-              live = arc < path && !(stop_turn && inside_r0(st.x, st.y, r0sq));
-            } else {
-              hl = hs * (g < (R)1 ? g : (R)1);
-            }
-            hl = hl > (R)a.h_max ? (R)a.h_max : (hl < (R)a.h_min ? (R)a.h_min : hl);
-          }
-          pts[(j * 3 + 0) * 64 + lane] = st.x;
-          pts[(j * 3 + 1) * 64 + lane] = st.y;
-          pts[(j * 3 + 2) * 64 + lane] = st.z;
-          const R r2 = radius2(st.x, st.y);
-          r2min = vmin(r2min, r2);
-          r2max = vmax(r2max, r2);
-        }
-      } else {
-        r2min = r2max = pr.r2;
-        auto take = [&](int j, bool go) {
-          if (go) pr.step(st, a.field, nodes, h);
-          pts[(j * 3 + 0) * 64 + lane] = pr.px;
-          pts[(j * 3 + 1) * 64 + lane] = pr.py;
-          pts[(j * 3 + 2) * 64 + lane] = pr.pz;
-          if constexpr (VAR == 1) live = live && !inside_r0(pr.px, pr.py, r0sq);
-          r2min = vmin(r2min, pr.r2);
-          r2max = vmax(r2max, pr.r2);
-        };
-        if (nb == B) {   // every block but a short last one: straight-line steps
-#pragma unroll
-          for (int j = 1; j <= B; ++j) take(j, !STOP || live);
-        } else {
-          for (int j = 1; j <= B; ++j) take(j, j <= nb && (!STOP || live));
-        }
-        // the block's increments go into the origin; the folded position (within an
-        // ulp of the last one) ends the block's last chord and starts the next block
-        if (!STOP || live0) {
-          pr.fold(st);
-          pts[(nb * 3 + 0) * 64 + lane] = pr.px;
-          pts[(nb * 3 + 1) * 64 + lane] = pr.py;
-          pts[(nb * 3 + 2) * 64 + lane] = pr.pz;
-          r2min = vmin(r2min, pr.r2);
-          r2max = vmax(r2max, pr.r2);
-        }
-      }
-      // the block's middle point, from this lane's own column
-      const R cx = pts[(jc * 3 + 0) * 64 + lane], cy = pts[(jc * 3 + 1) * 64 + lane],
-              cz = pts[(jc * 3 + 2) * 64 + lane];
-      // radial range of the block's chords (a chord point is within hmax/2 of an endpoint)
-      const float rmin = fmaxf((float)fsqrt(r2min) - 0.5f * (float)hmax, 0.0f);
-      const float rmax = (float)fsqrt(r2max);
-      // clamp in float first: fminf/fmaxf map NaN to the bound, so the index is in range
-      const int b_lo = (int)fminf(fmaxf(rmin, 0.0f), (float)(kTabBins - 1));
-      const int b_hi = (int)fminf(fmaxf(rmax, 0.0f), (float)(kTabBins - 1));
-      // candidates: per layer whose band meets the block's radial range, the run of
-      // hits that can reach the azimuth sector of the block's middle point. Each lane
-      // walks its own runs and stages (lane, hit) pairs in the wave's list (cheap
-      // steps, as many as the longest run in the wave); the staged pairs are then
-      // sphere-tested densely, one per lane, and the survivors kept at the list's
-      // front for the distance pass
-      const int L0 = s_ltab[b_lo] & 0xff, L1p = s_ltab[b_hi] >> 8;
-      const int n_lay = (valid && (!STOP || live0)) ? max(L1p - L0, 0) : 0;
-      const float phic = sector_atan2((float)cy, (float)cx);
-      int n_items = 0;   // survivors: items[0, n_items)
-      int n_stage = 0;   // staged candidates: items[n_items, n_items + n_stage)
-      for (int dl = 0; __ballot(dl < n_lay) != 0; ++dl) {
-        const bool has = dl < n_lay;
-        const int l = has ? L0 + dl : 0;
-        const float psic = wrap_pi(phic - s_slope[l] * (float)cz);
-        int sect = (int)((psic + kPi) * (kSectors / (2.0f * kPi)));
-        sect = sect < 0 ? 0 : (sect > kSectors - 1 ? kSectors - 1 : sect);
-        const uint32_t ent = has ? (uint32_t)s_sect[l * kSectors + sect] : 0u;
-        const int lb = s_loff[l], nl = s_loff[l + 1] - lb;
-        const bool all = ent == kSectAll;
-        const int start = all ? 0 : (int)(ent & 511u), cnt = all ? nl : (int)(ent >> 9);
-        // the run's first item and the step at which it wraps to the layer's first hit,
-        // formed before the loop (so the loop waits on none of the table reads)
-        const uint32_t first = ((uint32_t)lane << 16) | (uint32_t)(lb + start);
-        const int wrap = nl - start;
-        for (int k = 0;; ++k) {
-          const bool act = k < cnt;
-          const uint64_t m = __ballot(act);
-          if (m == 0) break;
-          const int off = k < wrap ? k : k - nl;
-          if (act) items[n_items + n_stage + lane_rank(m)] = first + (uint32_t)off;
-          n_stage += (int)__popcll(m);
-          if (n_items + n_stage > kCap - 64) {
-            n_items = test_staged<R, COUNT>(items, n_items, n_items + n_stage, pts, s_hits, jc, Kcull, lane, nb,
-                                            w_tests, w_chords);
-            n_stage = 0;
-            if (n_items > kCap - 64) {
-              flush_items<R, B, TILE, MODE>(items, n_items, pts, s_hits, slab, touch, wave, lane, nb, blk * B,
-                                            sqrt_lam);
-              n_items = 0;
-            }
-          }
-        }
-      }
-      if (n_stage)
-        n_items = test_staged<R, COUNT>(items, n_items, n_items + n_stage, pts, s_hits, jc, Kcull, lane, nb, w_tests,
-                                        w_chords);
-      if (n_items)
-        flush_items<R, B, TILE, MODE>(items, n_items, pts, s_hits, slab, touch, wave, lane, nb, blk * B, sqrt_lam);
-      if constexpr (COUNT) w_steps += (valid && (!STOP || live0)) ? nb : 0;
-    }
-    // The minima of a seed were folded by lanes of its own wave, and the slab is this
-    // workgroup's alone: a workgroup-scope release/acquire (the atomics complete at L2;
-    // the reads below bypass L1) orders them before the reads. An agent-scope fence
-    // here would write the whole L2's dirty lines back to memory at every tile.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-
-    if constexpr (MODE == 1) {
-      // ---- refinement outputs: inlier residuals (original hit order), argmin chords
-      if (in_tile) {
-        const int64_t base = a.base_of ? a.base_of[gidx] : gidx;
-        uint8_t* mrow = a.mask + (size_t)base * a.max_hits;
-        float* rrow = a.resid + (size_t)gidx * a.max_hits;
-        int32_t* arow = a.argmin_step + (size_t)gidx * a.max_hits;
-        double ph = 0.0;
-        for (int i = 0; i < nh; ++i) {
-          unsigned long long key = 0xffffffffffffffffULL;
-          if ((touch[i >> 5] >> (i & 31)) & 1u) {
-            key = load_coherent(slab + (size_t)i * TILE + tid);
-            slab[(size_t)i * TILE + tid] = 0xffffffffffffffffULL;
-          }
-          // no block came within the cull reach: the distance is beyond it (+inf here)
-          const float d2 = key == 0xffffffffffffffffULL ? INFINITY : __uint_as_float((unsigned)(key >> 32));
-          const double r = sqrt((double)d2) - (double)s_hits[i].drift;
-          const int o = a.hits_orig[hbase + i];
-          bool in;
-          if (a.define_mask) {
-            in = valid && (r * r < lam);
-            mrow[o] = in ? 1 : 0;
-          } else {
-            in = valid && mrow[o] != 0;
-          }
-          rrow[o] = in ? (float)r : NAN;
-          arow[o] = (in && key != 0xffffffffffffffffULL) ? (int32_t)(unsigned)(key & 0xffffffffu) : -1;
-          if (in) ph += r * r;
-        }
-        for (int i = nh; i < a.max_hits; ++i) {
-          if (a.define_mask) mrow[i] = 0;   // the whole row is defined, unused columns 0
-          rrow[i] = NAN;
-          arow[i] = -1;
-        }
-        a.phi[gidx] = valid ? ph : INFINITY;
-      } else {
-        for (int i = 0; i < nh; ++i)
-          if ((touch[i >> 5] >> (i & 31)) & 1u) slab[(size_t)i * TILE + tid] = 0xffffffffffffffffULL;
-      }
-      __threadfence_block();
+    if (sh.done) break;
+    if (sh.stage) {
+      stage_event<R>(a, L, sh.event, tid, TILE, B * hmax);
       __syncthreads();
-      continue;
     }
-    // ---- score (Eq. 1), in FP64 ---------------------------------------------------
-    double E = 0.0;
-    int cnt = 0;
-    for (int i = 0; i < nh; ++i) {
-      // rows without a mark were not written in this tile: +inf, nothing to reset
-      R m2 = (R)INFINITY;
-      if ((touch[i >> 5] >> (i & 31)) & 1u) {
-        m2 = load_coherent(slab + (size_t)i * TILE + tid);
-        slab[(size_t)i * TILE + tid] = (R)INFINITY;
+    for (;;) {
+      if (lane == 0) {
+        const int64_t ch = next_chunk(a, sh);
+        int sg = sh.seg;
+        if (ch >= 0)
+          while (a.segs[sg + 1].chunk0 <= ch) ++sg;
+        s_chunk[wave] = ch;
+        s_seg[wave] = sg;
       }
-      if (valid) {
-        const double r = sqrt((double)m2) - (double)s_hits[i].drift;
-        const double tq = r * r;
-        if (tq < lam) {
-          E += tq;
-          ++cnt;
-        } else {
-          E += lam;
+      wave_sync();
+      if (s_chunk[wave] < 0) break;
+      if (!filled) {
+        const int rows = (int)(a.slab_stride / TILE);
+        for (int i = 0; i < rows; ++i) slab[(size_t)i * TILE + lane] = slab_empty<Slab>();
+        filled = true;
+      }
+      State<R> st;
+      bool valid;
+      [[maybe_unused]] LaneSlot q = load_seed<R>(a, s_seg[wave], s_chunk[wave], lane, st, valid);
+      Prop<R, FIELD> pr;   // fixed steps: current point and the block's increments
+      pr.start(st);
+      pr.init_field(st, a.field, nodes);
+      for (int i = lane; i < a.touch_words; i += 64) touch[i] = 0u;
+      __threadfence_block();
+      wave_sync();
+
+      constexpr bool STOP = VAR != 0;    // lanes can end before the last block
+      constexpr bool ADAPT = VAR == 2;
+      // adaptive: at most 4 L / h_min + 8 trial steps per lane (every rejection at
+      // least shortens the step, and h_min steps are always taken)
+      const int nblocks = ADAPT ? (int)((4.0 * a.path_len / a.h_min + 8.0 + B - 1) / B) : (a.n_steps + B - 1) / B;
+      const R Kcull = (R)(0.5 * B * hmax + sqrt(lam) + (double)kCullMargin);
+      const R sqrt_lam = (R)sqrt(lam);
+      // beyond these the middle point of a block is out of every wire's reach
+      const float z_pad = (float)Kcull + a.ev_maxdrift[sh.event];
+      const float z_lo = a.wire_zmin - z_pad, z_hi = a.wire_zmax + z_pad;
+      // STOP (a lane's track can end early: at the end of its turn partition, the first
+      // step inside r < R0, or with adaptive steps at the end of the path): from then on
+      // the lane's state is frozen, so its later chords have zero length at that end
+      // point and cannot lower any distance; a block that starts frozen is not culled at
+      // all, and a wave whose lanes are all frozen leaves the loop (after writing the
+      // frozen state into the checkpoints still ahead, when a tape is recorded)
+      const R r0sq = (R)(a.R0 * a.R0);
+      const bool stop_turn = VAR == 1 || (ADAPT && a.turn_stop);
+      bool live = valid;                          // lanes without a seed have no track to end
+      R hl = (R)a.h_max, arc = (R)0;              // adaptive: next step and path so far
+      const R path = (R)a.path_len;
+      for (int blk = 0; blk < nblocks; ++blk) {
+        if constexpr (FIELD == 0 && MODE == 0 && VAR == 0 && !COUNT) {
+          // in the uniform field T_z is constant: a lane past the chamber and flying on
+          // has seen its last wire (0.1 mm: the FP32 rounding of z over a path)
+          const bool gone = !valid || ((float)st.z > z_hi + 0.1f && st.tz >= (R)0) ||
+                            ((float)st.z < z_lo - 0.1f && st.tz <= (R)0);
+          if (__ballot(!gone) == 0) break;
         }
-      }
-    }
-    if (!valid) E = INFINITY;
-    __threadfence_block();   // the resets land before the next tile's minima
-    long long idx = in_tile ? (long long)gidx : (long long)0x7fffffffffffffffLL;
-    if (in_tile) {
-      if (a.score) a.score[gidx] = E;
-      if (a.nin) a.nin[gidx] = cnt;
-    }
-    // ---- argmin of the tile (E, then index) -------------------------------------
-    double be = in_tile ? E : INFINITY;
+        if constexpr (STOP) {
+          if (__ballot(live) == 0) {
+            if constexpr (MODE == 1) {
+              // the remaining checkpoints hold the frozen state (as if stepped on)
+              if (a.tape && q.in_tile)
+                for (int step = blk * B; step < a.n_steps; step += B)
+                  if (step % a.ckpt == 0) write_tape<R>(a, step, q.gidx, st);
+            }
+            break;
+          }
+        }
+        const bool live0 = live;
+        const int nb = ADAPT ? B : min(B, a.n_steps - blk * B);
+        if constexpr (MODE == 1) {
+          const int step = blk * B;
+          // a checkpoint restarts the adjoint's recompute: the field there is evaluated
+          // at the stored state, as the recompute does
+          if (a.ckpt > 0 && step % a.ckpt == 0) pr.init_field(st, a.field, nodes);
+          if (a.tape && q.in_tile && step % a.ckpt == 0) write_tape<R>(a, step, q.gidx, st);
+        }
+        pts[0 * 64 + lane] = st.x;
+        pts[1 * 64 + lane] = st.y;
+        pts[2 * 64 + lane] = st.z;
+        R r2min, r2max;
+        if constexpr (ADAPT) {
+          r2min = r2max = radius2(st.x, st.y);
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      const double oe = __shfl_xor(be, o, 64);
-      const long long oi = __shfl_xor(idx, o, 64);
-      if (oe < be || (oe == be && oi < idx)) {
-        be = oe;
-        idx = oi;
-      }
-    }
-    if (lane == 0) {
-      s_red_e[wave] = be;
-      s_red_i[wave] = idx;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      for (int k = 1; k < WAVES; ++k)
-        if (s_red_e[k] < be || (s_red_e[k] == be && s_red_i[k] < idx)) {
-          be = s_red_e[k];
-          idx = s_red_i[k];
+          for (int j = 1; j <= B; ++j) {
+            // one trial step; accepted when its error estimate is within the bound
+            // (or it is the smallest step), else the lane stays and retries shorter
+            if (live) {
+              const R hs = hl < path - arc ? hl : path - arc;
+              State<R> tr = st;
+              R err;
+              rkn_step_err<R, FIELD>(tr, a.field, nodes, hs, err);
+              const bool acc = err <= (R)a.tol || hs <= (R)a.h_min;
+              R g = err > (R)0 ? (R)0.9 * fsqrt(fsqrt((R)a.tol / err)) : (R)4;
+              g = g > (R)4 ? (R)4 : (g < (R)0.25 ? (R)0.25 : g);
+              if (acc) {
+                st = tr;
+                arc += hs;
+                if (hs == hl) hl *= g;   // a cut last step leaves the step size
+                live = arc < path && !(stop_turn && inside_r0(st.x, st.y, r0sq));
+              } else {
+                hl = hs * (g < (R)1 ? g : (R)1);
+              }
+              hl = hl > (R)a.h_max ? (R)a.h_max : (hl < (R)a.h_min ? (R)a.h_min : hl);
+            }
+            pts[(j * 3 + 0) * 64 + lane] = st.x;
+            pts[(j * 3 + 1) * 64 + lane] = st.y;
+            pts[(j * 3 + 2) * 64 + lane] = st.z;
+            const R r2 = radius2(st.x, st.y);
+            r2min = vmin(r2min, r2);
+            r2max = vmax(r2max, r2);
+          }
+        } else {
+          r2min = r2max = pr.r2;
+          auto take = [&](int j, bool go) {
+            if (go) pr.step(st, a.field, nodes, h);
+            pts[(j * 3 + 0) * 64 + lane] = pr.px;
+            pts[(j * 3 + 1) * 64 + lane] = pr.py;
+            pts[(j * 3 + 2) * 64 + lane] = pr.pz;
+            if constexpr (VAR == 1) live = live && !inside_r0(pr.px, pr.py, r0sq);
+            r2min = vmin(r2min, pr.r2);
+            r2max = vmax(r2max, pr.r2);
+          };
+          if (nb == B) {   // every block but a short last one: straight-line steps
+#pragma unroll
+            for (int j = 1; j <= B; ++j) take(j, !STOP || live);
+          } else {
+            for (int j = 1; j <= B; ++j) take(j, j <= nb && (!STOP || live));
+          }
+          // the block's increments go into the origin; the folded position (within an
+          // ulp of the last one) ends the block's last chord and starts the next block
+          if (!STOP || live0) {
+            pr.fold(st);
+            pts[(nb * 3 + 0) * 64 + lane] = pr.px;
+            pts[(nb * 3 + 1) * 64 + lane] = pr.py;
+            pts[(nb * 3 + 2) * 64 + lane] = pr.pz;
+            r2min = vmin(r2min, pr.r2);
+            r2max = vmax(r2max, pr.r2);
+          }
         }
-      a.parts[ti].e = be;
-      a.parts[ti].idx = idx;
+        cull_block<R, B, TILE, MODE, VAR == 2, COUNT>(L, pts, items, slab, touch, lane, valid && (!STOP || live0),
+                                                      nb, blk * B, r2min, r2max, 0.5f * (float)hmax, z_lo, z_hi, Kcull,
+                                                      sqrt_lam, w_tests, w_chords);
+        if constexpr (COUNT) w_steps += (valid && (!STOP || live0)) ? nb : 0;
+      }
+      // The minima of a seed were folded by lanes of its own wave, and the slab is this
+      // workgroup's alone: a workgroup-scope release/acquire (the atomics complete at L2;
+      // the reads below bypass L1) orders them before the reads. An agent-scope fence
+      // here would write the whole L2's dirty lines back to memory at every chunk.
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      if constexpr (MODE == 1)
+        finish_refine<R, TILE>(a, L, slab, touch, lane, sh.hbase, sh.nh, s_seg[wave], s_chunk[wave], valid);
+      else
+        finish_scan<R, TILE>(a, L, slab, touch, lane, sh.nh, s_seg[wave], s_chunk[wave], valid);
     }
-    __syncthreads();
   }
   if constexpr (COUNT) {
     atomicAdd(a.work + 0, w_steps);
@@ -852,14 +1039,14 @@ __global__ void __launch_bounds__(64 * WAVES) scan_kernel(ScanArgs a) {
 }
 
 __global__ void __launch_bounds__(256)
-event_argmin_kernel(const ArgminPart* __restrict__ parts, const int32_t* __restrict__ ev_tiles,
+event_argmin_kernel(const ArgminPart* __restrict__ parts, const int64_t* __restrict__ ev_chunk, int64_t c0, int64_t c1,
                     int64_t* best_i, double* best_e) {
   const int e = blockIdx.x, tid = threadIdx.x;
-  const int t0 = ev_tiles[e], t1 = ev_tiles[e + 1];
+  const int64_t t0 = max(ev_chunk[e], c0), t1 = min(ev_chunk[e + 1], c1);
   double be = INFINITY;
   long long bi = 0x7fffffffffffffffLL;
-  for (int t = t0 + tid; t < t1; t += 256) {
-    const ArgminPart p = parts[t];
+  for (int64_t t = t0 + tid; t < t1; t += 256) {
+    const ArgminPart p = parts[t - c0];
     if (p.e < be || (p.e == be && p.idx < bi)) {
       be = p.e;
       bi = p.idx;
@@ -882,9 +1069,12 @@ event_argmin_kernel(const ArgminPart* __restrict__ parts, const int32_t* __restr
     __syncthreads();
   }
   if (tid == 0) {
+    // the first range of chunks defines the event's best, later ones lower it
     const bool none = t1 <= t0;
-    best_i[e] = none ? -1 : si[0];
-    best_e[e] = none ? INFINITY : se[0];
+    if (c0 == 0 || (!none && (best_i[e] < 0 || se[0] < best_e[e] || (se[0] == best_e[e] && si[0] < best_i[e])))) {
+      best_i[e] = none ? -1 : si[0];
+      best_e[e] = none ? INFINITY : se[0];
+    }
   }
 }
 
@@ -962,7 +1152,7 @@ static int scan_waves(const rkn_ctx* c, int precision, int B) {
 }
 
 template <typename R, int FIELD, int B, int WAVES, int MODE = 0>
-static hipError_t launch_scan_t(rkn_ctx* c, ScanArgs& a, int64_t max_tiles, bool alloc_only, DevBuf* slab_buf,
+static hipError_t launch_scan_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, bool alloc_only, DevBuf* slab_buf,
                                 void* raw_slab = nullptr, size_t raw_bytes = 0) {
   constexpr int TILE = 64 * WAVES;
   a.hits_bytes = (int)hits_lds_bytes(c, sizeof(R));
@@ -981,7 +1171,7 @@ static hipError_t launch_scan_t(rkn_ctx* c, ScanArgs& a, int64_t max_tiles, bool
   const int per_cu = resident_per_cu(c, (const void*)kern, TILE, smem);
   if (per_cu < 1) return hipErrorInvalidConfiguration;
   int64_t grid = (int64_t)per_cu * c->n_cu;
-  if (grid > max_tiles) grid = max_tiles;
+  if (grid > max_chunks) grid = max_chunks;
   if (grid < 1) grid = 1;
   a.slab_stride = (int64_t)(c->max_hits_event > 0 ? c->max_hits_event : 1) * TILE;
   const size_t per_wg = (size_t)a.slab_stride * (MODE == 0 ? sizeof(R) : sizeof(unsigned long long));
@@ -997,7 +1187,7 @@ static hipError_t launch_scan_t(rkn_ctx* c, ScanArgs& a, int64_t max_tiles, bool
     a.mscratch = slab_buf->p;
   }
   if (alloc_only) return hipSuccess;
-  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, c->stream, a.tile_counter);
+  hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(1), 0, c->stream, a.queue);
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(TILE), smem, c->stream, a);
   return hipGetLastError();
 }
@@ -1006,25 +1196,25 @@ int scan_tile(const rkn_ctx* c, const rkn_scan_params* p) {
   return 64 * scan_waves(c, p->precision, p->precision == 64 ? 4 : resolve_block_steps(c, p));
 }
 
-static hipError_t dispatch_scan(rkn_ctx* c, const rkn_scan_params* p, ScanArgs& a, int64_t max_tiles,
+static hipError_t dispatch_scan(rkn_ctx* c, const rkn_scan_params* p, ScanArgs& a, int64_t max_chunks,
                                 bool alloc_only, DevBuf* slab, void* raw_slab = nullptr, size_t raw_bytes = 0) {
   const int B = resolve_block_steps(c, p);
   if (p->precision == 64)
-    return c->field_kind == 0 ? launch_scan_t<double, 0, 4, 4>(c, a, max_tiles, alloc_only, slab, raw_slab, raw_bytes)
-                              : launch_scan_t<double, 1, 4, 4>(c, a, max_tiles, alloc_only, slab, raw_slab, raw_bytes);
+    return c->field_kind == 0 ? launch_scan_t<double, 0, 4, 4>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes)
+                              : launch_scan_t<double, 1, 4, 4>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes);
   if (c->field_kind == 0) {
-    if (B == 4) return launch_scan_t<float, 0, 4, 4>(c, a, max_tiles, alloc_only, slab, raw_slab, raw_bytes);
-    if (B == 6) return launch_scan_t<float, 0, 6, 4>(c, a, max_tiles, alloc_only, slab, raw_slab, raw_bytes);
-    return launch_scan_t<float, 0, 8, 4>(c, a, max_tiles, alloc_only, slab, raw_slab, raw_bytes);
+    if (B == 4) return launch_scan_t<float, 0, 4, 4>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes);
+    if (B == 6) return launch_scan_t<float, 0, 6, 4>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes);
+    return launch_scan_t<float, 0, 8, 4>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes);
   }
   const int W = scan_waves(c, 32, B);
   if (B == 4)
-    return W == 16 ? launch_scan_t<float, 1, 4, 16>(c, a, max_tiles, alloc_only, slab, raw_slab, raw_bytes)
-                   : launch_scan_t<float, 1, 4, 8>(c, a, max_tiles, alloc_only, slab, raw_slab, raw_bytes);
+    return W == 16 ? launch_scan_t<float, 1, 4, 16>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes)
+                   : launch_scan_t<float, 1, 4, 8>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes);
   if (B == 6)
-    return W == 12 ? launch_scan_t<float, 1, 6, 12>(c, a, max_tiles, alloc_only, slab, raw_slab, raw_bytes)
-                   : launch_scan_t<float, 1, 6, 8>(c, a, max_tiles, alloc_only, slab, raw_slab, raw_bytes);
-  return launch_scan_t<float, 1, 8, 8>(c, a, max_tiles, alloc_only, slab, raw_slab, raw_bytes);
+    return W == 12 ? launch_scan_t<float, 1, 6, 12>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes)
+                   : launch_scan_t<float, 1, 6, 8>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes);
+  return launch_scan_t<float, 1, 8, 8>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes);
 }
 
 FieldDev field_dev(const rkn_ctx* c) {
@@ -1043,13 +1233,8 @@ FieldDev field_dev(const rkn_ctx* c) {
   return f;
 }
 
-// Refinement forward pass over explicit seeds (FP32, block of 8 steps).
-hipError_t launch_refine_fwd(rkn_ctx* c, const rkn_scan_params* p, int64_t n_tiles, const Tile* d_tiles,
-                             const double* d_seeds5, const int64_t* d_perm, const int64_t* d_base_of,
-                             uint8_t* d_mask, int define_mask, float* d_resid, int32_t* d_argmin, double* d_phi,
-                             float* d_tape, int ckpt, int n_ckpt, int64_t n_pos) {
-  hipError_t e = c->r_counter.ensure(64);
-  if (e != hipSuccess) return e;
+// What every scan reads: the field, the prepared hits and the propagation parameters.
+static ScanArgs base_args(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& w) {
   ScanArgs a{};
   a.field = field_dev(c);
   a.hits32 = c->hits32.as<HitRec<float>>();
@@ -1061,17 +1246,35 @@ hipError_t launch_refine_fwd(rkn_ctx* c, const rkn_scan_params* p, int64_t n_til
   a.hits_phi = c->hits_phi.as<float>();
   a.layer_twist = c->layer_ext.as<float2>();
   a.n_layers = c->n_layers;
-  a.tiles = d_tiles;
-  a.n_tiles = n_tiles;
-  a.seeds5 = d_seeds5;
-  a.perm = d_perm;
-  a.tile_counter = c->r_counter.as<int>();
+  a.wire_zmin = c->wire_zmin;
+  a.wire_zmax = c->wire_zmax;
+  a.segs = w.segs;
+  a.n_seg = w.n_seg;
+  a.n_seg_dev = w.n_seg_dev;
+  a.ev_chunk = w.ev_chunk;
+  a.chunk0 = w.chunk0;
+  a.n_chunks = w.n_chunks;
+  a.n_chunks_dev = w.n_chunks_dev;
+  a.windows = w.windows;
+  a.seeds5 = w.seeds5;
+  a.perm = w.perm;
   a.R0 = p->R0;
   a.charge = p->charge;
   a.h = p->step_mm;
   a.lambda = p->lambda_mm2;
   a.n_steps = p->n_steps;
   a.turn_stop = p->turn_stop;
+  return a;
+}
+
+// Refinement forward pass over explicit seeds (FP32, block of 8 steps).
+hipError_t launch_refine_fwd(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& w, const int64_t* d_base_of,
+                             uint8_t* d_mask, int define_mask, float* d_resid, int32_t* d_argmin, double* d_phi,
+                             float* d_tape, int ckpt, int n_ckpt, int64_t n_pos) {
+  hipError_t e = c->r_counter.ensure(64);
+  if (e != hipSuccess) return e;
+  ScanArgs a = base_args(c, p, w);
+  a.queue = c->r_counter.as<unsigned long long>();
   a.hits_orig = c->hits_orig.as<int32_t>();
   a.base_of = d_base_of;
   a.mask = d_mask;
@@ -1084,34 +1287,16 @@ hipError_t launch_refine_fwd(rkn_ctx* c, const rkn_scan_params* p, int64_t n_til
   a.n_ckpt = n_ckpt;
   a.n_pos = n_pos;
   a.max_hits = c->max_hits_event > 0 ? c->max_hits_event : 1;
-  if (n_tiles == 0) return hipSuccess;
+  if (w.n_chunks == 0) return hipSuccess;
   static_assert(kRefineBlock == 8, "the refinement pass runs 8-step blocks");
-  return c->field_kind == 0 ? launch_scan_t<float, 0, 8, 4, 1>(c, a, n_tiles, false, &c->r_slab)
-                            : launch_scan_t<float, 1, 8, 8, 1>(c, a, n_tiles, false, &c->r_slab);
+  return c->field_kind == 0 ? launch_scan_t<float, 0, 8, 4, 1>(c, a, w.n_chunks, false, &c->r_slab)
+                            : launch_scan_t<float, 1, 8, 8, 1>(c, a, w.n_chunks, false, &c->r_slab);
 }
 
-static ScanArgs scan_args(rkn_ctx* c, const rkn_scan_params* p, const Tile* d_tiles, const WindowDev* d_windows,
-                          double* d_score, int32_t* d_nin, ArgminPart* parts, int* counter) {
-  ScanArgs a{};
-  a.field = field_dev(c);
-  a.hits32 = c->hits32.as<HitRec<float>>();
-  a.hits64 = c->hits64.as<HitRec<double>>();
-  a.ev_off = c->ev_off.as<int32_t>();
-  a.layer_off = c->layer_off.as<int32_t>();
-  a.layer_r = c->layer_r.as<float2>();
-  a.ev_maxdrift = c->ev_maxdrift.as<float>();
-  a.hits_phi = c->hits_phi.as<float>();
-  a.layer_twist = c->layer_ext.as<float2>();
-  a.n_layers = c->n_layers;
-  a.tiles = d_tiles;
-  a.windows = d_windows;
-  a.tile_counter = counter;
-  a.R0 = p->R0;
-  a.charge = p->charge;
-  a.h = p->step_mm;
-  a.lambda = p->lambda_mm2;
-  a.n_steps = p->n_steps;
-  a.turn_stop = p->turn_stop;
+static ScanArgs scan_args(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& w, double* d_score, int32_t* d_nin,
+                          ArgminPart* parts, unsigned long long* queue) {
+  ScanArgs a = base_args(c, p, w);
+  a.queue = queue;
   a.score = d_score;
   if (c->adapt) {   // set only for the adaptive scan entry point's call
     a.path_len = p->n_steps * p->step_mm;
@@ -1125,63 +1310,59 @@ static ScanArgs scan_args(rkn_ctx* c, const rkn_scan_params* p, const Tile* d_ti
   return a;
 }
 
-hipError_t launch_scan(rkn_ctx* c, const rkn_scan_params* p, int64_t n_tiles, const Tile* d_tiles,
-                       const WindowDev* d_windows, const double* d_seeds5, const int64_t* d_perm,
-                       double* d_score, int32_t* d_nin, int64_t* d_best_i, double* d_best_e,
-                       const int32_t* d_ev_tiles) {
-  hipError_t e = c->parts.ensure(sizeof(ArgminPart) * (size_t)(n_tiles > 0 ? n_tiles : 1));
+static hipError_t launch_event_argmin(rkn_ctx* c, const ScanSegs& w, const ArgminPart* parts, int64_t c0, int64_t c1,
+                                      int64_t* d_best_i, double* d_best_e) {
+  if (c->n_events > 0)
+    hipLaunchKernelGGL(event_argmin_kernel, dim3(c->n_events), dim3(256), 0, c->stream, parts, w.ev_chunk, c0, c1,
+                       d_best_i, d_best_e);
+  return hipGetLastError();
+}
+
+hipError_t launch_scan(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& w, double* d_score, int32_t* d_nin,
+                       int64_t* d_best_i, double* d_best_e) {
+  hipError_t e = c->parts.ensure(sizeof(ArgminPart) * (size_t)(w.n_chunks > 0 ? w.n_chunks : 1));
   if (e != hipSuccess) return e;
   e = c->counter.ensure(64);
   if (e != hipSuccess) return e;
-  ScanArgs a = scan_args(c, p, d_tiles, d_windows, d_score, d_nin, c->parts.as<ArgminPart>(), c->counter.as<int>());
-  a.n_tiles = n_tiles;
-  a.seeds5 = d_seeds5;
-  a.perm = d_perm;
-  if (n_tiles > 0) {
-    e = dispatch_scan(c, p, a, n_tiles, false, &c->mscratch);
+  ScanArgs a = scan_args(c, p, w, d_score, d_nin, c->parts.as<ArgminPart>(), c->counter.as<unsigned long long>());
+  if (w.n_chunks > 0) {
+    e = dispatch_scan(c, p, a, w.n_chunks, false, &c->mscratch);
     if (e != hipSuccess) return e;
   }
-  if (c->n_events > 0) {
-    hipLaunchKernelGGL(event_argmin_kernel, dim3(c->n_events), dim3(256), 0, c->stream,
-                       c->parts.as<ArgminPart>(), d_ev_tiles, d_best_i, d_best_e);
-  }
-  return hipGetLastError();
+  return launch_event_argmin(c, w, c->parts.as<ArgminPart>(), 0, w.n_chunks, d_best_i, d_best_e);
 }
 
-hipError_t launch_scan_dev(rkn_ctx* c, const rkn_scan_params* p, int64_t max_tiles, const int32_t* d_n_tiles,
-                           const Tile* d_tiles, const WindowDev* d_windows, double* d_score, int32_t* d_nin,
-                           int64_t* d_best_i, double* d_best_e, const int32_t* d_ev_tiles, bool alloc_only,
-                           const ScanScratch* scratch) {
+hipError_t launch_scan_dev(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& w, double* d_score, int32_t* d_nin,
+                           int64_t* d_best_i, double* d_best_e, bool alloc_only, const ScanScratch* scratch) {
   const ScanScratch own{&c->b_parts, &c->b_counter, &c->b_slab};
   const ScanScratch& s = scratch ? *scratch : own;
-  hipError_t e = s.parts->ensure(sizeof(ArgminPart) * (size_t)(max_tiles > 0 ? max_tiles : 1));
+  hipError_t e = s.parts->ensure(sizeof(ArgminPart) * (size_t)(w.n_chunks > 0 ? w.n_chunks : 1));
   if (e != hipSuccess) return e;
   e = s.counter->ensure(64);
   if (e != hipSuccess) return e;
-  ScanArgs a = scan_args(c, p, d_tiles, d_windows, d_score, d_nin, s.parts->as<ArgminPart>(), s.counter->as<int>());
-  a.n_tiles = max_tiles;
-  a.n_tiles_dev = d_n_tiles;
-  e = dispatch_scan(c, p, a, max_tiles, alloc_only, s.slab);
+  ScanArgs a = scan_args(c, p, w, d_score, d_nin, s.parts->as<ArgminPart>(), s.counter->as<unsigned long long>());
+  e = dispatch_scan(c, p, a, w.n_chunks, alloc_only, s.slab);
   if (e != hipSuccess || alloc_only) return e;
-  hipLaunchKernelGGL(event_argmin_kernel, dim3(c->n_events), dim3(256), 0, c->stream,
-                     s.parts->as<ArgminPart>(), d_ev_tiles, d_best_i, d_best_e);
-  return hipGetLastError();
+  return launch_event_argmin(c, w, s.parts->as<ArgminPart>(), 0, w.n_chunks, d_best_i, d_best_e);
 }
 
-hipError_t launch_scan_raw(rkn_ctx* c, const rkn_scan_params* p, int64_t n_tiles, const Tile* d_tiles,
-                           const WindowDev* d_windows, double* d_score, int32_t* d_nin, int64_t* d_best_i,
-                           double* d_best_e, const int32_t* d_ev_tiles, ArgminPart* d_parts, int* d_counter,
-                           void* d_slab, size_t slab_bytes) {
-  ScanArgs a = scan_args(c, p, d_tiles, d_windows, d_score, d_nin, d_parts, d_counter);
-  a.n_tiles = n_tiles;
-  if (n_tiles > 0) {
-    const hipError_t e = dispatch_scan(c, p, a, n_tiles, false, nullptr, d_slab, slab_bytes);
+hipError_t launch_scan_raw(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& w, double* d_score, int32_t* d_nin,
+                           int64_t* d_best_i, double* d_best_e, ArgminPart* d_parts, int64_t max_parts,
+                           unsigned long long* d_queue, void* d_slab, size_t slab_bytes) {
+  // as many launches as the argmin partials need; each lowers the events' best
+  for (int64_t c0 = 0; c0 < w.n_chunks || c0 == 0; c0 += max_parts) {
+    ScanSegs part = w;
+    part.chunk0 = c0;
+    part.n_chunks = std::min(max_parts, w.n_chunks - c0);
+    ScanArgs a = scan_args(c, p, part, d_score, d_nin, d_parts, d_queue);
+    if (part.n_chunks > 0) {
+      const hipError_t e = dispatch_scan(c, p, a, part.n_chunks, false, nullptr, d_slab, slab_bytes);
+      if (e != hipSuccess) return e;
+    }
+    const hipError_t e = launch_event_argmin(c, w, d_parts, c0, c0 + part.n_chunks, d_best_i, d_best_e);
     if (e != hipSuccess) return e;
   }
-  if (c->n_events > 0)
-    hipLaunchKernelGGL(event_argmin_kernel, dim3(c->n_events), dim3(256), 0, c->stream, d_parts, d_ev_tiles,
-                       d_best_i, d_best_e);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 size_t scan_slab_bytes_per_workgroup(const rkn_ctx* c, const rkn_scan_params* p) {
