@@ -111,6 +111,7 @@ rkn_status classify(rkn_ctx* c, const rkn_scan_params* q, int64_t n, const int32
   segs.n_seg = (int)list.segs.size() - 1;
   segs.ev_chunk = c->cl_evc.as<int64_t>();
   segs.n_chunks = list.chunks;
+  segs.max_lanes = list.max_lanes;
   segs.seeds5 = c->cl_seeds.as<double>();
   segs.perm = c->cl_perm.as<int64_t>();
   if (e == hipSuccess)

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -212,6 +213,7 @@ struct rkn_ctx {
   rkn_scan_params r_params{};
   int64_t r_n = 0, r_nchunks = 0, r_nchunks6 = 0;
   int r_nseg = 0;   // events with seeds
+  int r_lanes = 0, r_lanes6 = 0;   // seeds (trials) of a chunk at most
   int r_ckpt = 64, r_nckpt = 0;
   float r_tune_ms[4] = {0, 0, 0, 0};   // adjoint sweep times of the checkpoint tuner
   rkn::DevBuf r_seeds, r_seeds0, r_trials, r_event, r_segs, r_segs6, r_evc, r_evc6, r_ident, r_base6, r_mask, r_resid,
@@ -250,6 +252,7 @@ struct ScanSegs {
   const WindowDev* windows = nullptr;   // [n_seg]
   const double* seeds5 = nullptr;       // explicit seeds [n][5] in scan order
   const int64_t* perm = nullptr;        // scan order -> output index (explicit seeds)
+  int max_lanes = kChunk;               // seeds of a chunk at most
 };
 
 // Host-built segments of a scan, ordered by event.
@@ -257,11 +260,13 @@ struct SegList {
   std::vector<Seg> segs;
   std::vector<int64_t> ev_chunk;   // [n_events + 1]
   int64_t chunks = 0, seeds = 0;
+  int max_lanes = 0;               // seeds of a chunk at most
   explicit SegList(int n_events) : ev_chunk((size_t)n_events + 1, 0) {}
   void add(int event, int64_t size) {
     open(event);
     segs.push_back(Seg{seeds, size, chunks, event, 0});
     seeds += size;
+    max_lanes = std::max(max_lanes, (int)std::min<int64_t>(size, kChunk));
     chunks += (size + kChunk - 1) / kChunk;
   }
   void close() {

@@ -719,6 +719,7 @@ hipError_t refine_forward(rkn_ctx* c, bool trials, int define_mask, bool tape) {
   w.n_seg = c->r_nseg;
   w.ev_chunk = trials ? c->r_evc6.as<int64_t>() : c->r_evc.as<int64_t>();
   w.n_chunks = trials ? c->r_nchunks6 : c->r_nchunks;
+  w.max_lanes = trials ? c->r_lanes6 : c->r_lanes;
   w.seeds5 = trials ? c->r_trials.as<double>() : c->r_seeds.as<double>();
   w.perm = c->r_ident.as<int64_t>();
   return launch_refine_fwd(c, &c->r_params, w,
@@ -829,6 +830,8 @@ rkn_status rkn_refine_setup(rkn_ctx* c, const rkn_scan_params* p, int64_t n_seed
   c->r_nseg = (int)l1.segs.size() - 1;
   c->r_nchunks = l1.chunks;
   c->r_nchunks6 = l6.chunks;
+  c->r_lanes = l1.max_lanes;
+  c->r_lanes6 = l6.max_lanes;
   std::vector<int64_t> ident(6 * n_seeds), base6(6 * n_seeds);
   for (int64_t i = 0; i < 6 * n_seeds; ++i) {
     ident[i] = i;

@@ -46,6 +46,7 @@ constexpr int kSectors = 256;         // twisted-azimuth sectors of the candidat
 // A sector entry: the run's first hit (bits 0-8) and length (bits 9-15); kSectAll
 // stands for the whole layer (a run longer than 127 hits, or a reach past pi).
 constexpr uint32_t kSectAll = 0xffffu;
+constexpr int kPipeWaves = 8;   // waves per workgroup of pipe_kernel at most
 constexpr int kTraceFold = 8;   // rkn_trace: steps between folds of the block-relative sums
 constexpr float kPi = 3.14159265358979f;
 
@@ -65,6 +66,7 @@ struct ScanArgs {
   int hits_bytes;             // LDS bytes reserved for hit records
   int field_bytes;            // LDS bytes reserved for the field map (0: uniform)
   int touch_words;            // 32-bit words of a wave's row bitmap (>= max hits / 32)
+  int n_pairs, n_con, pair_bytes;   // pipe_kernel: pairs per workgroup, consumers and LDS bytes of one
   const Seg* segs;            // [n_seg + 1]: windows (or explicit seeds' events) and their chunks
   int n_seg;
   const int32_t* n_seg_dev;   // if set, the segment count is read here (captured launches)
@@ -286,7 +288,7 @@ __device__ __forceinline__ void fold_min(S* slab, uint32_t* touch, int hh, int s
 // reduction over the G lanes. In the scan, adjacent lanes first merge their minima
 // with one row shift (half the atomics, and half their L2 write-backs, for three
 // instructions); the refinement pass folds every lane's (distance, chord) key.
-template <typename R, int B, int TILE, int MODE, bool Y_FIRST, typename S>
+template <typename R, int B, int TILE, int COLS, int MODE, bool Y_FIRST, typename S>
 __device__ __forceinline__ void flush_items(const uint32_t* items, int n_items, const R* pts,
                                             const HitRec<R>* s_hits, S* slab, uint32_t* touch, int lane,
                                             int nb, int step0, R sqrt_lam) {
@@ -298,14 +300,14 @@ __device__ __forceinline__ void flush_items(const uint32_t* items, int n_items, 
     const uint32_t it = items[done + lane];
     const int s = (int)(it >> 16), hh = (int)(it & 0xffffu);
     const HitRec<R> w = s_hits[hh];
-    R px = pts[0 * 64 + s], py = pts[1 * 64 + s], pz = pts[2 * 64 + s];
+    R px = pts[0 * COLS + s], py = pts[1 * COLS + s], pz = pts[2 * COLS + s];
     R dmin = (R)INFINITY;
     int jmin = 0;
 #pragma unroll
     for (int j = 1; j <= B; ++j) {
       if (j <= nb) {
-        const R qx = pts[(j * 3 + 0) * 64 + s], qy = pts[(j * 3 + 1) * 64 + s],
-                qz = pts[(j * 3 + 2) * 64 + s];
+        const R qx = pts[(j * 3 + 0) * COLS + s], qy = pts[(j * 3 + 1) * COLS + s],
+                qz = pts[(j * 3 + 2) * COLS + s];
         const R d2 = j > 1 && !Y_FIRST
                          ? seg_wire_d2<R, true>(px, py, pz, qx, qy, qz, w.mx, w.my, w.mz, w.ux, w.uy, w.uz, w.L)
                          : seg_wire_d2<R>(px, py, pz, qx, qy, qz, w.mx, w.my, w.mz, w.ux, w.uy, w.uz, w.L);
@@ -332,8 +334,8 @@ __device__ __forceinline__ void flush_items(const uint32_t* items, int n_items, 
     R dmin = (R)INFINITY;
     int jmin = 0;
     for (int j = sub; j < nb; j += G) {
-      const R d2 = seg_wire_d2<R>(pts[(j * 3 + 0) * 64 + s], pts[(j * 3 + 1) * 64 + s], pts[(j * 3 + 2) * 64 + s],
-                                  pts[(j * 3 + 3) * 64 + s], pts[(j * 3 + 4) * 64 + s], pts[(j * 3 + 5) * 64 + s],
+      const R d2 = seg_wire_d2<R>(pts[(j * 3 + 0) * COLS + s], pts[(j * 3 + 1) * COLS + s], pts[(j * 3 + 2) * COLS + s],
+                                  pts[(j * 3 + 3) * COLS + s], pts[(j * 3 + 4) * COLS + s], pts[(j * 3 + 5) * COLS + s],
                                   w.mx, w.my, w.mz, w.ux, w.uy, w.uz, w.L);
       if (d2 < dmin) {   // the lane's chords in increasing order: keeps the lowest on ties
         dmin = d2;
@@ -373,7 +375,7 @@ __device__ __forceinline__ void wave_sync() {
 // middle point of the owner lane's block (column jc of its points). Survivors are
 // compacted in place from items[lo] on (every lane reads its chunk before any lane
 // writes, and survivors never pass the chunk being read); returns their end.
-template <typename R, bool COUNT>
+template <typename R, int COLS, bool COUNT>
 __device__ __forceinline__ int test_staged(uint32_t* items, int lo, int hi, const R* pts, const HitRec<R>* s_hits,
                                            int jc, R Kcull, int lane, int nb, unsigned long long& w_tests,
                                            unsigned long long& w_chords) {
@@ -385,7 +387,7 @@ __device__ __forceinline__ int test_staged(uint32_t* items, int lo, int hi, cons
     wave_sync();
     const int s = (int)(it >> 16), hh = (int)(it & 0xffffu);
     const HitRec<R> w = s_hits[hh];
-    const R cx = pts[(jc * 3 + 0) * 64 + s], cy = pts[(jc * 3 + 1) * 64 + s], cz = pts[(jc * 3 + 2) * 64 + s];
+    const R cx = pts[(jc * 3 + 0) * COLS + s], cy = pts[(jc * 3 + 1) * COLS + s], cz = pts[(jc * 3 + 2) * COLS + s];
     const R rx = cx - w.mx, ry = cy - w.my, rz = cz - w.mz;
     const R tt = rx * w.ux + ry * w.uy + rz * w.uz;
     const R d2 = rx * rx + ry * ry + rz * rz - tt * tt;
@@ -553,7 +555,8 @@ __device__ __forceinline__ int find_seg(const Seg* segs, int n_seg, int64_t ch) 
 
 // Wire candidates of one block for the wave's 64 lanes, and the chord distances of the
 // kept pairs. Per lane: whether its block is to be culled (on), the radial range of its
-// points (r2min, r2max) and its points in column `lane` of pts.
+// points (r2min, r2max) and its points in column `lane` of pts (COLS columns; lanes past
+// them have no block).
 //
 // A block whose middle point lies outside [z_lo, z_hi] is out of every wire's reach along
 // z (a quarter of the blocks of the 6000-step paths) and has no candidates. Only the scan
@@ -565,14 +568,15 @@ __device__ __forceinline__ int find_seg(const Seg* segs, int n_seg, int64_t ch) 
 // its own runs and stages (lane, hit) pairs in the wave's list (cheap steps, as many as
 // the longest run in the wave); the staged pairs are then sphere-tested densely, one
 // per lane, and the survivors kept at the list's front for the distance pass.
-template <typename R, int B, int TILE, int MODE, bool Y_FIRST, bool COUNT, typename S>
+template <typename R, int B, int TILE, int COLS, int MODE, bool Y_FIRST, bool COUNT, typename S>
 __device__ __forceinline__ void cull_block(const EventLds<R>& L, const R* pts, uint32_t* items, S* slab,
                                            uint32_t* touch, int lane, bool on, int nb, int step0, R r2min, R r2max,
                                            float half_h, float z_lo, float z_hi, R Kcull, R sqrt_lam, unsigned long long& w_tests,
                                            unsigned long long& w_chords) {
   const int jc = nb / 2;
   // the block's middle point, from this lane's own column
-  const R cx = pts[(jc * 3 + 0) * 64 + lane], cy = pts[(jc * 3 + 1) * 64 + lane], cz = pts[(jc * 3 + 2) * 64 + lane];
+  const R cx = pts[(jc * 3 + 0) * COLS + lane], cy = pts[(jc * 3 + 1) * COLS + lane],
+          cz = pts[(jc * 3 + 2) * COLS + lane];
   // radial range of the block's chords (a chord point is within hmax/2 of an endpoint)
   const float rmin = fmaxf((float)fsqrt(r2min) - half_h, 0.0f);
   const float rmax = (float)fsqrt(r2max);
@@ -607,45 +611,55 @@ __device__ __forceinline__ void cull_block(const EventLds<R>& L, const R* pts, u
       if (act) items[n_items + n_stage + lane_rank(m)] = first + (uint32_t)off;
       n_stage += (int)__popcll(m);
       if (n_items + n_stage > kCap - 64) {
-        n_items = test_staged<R, COUNT>(items, n_items, n_items + n_stage, pts, L.hits, jc, Kcull, lane, nb, w_tests,
+        n_items = test_staged<R, COLS, COUNT>(items, n_items, n_items + n_stage, pts, L.hits, jc, Kcull, lane, nb, w_tests,
                                         w_chords);
         n_stage = 0;
         if (n_items > kCap - 64) {
-          flush_items<R, B, TILE, MODE, Y_FIRST>(items, n_items, pts, L.hits, slab, touch, lane, nb, step0, sqrt_lam);
+          flush_items<R, B, TILE, COLS, MODE, Y_FIRST>(items, n_items, pts, L.hits, slab, touch, lane, nb, step0, sqrt_lam);
           n_items = 0;
         }
       }
     }
   }
   if (n_stage)
-    n_items = test_staged<R, COUNT>(items, n_items, n_items + n_stage, pts, L.hits, jc, Kcull, lane, nb, w_tests,
+    n_items = test_staged<R, COLS, COUNT>(items, n_items, n_items + n_stage, pts, L.hits, jc, Kcull, lane, nb, w_tests,
                                     w_chords);
-  if (n_items) flush_items<R, B, TILE, MODE, Y_FIRST>(items, n_items, pts, L.hits, slab, touch, lane, nb, step0, sqrt_lam);
+  if (n_items) flush_items<R, B, TILE, COLS, MODE, Y_FIRST>(items, n_items, pts, L.hits, slab, touch, lane, nb, step0, sqrt_lam);
 }
 
 // Results of a chunk's lanes from their slab column, read and reset at the marked rows.
+// Rows are read U at a time: 1 where other waves hide the reads' latency (and unmarked
+// rows are then not read at all), more where the wave is alone.
 // MODE 0: score (Eq. 1, FP64), n_in and the chunk's argmin (E, then index).
-template <typename R, int TILE, typename S>
+template <typename R, int TILE, int U, typename S>
 __device__ __forceinline__ void finish_scan(const ScanArgs& a, const EventLds<R>& L, S* slab, const uint32_t* touch,
                                             int lane, int nh, int seg, int64_t ch, bool valid) {
   const LaneSlot q = lane_slot(a, seg, ch, lane, nullptr);
   double E = 0.0;
   int cnt = 0;
-  for (int i = 0; i < nh; ++i) {
-    // rows without a mark were not written in this chunk: +inf, nothing to reset
-    R m2 = (R)INFINITY;
-    if ((touch[i >> 5] >> (i & 31)) & 1u) {
-      m2 = load_coherent(slab + (size_t)i * TILE + lane);
-      slab[(size_t)i * TILE + lane] = (R)INFINITY;
+  for (int i0 = 0; i0 < nh; i0 += U) {
+    R m2[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u;
+      m2[u] = (R)INFINITY;
+      // rows without a mark were not written in this chunk: +inf, nothing to reset
+      if (i < nh && (U > 1 || ((touch[i >> 5] >> (i & 31)) & 1u))) m2[u] = load_coherent(slab + (size_t)i * TILE + lane);
     }
-    if (valid) {
-      const double r = sqrt((double)m2) - (double)L.hits[i].drift;
-      const double tq = r * r;
-      if (tq < a.lambda) {
-        E += tq;
-        ++cnt;
-      } else {
-        E += a.lambda;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u;
+      if (i >= nh) break;
+      if ((touch[i >> 5] >> (i & 31)) & 1u) slab[(size_t)i * TILE + lane] = (R)INFINITY;
+      if (valid) {
+        const double r = sqrt((double)m2[u]) - (double)L.hits[i].drift;
+        const double tq = r * r;
+        if (tq < a.lambda) {
+          E += tq;
+          ++cnt;
+        } else {
+          E += a.lambda;
+        }
       }
     }
   }
@@ -673,7 +687,7 @@ __device__ __forceinline__ void finish_scan(const ScanArgs& a, const EventLds<R>
 }
 
 // MODE 1: inlier residuals (original hit order) and argmin chords.
-template <typename R, int TILE, typename S>
+template <typename R, int TILE, int U, typename S>
 __device__ __forceinline__ void finish_refine(const ScanArgs& a, const EventLds<R>& L, S* slab, const uint32_t* touch,
                                               int lane, int hbase, int nh, int seg, int64_t ch, bool valid) {
   const LaneSlot q = lane_slot(a, seg, ch, lane, nullptr);
@@ -683,26 +697,40 @@ __device__ __forceinline__ void finish_refine(const ScanArgs& a, const EventLds<
     float* rrow = a.resid + (size_t)q.gidx * a.max_hits;
     int32_t* arow = a.argmin_step + (size_t)q.gidx * a.max_hits;
     double ph = 0.0;
-    for (int i = 0; i < nh; ++i) {
-      unsigned long long key = 0xffffffffffffffffULL;
-      if ((touch[i >> 5] >> (i & 31)) & 1u) {
-        key = load_coherent(slab + (size_t)i * TILE + lane);
-        slab[(size_t)i * TILE + lane] = 0xffffffffffffffffULL;
+    for (int i0 = 0; i0 < nh; i0 += U) {
+      unsigned long long key[U];
+      int o[U];
+      uint8_t set[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u;
+        key[u] = 0xffffffffffffffffULL;
+        if (i >= nh) continue;
+        if (U > 1 || ((touch[i >> 5] >> (i & 31)) & 1u)) key[u] = load_coherent(slab + (size_t)i * TILE + lane);
+        o[u] = a.hits_orig[hbase + i];
       }
-      // no block came within the cull reach: the distance is beyond it (+inf here)
-      const float d2 = key == 0xffffffffffffffffULL ? INFINITY : __uint_as_float((unsigned)(key >> 32));
-      const double r = sqrt((double)d2) - (double)L.hits[i].drift;
-      const int o = a.hits_orig[hbase + i];
-      bool in;
-      if (a.define_mask) {
-        in = valid && (r * r < a.lambda);
-        mrow[o] = in ? 1 : 0;
-      } else {
-        in = valid && mrow[o] != 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i0 + u < nh && !a.define_mask) set[u] = mrow[o[u]];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u;
+        if (i >= nh) break;
+        if ((touch[i >> 5] >> (i & 31)) & 1u) slab[(size_t)i * TILE + lane] = 0xffffffffffffffffULL;
+        // no block came within the cull reach: the distance is beyond it (+inf here)
+        const float d2 = key[u] == 0xffffffffffffffffULL ? INFINITY : __uint_as_float((unsigned)(key[u] >> 32));
+        const double r = sqrt((double)d2) - (double)L.hits[i].drift;
+        bool in;
+        if (a.define_mask) {
+          in = valid && (r * r < a.lambda);
+          mrow[o[u]] = in ? 1 : 0;
+        } else {
+          in = valid && set[u] != 0;
+        }
+        rrow[o[u]] = in ? (float)r : NAN;
+        arow[o[u]] = (in && key[u] != 0xffffffffffffffffULL) ? (int32_t)(unsigned)(key[u] & 0xffffffffu) : -1;
+        if (in) ph += r * r;
       }
-      rrow[o] = in ? (float)r : NAN;
-      arow[o] = (in && key != 0xffffffffffffffffULL) ? (int32_t)(unsigned)(key & 0xffffffffu) : -1;
-      if (in) ph += r * r;
     }
     for (int i = nh; i < a.max_hits; ++i) {
       if (a.define_mask) mrow[i] = 0;   // the whole row is defined, unused columns 0
@@ -1013,7 +1041,7 @@ __global__ void __launch_bounds__(64 * WAVES) scan_kernel(ScanArgs a) {
             r2max = vmax(r2max, pr.r2);
           }
         }
-        cull_block<R, B, TILE, MODE, VAR == 2, COUNT>(L, pts, items, slab, touch, lane, valid && (!STOP || live0),
+        cull_block<R, B, TILE, 64, MODE, VAR == 2, COUNT>(L, pts, items, slab, touch, lane, valid && (!STOP || live0),
                                                       nb, blk * B, r2min, r2max, 0.5f * (float)hmax, z_lo, z_hi, Kcull,
                                                       sqrt_lam, w_tests, w_chords);
         if constexpr (COUNT) w_steps += (valid && (!STOP || live0)) ? nb : 0;
@@ -1026,15 +1054,201 @@ __global__ void __launch_bounds__(64 * WAVES) scan_kernel(ScanArgs a) {
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
       if constexpr (MODE == 1)
-        finish_refine<R, TILE>(a, L, slab, touch, lane, sh.hbase, sh.nh, s_seg[wave], s_chunk[wave], valid);
+        finish_refine<R, TILE, 1>(a, L, slab, touch, lane, sh.hbase, sh.nh, s_seg[wave], s_chunk[wave], valid);
       else
-        finish_scan<R, TILE>(a, L, slab, touch, lane, sh.nh, s_seg[wave], s_chunk[wave], valid);
+        finish_scan<R, TILE, 1>(a, L, slab, touch, lane, sh.nh, s_seg[wave], s_chunk[wave], valid);
     }
   }
   if constexpr (COUNT) {
     atomicAdd(a.work + 0, w_steps);
     atomicAdd(a.work + 1, w_tests);
     atomicAdd(a.work + 2, w_chords);
+  }
+}
+
+// The same scan for launches of few chunks, where a chunk's 6000 dependent steps and not
+// the chip's rate set the time: propagation and culling run side by side. A pair is one
+// producer wave, which only steps its seeds and writes the points of C blocks per phase
+// into one of two LDS buffers, and C consumer waves, which cull and compare one block each
+// of the phase before. A workgroup holds a.n_pairs pairs (chunks of any events) that share
+// the field map; the producers come first, so that they sit on different SIMDs. COLS:
+// columns of the points (seeds of a chunk at most).
+// Same blocks, lists and arithmetic per chunk as scan_kernel: the same results.
+//
+// What bounds it is the producer's chain, about 930 cycles per step in the field map (138
+// VALU instructions of one wave, 4 cycles each, and two LDS lookups). One wave doing both
+// took 1800: 96 seeds of 6000 steps 4.5 -> 2.3 ms with 7 consumers (3.7 with 1, 2.6 with
+// 2), 6^5 FP64 seeds in the uniform field 1.07 -> 0.37 ms, the refinement's forward pass
+// over 512 events of 8 seeds 6.7 -> 3.0 ms (two pairs per CU, one round instead of two).
+template <typename R, int FIELD, int B, int COLS, int MODE, int VAR>
+__global__ void __launch_bounds__(64 * kPipeWaves) pipe_kernel(ScanArgs a) {
+  using Slab = typename std::conditional<MODE == 0, R, unsigned long long>::type;
+  constexpr int kPts = (B + 1) * 3 * COLS;   // points of one block
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ int s_blocks[2][kPipeWaves];   // blocks written in a phase, per pair
+  const int C = a.n_con;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n_pairs = a.n_pairs;
+  const bool producer = wave < n_pairs;
+  const int pair = producer ? wave : (wave - n_pairs) / C;
+  const int con = producer ? 0 : (wave - n_pairs) % C;
+  const int sub = producer ? 0 : 1 + con;   // the wave's number within its pair
+  float2* s_field = reinterpret_cast<float2*>(smem);
+  unsigned char* mine = smem + a.field_bytes + (size_t)pair * a.pair_bytes;
+  EventLds<R> L;
+  L.hits = reinterpret_cast<HitRec<R>*>(mine);
+  R* s_pts = reinterpret_cast<R*>(mine + a.hits_bytes);
+  R* s_r2 = s_pts + 2 * C * kPts;          // per block: r2min (-1: not to be culled), r2max
+  L.sect = reinterpret_cast<uint16_t*>(s_r2 + 2 * C * 128);
+  L.ltab = reinterpret_cast<uint16_t*>(reinterpret_cast<unsigned char*>(L.sect) + a.sect_bytes);
+  uint32_t* items = reinterpret_cast<uint32_t*>(L.ltab + kTabBins) + con * kCap;
+  uint32_t* touch = reinterpret_cast<uint32_t*>(L.ltab + kTabBins) + C * kCap;
+  L.loff = reinterpret_cast<int*>(touch + a.touch_words);
+  L.slope = reinterpret_cast<float*>(L.loff + a.n_layers + 1);
+  Slab* slab = reinterpret_cast<Slab*>(a.mscratch) + ((size_t)blockIdx.x * n_pairs + pair) * a.slab_stride;
+  const float2* nodes = nullptr;
+  if constexpr (FIELD == 1) {
+    const int nn = (int)padded_field_nodes(a.field.nr, a.field.nz);
+    for (int i = tid; i < nn; i += blockDim.x) s_field[i] = a.field.nodes[i];
+    nodes = s_field;   // made visible by the barriers before the first chunk
+  }
+  const int rows = (int)(a.slab_stride / 64);
+  for (int i = sub; i < rows; i += 1 + C) slab[(size_t)i * 64 + lane] = slab_empty<Slab>();
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): in L2 before another wave's atomics
+  const int n_seg = a.n_seg_dev ? *a.n_seg_dev : a.n_seg;
+  const int64_t n_chunks = a.n_chunks_dev ? *a.n_chunks_dev : a.n_chunks;
+  const R h = (R)a.h;
+  const double lam = a.lambda;
+  const R Kcull = (R)(0.5 * B * a.h + sqrt(lam) + (double)kCullMargin);
+  const R sqrt_lam = (R)sqrt(lam);
+  const R r0sq = (R)(a.R0 * a.R0);
+  const int nblocks = (a.n_steps + B - 1) / B;
+  constexpr bool STOP = VAR != 0;
+  int cur_event = -1;
+  for (int64_t g = blockIdx.x; g * n_pairs < n_chunks; g += gridDim.x) {
+    const bool has = g * n_pairs + pair < n_chunks;
+    const int64_t ch = a.chunk0 + min(g * n_pairs + pair, n_chunks - 1);
+    const int seg = __builtin_amdgcn_readfirstlane(find_seg(a.segs, n_seg, ch));
+    const int ev = a.segs[seg].event;
+    const int hbase = a.ev_off[ev];
+    const int nh = a.ev_off[ev + 1] - hbase;
+    __syncthreads();   // the pair is done with its last chunk's tables
+    if (ev != cur_event) stage_event<R>(a, L, ev, sub * 64 + lane, 64 * (1 + C), B * a.h);
+    cur_event = ev;
+    if (producer)
+      for (int i = lane; i < a.touch_words; i += 64) touch[i] = 0u;
+    __syncthreads();
+    const float z_pad = (float)Kcull + a.ev_maxdrift[ev];
+    const float z_lo = a.wire_zmin - z_pad, z_hi = a.wire_zmax + z_pad;
+    bool valid = false;
+    if (producer) {
+      State<R> st;
+      const LaneSlot q = load_seed<R>(a, seg, ch, lane, st, valid);
+      valid = valid && has;
+      Prop<R, FIELD> pr;
+      pr.start(st);
+      pr.init_field(st, a.field, nodes);
+      bool live = valid;   // as in scan_kernel
+      int blk = 0;
+      for (int ph = 0;; ++ph) {
+        int made = 0;
+        for (int c = 0; c < C && blk < nblocks && has; ++c) {
+          if constexpr (STOP) {
+            if (__ballot(live) == 0) {
+              if constexpr (MODE == 1) {
+                if (a.tape && q.in_tile)
+                  for (int step = blk * B; step < a.n_steps; step += B)
+                    if (step % a.ckpt == 0) write_tape<R>(a, step, q.gidx, st);
+              }
+              blk = nblocks;
+              break;
+            }
+          }
+          if constexpr (FIELD == 0 && MODE == 0 && VAR == 0) {
+            const bool gone = !valid || ((float)st.z > z_hi + 0.1f && st.tz >= (R)0) ||
+                              ((float)st.z < z_lo - 0.1f && st.tz <= (R)0);
+            if (__ballot(!gone) == 0) {
+              blk = nblocks;
+              break;
+            }
+          }
+          const bool live0 = live;
+          const int nb = min(B, a.n_steps - blk * B);
+          if constexpr (MODE == 1) {
+            const int step = blk * B;
+            if (a.ckpt > 0 && step % a.ckpt == 0) pr.init_field(st, a.field, nodes);
+            if (a.tape && q.in_tile && step % a.ckpt == 0) write_tape<R>(a, step, q.gidx, st);
+          }
+          R* pts = s_pts + ((ph & 1) * C + c) * kPts;
+          R* r2 = s_r2 + ((ph & 1) * C + c) * 128;
+          R r2min, r2max;
+          r2min = r2max = pr.r2;
+          if (COLS == 64 || lane < COLS) {
+            pts[0 * COLS + lane] = st.x;
+            pts[1 * COLS + lane] = st.y;
+            pts[2 * COLS + lane] = st.z;
+            auto take = [&](int j, bool go) {
+              if (go) pr.step(st, a.field, nodes, h);
+              pts[(j * 3 + 0) * COLS + lane] = pr.px;
+              pts[(j * 3 + 1) * COLS + lane] = pr.py;
+              pts[(j * 3 + 2) * COLS + lane] = pr.pz;
+              if constexpr (VAR == 1) live = live && !inside_r0(pr.px, pr.py, r0sq);
+              r2min = vmin(r2min, pr.r2);
+              r2max = vmax(r2max, pr.r2);
+            };
+            if (nb == B) {
+#pragma unroll
+              for (int j = 1; j <= B; ++j) take(j, !STOP || live);
+            } else {
+              for (int j = 1; j <= B; ++j) take(j, j <= nb && (!STOP || live));
+            }
+            if (!STOP || live0) {
+              pr.fold(st);
+              pts[(nb * 3 + 0) * COLS + lane] = pr.px;
+              pts[(nb * 3 + 1) * COLS + lane] = pr.py;
+              pts[(nb * 3 + 2) * COLS + lane] = pr.pz;
+              r2min = vmin(r2min, pr.r2);
+              r2max = vmax(r2max, pr.r2);
+            }
+          }
+          r2[lane] = valid && (!STOP || live0) ? r2min : (R)-1;
+          r2[64 + lane] = r2max;
+          ++blk;
+          ++made;
+        }
+        if (lane == 0) s_blocks[ph & 1][pair] = made;
+        __syncthreads();
+        int any = 0;
+        for (int k = 0; k < n_pairs; ++k) any |= s_blocks[ph & 1][k];
+        if (__builtin_amdgcn_readfirstlane(any) == 0) break;
+      }
+    } else {
+      for (int ph = 0;; ++ph) {
+        const int prev = (ph & 1) ^ 1;
+        if (ph > 0 && con < s_blocks[prev][pair]) {
+          const int blk = (ph - 1) * C + con;
+          const R* r2 = s_r2 + (prev * C + con) * 128;
+          unsigned long long w_tests = 0, w_chords = 0;
+          cull_block<R, B, 64, COLS, MODE, false, false>(L, s_pts + (prev * C + con) * kPts, items, slab, touch, lane,
+                                                   !(r2[lane] < (R)0), min(B, a.n_steps - blk * B), blk * B, r2[lane],
+                                                   r2[64 + lane], 0.5f * (float)a.h, z_lo, z_hi, Kcull, sqrt_lam,
+                                                   w_tests, w_chords);
+        }
+        __syncthreads();
+        int any = 0;
+        for (int k = 0; k < n_pairs; ++k) any |= s_blocks[ph & 1][k];
+        if (__builtin_amdgcn_readfirstlane(any) == 0) break;
+      }
+      __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the minima are in L2
+    }
+    __syncthreads();
+    if (producer && has) {
+      if constexpr (MODE == 1)
+        finish_refine<R, 64, 8>(a, L, slab, touch, lane, hbase, nh, seg, ch, valid);
+      else
+        finish_scan<R, 64, 8>(a, L, slab, touch, lane, nh, seg, ch, valid);
+      __builtin_amdgcn_s_waitcnt(0x0f70);   // the resets, before the next chunk's minima
+    }
   }
 }
 
@@ -1192,6 +1406,76 @@ static hipError_t launch_scan_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, boo
   return hipGetLastError();
 }
 
+// LDS of one pair of pipe_kernel<R, ., B, cols, ...> with C consumers.
+static size_t pair_lds_bytes(const rkn_ctx* c, size_t rsize, int B, int cols, int C) {
+  return align64(hits_lds_bytes(c, rsize) + 2 * (size_t)C * ((size_t)(B + 1) * 3 * cols + 128) * rsize +
+                 sect_table_bytes(c) + kTabBins * 2 + (size_t)C * kCap * 4 + (size_t)touch_words(c) * 4 +
+                 (size_t)(2 * std::max(c->n_layers, 1) + 1) * 4);
+}
+
+// Launches pipe_kernel if the launch suits it (false otherwise): fixed steps, and chunks
+// few enough that each CU gets at most as many pairs as its LDS holds; then each pair has
+// as many consumers as fit. Past that scan_kernel's waves fill the chip and are the faster
+// (768 chunks of 64 trials in the field map, two rounds of pairs: Gauss-Newton 43 ms
+// against 37), except where an event has at most 16 seeds: its one wave per workgroup
+// takes two rounds as well (1000 events of 8 seeds: 10.3 ms against 16.7).
+template <typename R, int FIELD, int B, int COLS, int MODE>
+static bool launch_pipe_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, bool alloc_only, DevBuf* slab_buf,
+                          void* raw_slab, size_t raw_bytes, hipError_t* err) {
+  if (a.work || a.h_max > 0 || max_chunks < 1) return false;
+  auto kern = a.turn_stop ? pipe_kernel<R, FIELD, B, COLS, MODE, 1> : pipe_kernel<R, FIELD, B, COLS, MODE, 0>;
+  const size_t field = field_lds_bytes(c, FIELD), room = (size_t)c->max_lds_block - 512;
+  auto fits = [&](int64_t pairs, int con) {   // that many pairs of con consumers on one CU
+    const size_t pair = pair_lds_bytes(c, sizeof(R), B, COLS, con);
+    return FIELD == 1 ? pairs * (1 + con) <= kPipeWaves && field + pairs * pair <= room
+                      : 1 + con <= kPipeWaves && pairs * (pair + 512) <= room && pairs * (1 + con) <= 16;
+  };
+  int64_t per_cu = (max_chunks + c->n_cu - 1) / c->n_cu;
+  if (!fits(per_cu, 1)) {
+    if (COLS > 16) return false;
+    int64_t most = kPipeWaves;
+    while (most > 0 && !fits(most, 1)) --most;
+    if (per_cu > 2 * most) return false;
+    per_cu = most;
+  }
+  const int n = FIELD == 1 ? (int)per_cu : 1;
+  int con = kPipeWaves - 1, threads = 0, resident = 0;
+  size_t pair = 0, smem = 0;
+  for (; con >= 1; --con) {
+    if (!fits(per_cu, con)) continue;
+    pair = pair_lds_bytes(c, sizeof(R), B, COLS, con);
+    smem = field + n * pair;
+    threads = 64 * n * (1 + con);
+    resident = resident_per_cu(c, (const void*)kern, threads, smem);
+    if ((int64_t)resident * n >= per_cu) break;
+  }
+  if (con < 1) return false;
+  *err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if (*err != hipSuccess) return true;
+  const int64_t groups = (max_chunks + n - 1) / n;
+  const int64_t grid = std::min(groups, (int64_t)resident * c->n_cu);
+  a.field_bytes = (int)field;
+  a.hits_bytes = (int)hits_lds_bytes(c, sizeof(R));
+  a.sect_bytes = (int)sect_table_bytes(c);
+  a.touch_words = touch_words(c);
+  a.n_pairs = n;
+  a.n_con = con;
+  a.pair_bytes = (int)pair;
+  a.slab_stride = (int64_t)(c->max_hits_event > 0 ? c->max_hits_event : 1) * 64;
+  const size_t bytes = (size_t)grid * n * a.slab_stride * (MODE == 0 ? sizeof(R) : sizeof(unsigned long long));
+  if (raw_slab) {
+    if (bytes > raw_bytes) return false;
+    a.mscratch = raw_slab;
+  } else {
+    if ((*err = slab_buf->ensure(bytes)) != hipSuccess) return true;
+    a.mscratch = slab_buf->p;
+  }
+  if (alloc_only) return true;
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), smem, c->stream, a);
+  *err = hipGetLastError();
+  return true;
+}
+
 int scan_tile(const rkn_ctx* c, const rkn_scan_params* p) {
   return 64 * scan_waves(c, p->precision, p->precision == 64 ? 4 : resolve_block_steps(c, p));
 }
@@ -1199,6 +1483,18 @@ int scan_tile(const rkn_ctx* c, const rkn_scan_params* p) {
 static hipError_t dispatch_scan(rkn_ctx* c, const rkn_scan_params* p, ScanArgs& a, int64_t max_chunks,
                                 bool alloc_only, DevBuf* slab, void* raw_slab = nullptr, size_t raw_bytes = 0) {
   const int B = resolve_block_steps(c, p);
+  hipError_t e = hipSuccess;
+  auto pipe = [&](auto launch) { return launch(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes, &e); };
+  bool done;
+  if (p->precision == 64)
+    done = c->field_kind == 0 ? pipe(launch_pipe_t<double, 0, 4, 64, 0>) : pipe(launch_pipe_t<double, 1, 4, 64, 0>);
+  else if (c->field_kind == 0)
+    done = B == 4 ? pipe(launch_pipe_t<float, 0, 4, 64, 0>)
+                  : (B == 6 ? pipe(launch_pipe_t<float, 0, 6, 64, 0>) : pipe(launch_pipe_t<float, 0, 8, 64, 0>));
+  else
+    done = B == 4 ? pipe(launch_pipe_t<float, 1, 4, 64, 0>)
+                  : (B == 6 ? pipe(launch_pipe_t<float, 1, 6, 64, 0>) : pipe(launch_pipe_t<float, 1, 8, 64, 0>));
+  if (done) return e;
   if (p->precision == 64)
     return c->field_kind == 0 ? launch_scan_t<double, 0, 4, 4>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes)
                               : launch_scan_t<double, 1, 4, 4>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes);
@@ -1289,6 +1585,13 @@ hipError_t launch_refine_fwd(rkn_ctx* c, const rkn_scan_params* p, const ScanSeg
   a.max_hits = c->max_hits_event > 0 ? c->max_hits_event : 1;
   if (w.n_chunks == 0) return hipSuccess;
   static_assert(kRefineBlock == 8, "the refinement pass runs 8-step blocks");
+  auto pipe = [&](auto launch) { return launch(c, a, w.n_chunks, false, &c->r_slab, nullptr, (size_t)0, &e); };
+  // few seeds per event (trials: 6 per seed): narrower points leave LDS for more pairs
+  const bool done = c->field_kind == 0    ? pipe(launch_pipe_t<float, 0, 8, 64, 1>)
+                    : w.max_lanes <= 16   ? pipe(launch_pipe_t<float, 1, 8, 16, 1>)
+                    : w.max_lanes <= 48   ? pipe(launch_pipe_t<float, 1, 8, 48, 1>)
+                                          : pipe(launch_pipe_t<float, 1, 8, 64, 1>);
+  if (done) return e;
   return c->field_kind == 0 ? launch_scan_t<float, 0, 8, 4, 1>(c, a, w.n_chunks, false, &c->r_slab)
                             : launch_scan_t<float, 1, 8, 8, 1>(c, a, w.n_chunks, false, &c->r_slab);
 }
