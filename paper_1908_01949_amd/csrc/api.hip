@@ -241,6 +241,7 @@ rkn_status rkn_upload_field_uniform(rkn_ctx* c, double bz) {
   if (!is_fin(bz)) return arg_err(c, "bz must be finite");
   c->field_kind = 0;
   c->bz = bz;
+  c->b_max = (float)fabs(bz);
   rkn::batch_release(c);   // captured graphs hold the previous field's kind and nodes
   c->refine_release();     // checkpoints were propagated in the previous field
   return RKN_OK;
@@ -256,6 +257,9 @@ rkn_status rkn_upload_field_rz(rkn_ctx* c, int32_t nr, int32_t nz, double r0, do
   if (!br || !bz) return arg_err(c, "NULL field array");
   for (size_t i = 0; i < (size_t)nr * nz; ++i)
     if (!std::isfinite(br[i]) || !std::isfinite(bz[i])) return arg_err(c, "non-finite field node");
+  double b_max = 0.0;   // bilinear: the largest node bounds the cell
+  for (size_t i = 0; i < (size_t)nr * nz; ++i)
+    b_max = std::max(b_max, 1.001 * sqrt((double)br[i] * br[i] + (double)bz[i] * bz[i]));
   // device layout: [nz + 1][nr + 1], the extra column and row repeating the edge
   std::vector<float2> nodes(rkn::padded_field_nodes(nr, nz));
   for (int j = 0; j <= nz; ++j)
@@ -274,6 +278,7 @@ rkn_status rkn_upload_field_rz(rkn_ctx* c, int32_t nr, int32_t nz, double r0, do
   c->z0 = z0;
   c->z1 = z1;
   c->bz = 0.0;
+  c->b_max = (float)b_max;
   rkn::batch_release(c);   // captured graphs hold the previous field's kind and nodes
   c->refine_release();     // checkpoints were propagated in the previous field
   return RKN_OK;

@@ -160,6 +160,7 @@ struct rkn_ctx {
   // field
   int field_kind = -1;               // 0 uniform, 1 rz
   double bz = 0.0;
+  float b_max = 0;                   // |B| is nowhere larger
   int nr = 0, nz = 0;
   double r0 = 0, r1 = 0, z0 = 0, z1 = 0;
   rkn::DevBuf field_nodes;           // float2 (B_r, B_z) [nz][nr]
@@ -210,6 +211,7 @@ struct rkn_ctx {
 
   // refinement (refine.hip): seeds grouped by event, inlier sets fixed at setup
   bool r_ready = false;
+  bool r_at_setup = false;             // seeds and forward outputs are still the setup pass's
   rkn_scan_params r_params{};
   int64_t r_n = 0, r_nchunks = 0, r_nchunks6 = 0;
   int r_nseg = 0;   // events with seeds
@@ -226,7 +228,7 @@ struct rkn_ctx {
                                       &r_cgrad,  &r_slab,   &r_counter, &r_tape6, &r_segoff, &r_segout, &r_accept};
   void refine_release() {
     for (rkn::DevBuf* b : refine_buffers_) b->release();
-    r_ready = false;
+    r_ready = r_at_setup = false;
   }
 
   bool set_err(const std::string& s) {

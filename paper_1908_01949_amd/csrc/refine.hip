@@ -816,6 +816,7 @@ rkn_status rkn_refine_setup(rkn_ctx* c, const rkn_scan_params* p, int64_t n_seed
   }
   hipError_t e;
   if ((e = hipSetDevice(c->device)) != hipSuccess) return rerr(c, e, "hipSetDevice");
+  c->r_at_setup = false;
   c->r_params = *p;
   c->r_params.block_steps = 8;
   c->r_n = n_seeds;
@@ -911,6 +912,7 @@ rkn_status rkn_refine_setup(rkn_ctx* c, const rkn_scan_params* p, int64_t n_seed
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return rerr(c, e, "refine setup");
   c->r_ready = true;
+  c->r_at_setup = true;
   return RKN_OK;
 }
 
@@ -937,6 +939,7 @@ rkn_status rkn_residuals_fwd(rkn_ctx* c, const double* seeds5, float* resid, dou
   const size_t n = (size_t)c->r_n, H = (size_t)(c->max_hits_event > 0 ? c->max_hits_event : 1);
   hipError_t e;
   if ((e = hipSetDevice(c->device)) != hipSuccess) return rerr(c, e, "hipSetDevice");
+  c->r_at_setup = false;
   if (seeds5 &&
       (e = hipMemcpyAsync(c->r_seeds.p, seeds5, sizeof(double) * 5 * n, dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                           c->stream)) != hipSuccess)
@@ -1012,9 +1015,13 @@ rkn_status rkn_gn_refine(rkn_ctx* c, int32_t iters, const double* scale, double*
   DevBuf phi_hist;
   if ((e = phi_hist.ensure(sizeof(double) * n * (iters + 1))) != hipSuccess) return rerr(c, e, "refine alloc");
   const dim3 g1((unsigned)((n + 255) / 256)), b1(256);
-  // start from the setup seeds; the inlier sets stay those of the setup pass
-  e = hipMemcpyAsync(c->r_seeds.p, c->r_seeds0.p, sizeof(double) * 5 * n, hipMemcpyDeviceToDevice, c->stream);
-  if (e == hipSuccess) e = refine_forward(c, false, 0, true);
+  // start from the setup seeds; the inlier sets stay those of the setup pass, whose
+  // outputs are this pass's unless another call has replaced them
+  if (!c->r_at_setup) {
+    e = hipMemcpyAsync(c->r_seeds.p, c->r_seeds0.p, sizeof(double) * 5 * n, hipMemcpyDeviceToDevice, c->stream);
+    if (e == hipSuccess) e = refine_forward(c, false, 0, true);
+  }
+  c->r_at_setup = false;
   if (e == hipSuccess)
     e = hipMemcpyAsync(c->r_phicur.p, c->r_phi.p, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream);
   const int H = c->max_hits_event > 0 ? c->max_hits_event : 1;

@@ -46,7 +46,7 @@ constexpr int kSectors = 256;         // twisted-azimuth sectors of the candidat
 // A sector entry: the run's first hit (bits 0-8) and length (bits 9-15); kSectAll
 // stands for the whole layer (a run longer than 127 hits, or a reach past pi).
 constexpr uint32_t kSectAll = 0xffffu;
-constexpr int kPipeWaves = 8;   // waves per workgroup of pipe_kernel at most
+constexpr int kPipeWaves = 12;  // waves per workgroup of pipe_kernel at most
 constexpr int kTraceFold = 8;   // rkn_trace: steps between folds of the block-relative sums
 constexpr float kPi = 3.14159265358979f;
 
@@ -61,6 +61,7 @@ struct ScanArgs {
   const float* hits_phi;      // twisted azimuth psi of each layer-ordered hit's wire centre
   const float2* layer_twist;  // [n_events][n_layers] (dphi/dz of the layer's wires, psi deviation)
   float wire_zmin, wire_zmax; // z extent of all wires
+  float b_max;                // |B| is nowhere larger
   int n_layers;
   int sect_bytes;             // LDS bytes reserved for the layer x sector table
   int hits_bytes;             // LDS bytes reserved for hit records
@@ -71,6 +72,7 @@ struct ScanArgs {
   int n_seg;
   const int32_t* n_seg_dev;   // if set, the segment count is read here (captured launches)
   const int64_t* ev_chunk;    // first chunk of each event [n_events + 1]
+  int walk;                   // 1: windows walked in scan order, lanes out of reach in z not culled
   int64_t chunk0, n_chunks;   // the chunks to scan: [chunk0, chunk0 + n_chunks)
   const int64_t* n_chunks_dev;   // if set, n_chunks is read here
   const WindowDev* windows;
@@ -503,8 +505,10 @@ __device__ __forceinline__ LaneSlot lane_slot(const ScanArgs& a, int seg, int64_
       for (int d = 0; d < 5; ++d) v[d] = a.seeds5[q.gidx * 5 + d];
     }
     q.gidx = a.perm[q.gidx];
-  } else {
+  } else if (a.walk) {
     q.gidx = sg.gbase + window_scan_seed(a.windows[seg], local, v);
+  } else if (v) {
+    window_seed(a.windows[seg], local, v);
   }
   return q;
 }
@@ -553,14 +557,109 @@ __device__ __forceinline__ int find_seg(const Seg* segs, int n_seg, int64_t ch) 
   return lo;
 }
 
+// One block of fixed steps of a wave's lanes: the points into the lanes' columns, the
+// radial range of the block (r2min, r2max), and the block's increments into the origin
+// (the folded position, within an ulp of the last one, ends the block's last chord and
+// starts the next block). VAR 1: a lane whose track ended keeps its state.
+//
+// Where no lane can come back inside r < R0 within the block (steady lanes move at most
+// 1.1 h per step), the live lanes step without a test in between, and the scheduler can
+// overlap their steps. Tested after every step, a step took half as long again: 24 events'
+// turn loop, 308 -> 292 ms.
+template <typename R, int FIELD, int B, int COLS, int VAR>
+__device__ __forceinline__ void take_block(const ScanArgs& a, const float2* nodes, State<R>& st, Prop<R, FIELD>& pr,
+                                           R* pts, int lane, int nb, R h, R r0sq, R far2, bool steady, bool& live,
+                                           R& r2min, R& r2max) {
+  const bool live0 = live;
+  pts[0 * COLS + lane] = st.x;
+  pts[1 * COLS + lane] = st.y;
+  pts[2 * COLS + lane] = st.z;
+  r2min = r2max = pr.r2;
+  auto take = [&](int j, bool go) {
+    if (go) pr.step(st, a.field, nodes, h);
+    pts[(j * 3 + 0) * COLS + lane] = pr.px;
+    pts[(j * 3 + 1) * COLS + lane] = pr.py;
+    pts[(j * 3 + 2) * COLS + lane] = pr.pz;
+    r2min = vmin(r2min, pr.r2);
+    r2max = vmax(r2max, pr.r2);
+  };
+  if constexpr (VAR == 1) {
+    if (nb == B && __ballot(live && (!steady || pr.r2 < far2)) == 0) {
+      if (live) {
+#pragma unroll
+        for (int j = 1; j <= B; ++j) take(j, true);
+      }
+    } else {
+      for (int j = 1; j <= B; ++j) {
+        take(j, j <= nb && live);
+        live = live && !inside_r0(pr.px, pr.py, r0sq);
+      }
+    }
+  } else if (nb == B) {   // every block but a short last one: straight-line steps
+#pragma unroll
+    for (int j = 1; j <= B; ++j) take(j, true);
+  } else {
+    for (int j = 1; j <= B; ++j) take(j, j <= nb);
+  }
+  if (VAR == 0 || live0) {
+    pr.fold(st);
+    pts[(nb * 3 + 0) * COLS + lane] = pr.px;
+    pts[(nb * 3 + 1) * COLS + lane] = pr.py;
+    pts[(nb * 3 + 2) * COLS + lane] = pr.pz;
+    r2min = vmin(r2min, pr.r2);
+    r2max = vmax(r2max, pr.r2);
+  }
+}
+
+// take_block for a seed on four lanes (see QuadProp): the wave's 16 seeds from column sd.
+template <int B, int COLS, int VAR>
+__device__ __forceinline__ void take_block_quad(const ScanArgs& a, const float* nodes, QuadProp& pr, float* pts, int sd,
+                                                int comp, int nb, float h, float r0sq, float far2, bool steady,
+                                                bool& live, float& r2min, float& r2max) {
+  const bool live0 = live;
+  float* col = pts + comp * COLS + sd;
+  col[0] = pr.s;
+  r2min = r2max = pr.r2;
+  auto take = [&](int j, bool go) {
+    if (go) pr.step(a.field, nodes, h);
+    col[j * 3 * COLS] = pr.p;
+    r2min = fminf(r2min, pr.r2);
+    r2max = fmaxf(r2max, pr.r2);
+  };
+  if (nb == B && (VAR == 0 || __ballot(live && (!steady || pr.r2 < far2)) == 0)) {
+    if (VAR == 0 || live) {
+#pragma unroll
+      for (int j = 1; j <= B; ++j) take(j, true);
+    }
+  } else {
+    for (int j = 1; j <= B; ++j) {
+      take(j, j <= nb && (VAR == 0 || live));
+      if constexpr (VAR == 1) live = live && !inside_r0(quad_perm<0x00>(pr.p), quad_perm<0x55>(pr.p), r0sq);
+    }
+  }
+  if (VAR == 0 || live0) {
+    pr.fold();
+    col[nb * 3 * COLS] = pr.p;
+    r2min = fminf(r2min, pr.r2);
+    r2max = fmaxf(r2max, pr.r2);
+  }
+}
+
+// Whether a lane's steps keep |T| near 1 over the whole path (the integrator's drift per
+// step is of order (h |lam B|)^5), so that none is longer than 1.1 h.
+template <typename R>
+__device__ __forceinline__ bool steady_lane(const ScanArgs& a, R lam) {
+  return a.n_steps <= 100000 && fabsf((float)lam) * (float)a.h * a.b_max < 0.02f;
+}
+
 // Wire candidates of one block for the wave's 64 lanes, and the chord distances of the
 // kept pairs. Per lane: whether its block is to be culled (on), the radial range of its
 // points (r2min, r2max) and its points in column `lane` of pts (COLS columns; lanes past
 // them have no block).
 //
-// A block whose middle point lies outside [z_lo, z_hi] is out of every wire's reach along
-// z (a quarter of the blocks of the 6000-step paths) and has no candidates. Only the scan
-// drops it: the refinement's inliers count wherever they are, and the counting instance
+// With z_skip, a block whose middle point lies outside [z_lo, z_hi] is out of every wire's
+// reach along z (a quarter of the blocks of the 6000-step paths) and has no candidates.
+// Only the scan drops it: the refinement's inliers count wherever they are, and the counting instance
 // counts the pairs of the radial and sphere rules.
 //
 // Per layer whose band meets the block's radial range, the candidates are the run of
@@ -571,7 +670,7 @@ __device__ __forceinline__ int find_seg(const Seg* segs, int n_seg, int64_t ch) 
 template <typename R, int B, int TILE, int COLS, int MODE, bool Y_FIRST, bool COUNT, typename S>
 __device__ __forceinline__ void cull_block(const EventLds<R>& L, const R* pts, uint32_t* items, S* slab,
                                            uint32_t* touch, int lane, bool on, int nb, int step0, R r2min, R r2max,
-                                           float half_h, float z_lo, float z_hi, R Kcull, R sqrt_lam, unsigned long long& w_tests,
+                                           float half_h, bool z_skip, float z_lo, float z_hi, R Kcull, R sqrt_lam, unsigned long long& w_tests,
                                            unsigned long long& w_chords) {
   const int jc = nb / 2;
   // the block's middle point, from this lane's own column
@@ -584,7 +683,7 @@ __device__ __forceinline__ void cull_block(const EventLds<R>& L, const R* pts, u
   const int b_lo = (int)fminf(fmaxf(rmin, 0.0f), (float)(kTabBins - 1));
   const int b_hi = (int)fminf(fmaxf(rmax, 0.0f), (float)(kTabBins - 1));
   const int L0 = L.ltab[b_lo] & 0xff, L1p = L.ltab[b_hi] >> 8;
-  const bool z_in = MODE != 0 || COUNT || !((float)cz > z_hi || (float)cz < z_lo);
+  const bool z_in = MODE != 0 || COUNT || !z_skip || !((float)cz > z_hi || (float)cz < z_lo);
   const int n_lay = on && z_in ? max(L1p - L0, 0) : 0;
   const float phic = sector_atan2((float)cy, (float)cx);
   int n_items = 0;   // survivors: items[0, n_items)
@@ -948,6 +1047,8 @@ __global__ void __launch_bounds__(64 * WAVES) scan_kernel(ScanArgs a) {
       const R r0sq = (R)(a.R0 * a.R0);
       const bool stop_turn = VAR == 1 || (ADAPT && a.turn_stop);
       bool live = valid;                          // lanes without a seed have no track to end
+      const R far2 = (R)((a.R0 + 1.1 * B * a.h + 1.0) * (a.R0 + 1.1 * B * a.h + 1.0));
+      const bool steady = VAR == 1 && steady_lane(a, st.lam);
       R hl = (R)a.h_max, arc = (R)0;              // adaptive: next step and path so far
       const R path = (R)a.path_len;
       for (int blk = 0; blk < nblocks; ++blk) {
@@ -978,11 +1079,11 @@ __global__ void __launch_bounds__(64 * WAVES) scan_kernel(ScanArgs a) {
           if (a.ckpt > 0 && step % a.ckpt == 0) pr.init_field(st, a.field, nodes);
           if (a.tape && q.in_tile && step % a.ckpt == 0) write_tape<R>(a, step, q.gidx, st);
         }
-        pts[0 * 64 + lane] = st.x;
-        pts[1 * 64 + lane] = st.y;
-        pts[2 * 64 + lane] = st.z;
         R r2min, r2max;
         if constexpr (ADAPT) {
+          pts[0 * 64 + lane] = st.x;
+          pts[1 * 64 + lane] = st.y;
+          pts[2 * 64 + lane] = st.z;
           r2min = r2max = radius2(st.x, st.y);
 #pragma unroll
           for (int j = 1; j <= B; ++j) {
@@ -1014,35 +1115,10 @@ __global__ void __launch_bounds__(64 * WAVES) scan_kernel(ScanArgs a) {
             r2max = vmax(r2max, r2);
           }
         } else {
-          r2min = r2max = pr.r2;
-          auto take = [&](int j, bool go) {
-            if (go) pr.step(st, a.field, nodes, h);
-            pts[(j * 3 + 0) * 64 + lane] = pr.px;
-            pts[(j * 3 + 1) * 64 + lane] = pr.py;
-            pts[(j * 3 + 2) * 64 + lane] = pr.pz;
-            if constexpr (VAR == 1) live = live && !inside_r0(pr.px, pr.py, r0sq);
-            r2min = vmin(r2min, pr.r2);
-            r2max = vmax(r2max, pr.r2);
-          };
-          if (nb == B) {   // every block but a short last one: straight-line steps
-#pragma unroll
-            for (int j = 1; j <= B; ++j) take(j, !STOP || live);
-          } else {
-            for (int j = 1; j <= B; ++j) take(j, j <= nb && (!STOP || live));
-          }
-          // the block's increments go into the origin; the folded position (within an
-          // ulp of the last one) ends the block's last chord and starts the next block
-          if (!STOP || live0) {
-            pr.fold(st);
-            pts[(nb * 3 + 0) * 64 + lane] = pr.px;
-            pts[(nb * 3 + 1) * 64 + lane] = pr.py;
-            pts[(nb * 3 + 2) * 64 + lane] = pr.pz;
-            r2min = vmin(r2min, pr.r2);
-            r2max = vmax(r2max, pr.r2);
-          }
+          take_block<R, FIELD, B, 64, VAR>(a, nodes, st, pr, pts, lane, nb, h, r0sq, far2, steady, live, r2min, r2max);
         }
         cull_block<R, B, TILE, 64, MODE, VAR == 2, COUNT>(L, pts, items, slab, touch, lane, valid && (!STOP || live0),
-                                                      nb, blk * B, r2min, r2max, 0.5f * (float)hmax, z_lo, z_hi, Kcull,
+                                                      nb, blk * B, r2min, r2max, 0.5f * (float)hmax, a.walk, z_lo, z_hi, Kcull,
                                                       sqrt_lam, w_tests, w_chords);
         if constexpr (COUNT) w_steps += (valid && (!STOP || live0)) ? nb : 0;
       }
@@ -1068,31 +1144,34 @@ __global__ void __launch_bounds__(64 * WAVES) scan_kernel(ScanArgs a) {
 
 // The same scan for launches of few chunks, where a chunk's 6000 dependent steps and not
 // the chip's rate set the time: propagation and culling run side by side. A pair is one
-// producer wave, which only steps its seeds and writes the points of C blocks per phase
-// into one of two LDS buffers, and C consumer waves, which cull and compare one block each
-// of the phase before. A workgroup holds a.n_pairs pairs (chunks of any events) that share
-// the field map; the producers come first, so that they sit on different SIMDs. COLS:
-// columns of the points (seeds of a chunk at most).
+// chunk's producer waves, which only step its seeds and write the points of C blocks per
+// phase into one of two LDS buffers, and C consumer waves, which cull and compare one
+// block each of the phase before. A workgroup holds a.n_pairs pairs (chunks of any events)
+// that share the field map; the producers come first, so that they sit on different SIMDs.
+// COLS: columns of the points (seeds of a chunk at most). QUAD: a seed on four lanes, 16
+// to a producer (QuadProp).
 // Same blocks, lists and arithmetic per chunk as scan_kernel: the same results.
 //
-// What bounds it is the producer's chain, about 930 cycles per step in the field map (138
-// VALU instructions of one wave, 4 cycles each, and two LDS lookups). One wave doing both
-// took 1800: 96 seeds of 6000 steps 4.5 -> 2.3 ms with 7 consumers (3.7 with 1, 2.6 with
-// 2), 6^5 FP64 seeds in the uniform field 1.07 -> 0.37 ms, the refinement's forward pass
-// over 512 events of 8 seeds 6.7 -> 3.0 ms (two pairs per CU, one round instead of two).
-template <typename R, int FIELD, int B, int COLS, int MODE, int VAR>
+// What bounds it is the producers' instruction stream: a wave alone on its SIMD issues a
+// VALU instruction every 5.6 to 8 cycles. A map step is 138 of them and took 930 cycles on
+// one lane per seed, 90 and 650 on four; one wave stepping and culling took 1800. 96 seeds
+// of 6000 steps: 4.5 -> 2.3 (7 consumers; 3.7 with 1) -> 1.8 ms on quads; 6^5 FP64 seeds in
+// the uniform field 1.07 -> 0.37 ms; the refinement's forward pass over 512 events of 8
+// seeds 6.7 -> 3.0 -> 2.2 ms (two pairs per CU, one round instead of two).
+template <typename R, int FIELD, int B, int COLS, int MODE, int VAR, bool QUAD>
 __global__ void __launch_bounds__(64 * kPipeWaves) pipe_kernel(ScanArgs a) {
   using Slab = typename std::conditional<MODE == 0, R, unsigned long long>::type;
   constexpr int kPts = (B + 1) * 3 * COLS;   // points of one block
+  constexpr int NP = QUAD ? COLS / 16 : 1;   // producers of a pair
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ int s_blocks[2][kPipeWaves];   // blocks written in a phase, per pair
+  __shared__ int s_blocks[2][kPipeWaves];    // blocks written in a phase, per producer
   const int C = a.n_con;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n_pairs = a.n_pairs;
-  const bool producer = wave < n_pairs;
-  const int pair = producer ? wave : (wave - n_pairs) / C;
-  const int con = producer ? 0 : (wave - n_pairs) % C;
-  const int sub = producer ? 0 : 1 + con;   // the wave's number within its pair
+  const int n_pairs = a.n_pairs, n_prod = n_pairs * NP;
+  const bool producer = wave < n_prod;
+  const int pair = producer ? wave / NP : (wave - n_prod) / C;
+  const int con = producer ? 0 : (wave - n_prod) % C;
+  const int sub = producer ? wave % NP : NP + con;   // the wave's number within its pair
   float2* s_field = reinterpret_cast<float2*>(smem);
   unsigned char* mine = smem + a.field_bytes + (size_t)pair * a.pair_bytes;
   EventLds<R> L;
@@ -1113,7 +1192,7 @@ __global__ void __launch_bounds__(64 * kPipeWaves) pipe_kernel(ScanArgs a) {
     nodes = s_field;   // made visible by the barriers before the first chunk
   }
   const int rows = (int)(a.slab_stride / 64);
-  for (int i = sub; i < rows; i += 1 + C) slab[(size_t)i * 64 + lane] = slab_empty<Slab>();
+  for (int i = sub; i < rows; i += NP + C) slab[(size_t)i * 64 + lane] = slab_empty<Slab>();
   __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): in L2 before another wave's atomics
   const int n_seg = a.n_seg_dev ? *a.n_seg_dev : a.n_seg;
   const int64_t n_chunks = a.n_chunks_dev ? *a.n_chunks_dev : a.n_chunks;
@@ -1122,6 +1201,7 @@ __global__ void __launch_bounds__(64 * kPipeWaves) pipe_kernel(ScanArgs a) {
   const R Kcull = (R)(0.5 * B * a.h + sqrt(lam) + (double)kCullMargin);
   const R sqrt_lam = (R)sqrt(lam);
   const R r0sq = (R)(a.R0 * a.R0);
+  const R far2 = (R)((a.R0 + 1.1 * B * a.h + 1.0) * (a.R0 + 1.1 * B * a.h + 1.0));
   const int nblocks = (a.n_steps + B - 1) / B;
   constexpr bool STOP = VAR != 0;
   int cur_event = -1;
@@ -1133,116 +1213,146 @@ __global__ void __launch_bounds__(64 * kPipeWaves) pipe_kernel(ScanArgs a) {
     const int hbase = a.ev_off[ev];
     const int nh = a.ev_off[ev + 1] - hbase;
     __syncthreads();   // the pair is done with its last chunk's tables
-    if (ev != cur_event) stage_event<R>(a, L, ev, sub * 64 + lane, 64 * (1 + C), B * a.h);
+    if (ev != cur_event) stage_event<R>(a, L, ev, sub * 64 + lane, 64 * (NP + C), B * a.h);
     cur_event = ev;
-    if (producer)
+    if (sub == 0)
       for (int i = lane; i < a.touch_words; i += 64) touch[i] = 0u;
     __syncthreads();
     const float z_pad = (float)Kcull + a.ev_maxdrift[ev];
     const float z_lo = a.wire_zmin - z_pad, z_hi = a.wire_zmax + z_pad;
-    bool valid = false;
+    // blocks written in phase ph, by a producer of this pair or of any; after the barrier
+    auto blocks_of_pair = [&](int ph) {
+      int m = 0;
+      for (int k = 0; k < NP; ++k) m = max(m, s_blocks[ph & 1][pair * NP + k]);
+      return __builtin_amdgcn_readfirstlane(m);
+    };
+    auto any_block = [&](int ph) {
+      int m = 0;
+      for (int k = 0; k < n_prod; ++k) m |= s_blocks[ph & 1][k];
+      return __builtin_amdgcn_readfirstlane(m) != 0;
+    };
     if (producer) {
+      // the lane's seed (column of the points) and, on quads, its component
+      const int sd = QUAD ? sub * 16 + (lane >> 2) : lane;
+      const int comp = QUAD ? min(lane & 3, 2) : 0;
       State<R> st;
-      const LaneSlot q = load_seed<R>(a, seg, ch, lane, st, valid);
+      bool valid;
+      const LaneSlot q = load_seed<R>(a, seg, ch, sd, st, valid);
       valid = valid && has;
       Prop<R, FIELD> pr;
-      pr.start(st);
-      pr.init_field(st, a.field, nodes);
+      QuadProp qp;
+      const float* qnodes = nullptr;
+      if constexpr (QUAD) {
+        qp.s = comp == 0 ? st.x : (comp == 1 ? st.y : st.z);
+        qp.st = comp == 0 ? st.tx : (comp == 1 ? st.ty : st.tz);
+        qp.cs = qp.cst = 0.0f;
+        qp.lam = st.lam;
+        qp.is_z = comp == 2;
+        qnodes = reinterpret_cast<const float*>(nodes) + (comp == 2 ? 1 : 0);
+        qp.start();
+        qp.init_field(a.field, qnodes);
+      } else {
+        pr.start(st);
+        pr.init_field(st, a.field, nodes);
+      }
       bool live = valid;   // as in scan_kernel
+      const bool steady = VAR == 1 && steady_lane(a, st.lam);
+      [[maybe_unused]] auto tape = [&](int step) {
+        if constexpr (QUAD) {
+          float* tp = a.tape + (size_t)(step / a.ckpt) * 13 * a.n_pos + q.gidx;
+          tp[(size_t)comp * a.n_pos] = qp.s;
+          tp[(size_t)(3 + comp) * a.n_pos] = qp.cs;
+          tp[(size_t)(6 + comp) * a.n_pos] = qp.st;
+          tp[(size_t)(9 + comp) * a.n_pos] = qp.cst;
+          if (comp == 0) tp[(size_t)12 * a.n_pos] = qp.lam;
+        } else {
+          write_tape<R>(a, step, q.gidx, st);
+        }
+      };
       int blk = 0;
+      bool ended = !has;   // the wave's seeds have no block left
       for (int ph = 0;; ++ph) {
         int made = 0;
-        for (int c = 0; c < C && blk < nblocks && has; ++c) {
+        for (int c = 0; c < C && blk < nblocks; ++c, ++blk) {
+          R* r2 = s_r2 + ((ph & 1) * C + c) * 128;
           if constexpr (STOP) {
-            if (__ballot(live) == 0) {
+            if (!ended && __ballot(live) == 0) {
+              ended = true;
               if constexpr (MODE == 1) {
                 if (a.tape && q.in_tile)
                   for (int step = blk * B; step < a.n_steps; step += B)
-                    if (step % a.ckpt == 0) write_tape<R>(a, step, q.gidx, st);
+                    if (step % a.ckpt == 0) tape(step);
               }
-              blk = nblocks;
-              break;
             }
           }
           if constexpr (FIELD == 0 && MODE == 0 && VAR == 0) {
             const bool gone = !valid || ((float)st.z > z_hi + 0.1f && st.tz >= (R)0) ||
                               ((float)st.z < z_lo - 0.1f && st.tz <= (R)0);
-            if (__ballot(!gone) == 0) {
+            ended = ended || __ballot(!gone) == 0;
+          }
+          if (ended) {
+            if (NP == 1) {
               blk = nblocks;
               break;
             }
+            // another producer of the pair may go on: no block of these seeds there
+            r2[sd] = (R)-1;
+            continue;
           }
           const bool live0 = live;
           const int nb = min(B, a.n_steps - blk * B);
           if constexpr (MODE == 1) {
             const int step = blk * B;
-            if (a.ckpt > 0 && step % a.ckpt == 0) pr.init_field(st, a.field, nodes);
-            if (a.tape && q.in_tile && step % a.ckpt == 0) write_tape<R>(a, step, q.gidx, st);
+            if (a.ckpt > 0 && step % a.ckpt == 0) {
+              if constexpr (QUAD)
+                qp.init_field(a.field, qnodes);
+              else
+                pr.init_field(st, a.field, nodes);
+            }
+            if (a.tape && q.in_tile && step % a.ckpt == 0) tape(step);
           }
           R* pts = s_pts + ((ph & 1) * C + c) * kPts;
-          R* r2 = s_r2 + ((ph & 1) * C + c) * 128;
-          R r2min, r2max;
-          r2min = r2max = pr.r2;
-          if (COLS == 64 || lane < COLS) {
-            pts[0 * COLS + lane] = st.x;
-            pts[1 * COLS + lane] = st.y;
-            pts[2 * COLS + lane] = st.z;
-            auto take = [&](int j, bool go) {
-              if (go) pr.step(st, a.field, nodes, h);
-              pts[(j * 3 + 0) * COLS + lane] = pr.px;
-              pts[(j * 3 + 1) * COLS + lane] = pr.py;
-              pts[(j * 3 + 2) * COLS + lane] = pr.pz;
-              if constexpr (VAR == 1) live = live && !inside_r0(pr.px, pr.py, r0sq);
-              r2min = vmin(r2min, pr.r2);
-              r2max = vmax(r2max, pr.r2);
-            };
-            if (nb == B) {
-#pragma unroll
-              for (int j = 1; j <= B; ++j) take(j, !STOP || live);
-            } else {
-              for (int j = 1; j <= B; ++j) take(j, j <= nb && (!STOP || live));
-            }
-            if (!STOP || live0) {
-              pr.fold(st);
-              pts[(nb * 3 + 0) * COLS + lane] = pr.px;
-              pts[(nb * 3 + 1) * COLS + lane] = pr.py;
-              pts[(nb * 3 + 2) * COLS + lane] = pr.pz;
-              r2min = vmin(r2min, pr.r2);
-              r2max = vmax(r2max, pr.r2);
-            }
+          R r2min = (R)-1, r2max = (R)-1;
+          if constexpr (QUAD) {
+            take_block_quad<B, COLS, VAR>(a, qnodes, qp, pts, sd, comp, nb, h, r0sq, far2, steady, live, r2min, r2max);
+          } else {
+            if (COLS == 64 || lane < COLS)
+              take_block<R, FIELD, B, COLS, VAR>(a, nodes, st, pr, pts, lane, nb, h, r0sq, far2, steady, live, r2min,
+                                                 r2max);
           }
-          r2[lane] = valid && (!STOP || live0) ? r2min : (R)-1;
-          r2[64 + lane] = r2max;
-          ++blk;
-          ++made;
+          r2[sd] = valid && (!STOP || live0) ? r2min : (R)-1;
+          r2[64 + sd] = r2max;
+          made = c + 1;
         }
-        if (lane == 0) s_blocks[ph & 1][pair] = made;
+        if (lane == 0) s_blocks[ph & 1][wave] = made;
         __syncthreads();
-        int any = 0;
-        for (int k = 0; k < n_pairs; ++k) any |= s_blocks[ph & 1][k];
-        if (__builtin_amdgcn_readfirstlane(any) == 0) break;
+        if (!any_block(ph)) break;
       }
     } else {
       for (int ph = 0;; ++ph) {
         const int prev = (ph & 1) ^ 1;
-        if (ph > 0 && con < s_blocks[prev][pair]) {
+        if (ph > 0 && con < blocks_of_pair(ph - 1)) {
           const int blk = (ph - 1) * C + con;
           const R* r2 = s_r2 + (prev * C + con) * 128;
           unsigned long long w_tests = 0, w_chords = 0;
+          const bool on = (COLS == 64 || lane < COLS) && !(r2[lane] < (R)0);
           cull_block<R, B, 64, COLS, MODE, false, false>(L, s_pts + (prev * C + con) * kPts, items, slab, touch, lane,
-                                                   !(r2[lane] < (R)0), min(B, a.n_steps - blk * B), blk * B, r2[lane],
-                                                   r2[64 + lane], 0.5f * (float)a.h, z_lo, z_hi, Kcull, sqrt_lam,
-                                                   w_tests, w_chords);
+                                                         on, min(B, a.n_steps - blk * B), blk * B, r2[lane],
+                                                         r2[64 + lane], 0.5f * (float)a.h, a.walk, z_lo, z_hi, Kcull,
+                                                         sqrt_lam, w_tests, w_chords);
         }
         __syncthreads();
-        int any = 0;
-        for (int k = 0; k < n_pairs; ++k) any |= s_blocks[ph & 1][k];
-        if (__builtin_amdgcn_readfirstlane(any) == 0) break;
+        if (!any_block(ph)) break;
       }
       __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the minima are in L2
     }
     __syncthreads();
-    if (producer && has) {
+    if (sub == 0 && has) {
+      bool valid;
+      {
+        State<R> st;
+        load_seed<R>(a, seg, ch, lane, st, valid);
+      }
       if constexpr (MODE == 1)
         finish_refine<R, 64, 8>(a, L, slab, touch, lane, hbase, nh, seg, ch, valid);
       else
@@ -1365,6 +1475,16 @@ static int scan_waves(const rkn_ctx* c, int precision, int B) {
   return 8;
 }
 
+// Whether a launch walks its windows in scan order and skips lanes past the wires' z range
+// (long: more than one chunk per wave). A launch of one window that fits the chip at once
+// gains nothing from either (10 windows of 8^5..12^5 seeds: 0.97-1.02) and keeps the
+// grid's order, in which the wave's lists, and with them the rounding of each distance,
+// are those of the seeds' own neighbours; so do explicit seeds, whose order is the
+// caller's.
+static int walks(const ScanArgs& a, bool longer) {
+  return longer || (!a.seeds5 && (a.n_seg_dev || a.n_seg > 1)) ? 1 : 0;
+}
+
 template <typename R, int FIELD, int B, int WAVES, int MODE = 0>
 static hipError_t launch_scan_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, bool alloc_only, DevBuf* slab_buf,
                                 void* raw_slab = nullptr, size_t raw_bytes = 0) {
@@ -1385,6 +1505,7 @@ static hipError_t launch_scan_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, boo
   const int per_cu = resident_per_cu(c, (const void*)kern, TILE, smem);
   if (per_cu < 1) return hipErrorInvalidConfiguration;
   int64_t grid = (int64_t)per_cu * c->n_cu;
+  a.walk = walks(a, max_chunks > grid * WAVES);
   if (grid > max_chunks) grid = max_chunks;
   if (grid < 1) grid = 1;
   a.slab_stride = (int64_t)(c->max_hits_event > 0 ? c->max_hits_event : 1) * TILE;
@@ -1415,22 +1536,26 @@ static size_t pair_lds_bytes(const rkn_ctx* c, size_t rsize, int B, int cols, in
 
 // Launches pipe_kernel if the launch suits it (false otherwise): fixed steps, and chunks
 // few enough that each CU gets at most as many pairs as its LDS holds; then each pair has
-// as many consumers as fit. Past that scan_kernel's waves fill the chip and are the faster
+// as many consumers as fit. QUAD: seeds on four lanes, while each producer gets a SIMD of
+// its own (two producers on one share its issue slots: 17 000 seeds of one event 2.68 ms
+// on one lane each, 2.81 on four). Past that scan_kernel's waves fill the chip and are the faster
 // (768 chunks of 64 trials in the field map, two rounds of pairs: Gauss-Newton 43 ms
 // against 37), except where an event has at most 16 seeds: its one wave per workgroup
 // takes two rounds as well (1000 events of 8 seeds: 10.3 ms against 16.7).
-template <typename R, int FIELD, int B, int COLS, int MODE>
+template <typename R, int FIELD, int B, int COLS, int MODE, bool QUAD = false>
 static bool launch_pipe_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, bool alloc_only, DevBuf* slab_buf,
                           void* raw_slab, size_t raw_bytes, hipError_t* err) {
   if (a.work || a.h_max > 0 || max_chunks < 1) return false;
-  auto kern = a.turn_stop ? pipe_kernel<R, FIELD, B, COLS, MODE, 1> : pipe_kernel<R, FIELD, B, COLS, MODE, 0>;
+  auto kern = a.turn_stop ? pipe_kernel<R, FIELD, B, COLS, MODE, 1, QUAD> : pipe_kernel<R, FIELD, B, COLS, MODE, 0, QUAD>;
+  constexpr int prod = QUAD ? COLS / 16 : 1;   // producers of a pair
   const size_t field = field_lds_bytes(c, FIELD), room = (size_t)c->max_lds_block - 512;
   auto fits = [&](int64_t pairs, int con) {   // that many pairs of con consumers on one CU
     const size_t pair = pair_lds_bytes(c, sizeof(R), B, COLS, con);
-    return FIELD == 1 ? pairs * (1 + con) <= kPipeWaves && field + pairs * pair <= room
-                      : 1 + con <= kPipeWaves && pairs * (pair + 512) <= room && pairs * (1 + con) <= 16;
+    return FIELD == 1 ? pairs * (prod + con) <= kPipeWaves && field + pairs * pair <= room
+                      : prod + con <= kPipeWaves && pairs * (pair + 512) <= room && pairs * (prod + con) <= 16;
   };
   int64_t per_cu = (max_chunks + c->n_cu - 1) / c->n_cu;
+  if (QUAD && per_cu * prod > 4) return false;   // a SIMD for each producer
   if (!fits(per_cu, 1)) {
     if (COLS > 16) return false;
     int64_t most = kPipeWaves;
@@ -1439,13 +1564,13 @@ static bool launch_pipe_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, bool allo
     per_cu = most;
   }
   const int n = FIELD == 1 ? (int)per_cu : 1;
-  int con = kPipeWaves - 1, threads = 0, resident = 0;
+  int con = 7, threads = 0, resident = 0;
   size_t pair = 0, smem = 0;
   for (; con >= 1; --con) {
     if (!fits(per_cu, con)) continue;
     pair = pair_lds_bytes(c, sizeof(R), B, COLS, con);
     smem = field + n * pair;
-    threads = 64 * n * (1 + con);
+    threads = 64 * n * (prod + con);
     resident = resident_per_cu(c, (const void*)kern, threads, smem);
     if ((int64_t)resident * n >= per_cu) break;
   }
@@ -1458,6 +1583,7 @@ static bool launch_pipe_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, bool allo
   a.hits_bytes = (int)hits_lds_bytes(c, sizeof(R));
   a.sect_bytes = (int)sect_table_bytes(c);
   a.touch_words = touch_words(c);
+  a.walk = walks(a, false);
   a.n_pairs = n;
   a.n_con = con;
   a.pair_bytes = (int)pair;
@@ -1492,8 +1618,9 @@ static hipError_t dispatch_scan(rkn_ctx* c, const rkn_scan_params* p, ScanArgs& 
     done = B == 4 ? pipe(launch_pipe_t<float, 0, 4, 64, 0>)
                   : (B == 6 ? pipe(launch_pipe_t<float, 0, 6, 64, 0>) : pipe(launch_pipe_t<float, 0, 8, 64, 0>));
   else
-    done = B == 4 ? pipe(launch_pipe_t<float, 1, 4, 64, 0>)
-                  : (B == 6 ? pipe(launch_pipe_t<float, 1, 6, 64, 0>) : pipe(launch_pipe_t<float, 1, 8, 64, 0>));
+    done = B == 4   ? pipe(launch_pipe_t<float, 1, 4, 64, 0, true>) || pipe(launch_pipe_t<float, 1, 4, 64, 0>)
+           : B == 6 ? pipe(launch_pipe_t<float, 1, 6, 64, 0, true>) || pipe(launch_pipe_t<float, 1, 6, 64, 0>)
+                    : pipe(launch_pipe_t<float, 1, 8, 64, 0, true>) || pipe(launch_pipe_t<float, 1, 8, 64, 0>);
   if (done) return e;
   if (p->precision == 64)
     return c->field_kind == 0 ? launch_scan_t<double, 0, 4, 4>(c, a, max_chunks, alloc_only, slab, raw_slab, raw_bytes)
@@ -1544,6 +1671,7 @@ static ScanArgs base_args(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& 
   a.n_layers = c->n_layers;
   a.wire_zmin = c->wire_zmin;
   a.wire_zmax = c->wire_zmax;
+  a.b_max = c->b_max;
   a.segs = w.segs;
   a.n_seg = w.n_seg;
   a.n_seg_dev = w.n_seg_dev;
@@ -1587,10 +1715,15 @@ hipError_t launch_refine_fwd(rkn_ctx* c, const rkn_scan_params* p, const ScanSeg
   static_assert(kRefineBlock == 8, "the refinement pass runs 8-step blocks");
   auto pipe = [&](auto launch) { return launch(c, a, w.n_chunks, false, &c->r_slab, nullptr, (size_t)0, &e); };
   // few seeds per event (trials: 6 per seed): narrower points leave LDS for more pairs
-  const bool done = c->field_kind == 0    ? pipe(launch_pipe_t<float, 0, 8, 64, 1>)
-                    : w.max_lanes <= 16   ? pipe(launch_pipe_t<float, 1, 8, 16, 1>)
-                    : w.max_lanes <= 48   ? pipe(launch_pipe_t<float, 1, 8, 48, 1>)
-                                          : pipe(launch_pipe_t<float, 1, 8, 64, 1>);
+  bool done;
+  if (c->field_kind == 0)
+    done = pipe(launch_pipe_t<float, 0, 8, 64, 1>);
+  else if (w.max_lanes <= 16)
+    done = pipe(launch_pipe_t<float, 1, 8, 16, 1, true>) || pipe(launch_pipe_t<float, 1, 8, 16, 1>);
+  else if (w.max_lanes <= 48)
+    done = pipe(launch_pipe_t<float, 1, 8, 48, 1, true>) || pipe(launch_pipe_t<float, 1, 8, 48, 1>);
+  else
+    done = pipe(launch_pipe_t<float, 1, 8, 64, 1, true>) || pipe(launch_pipe_t<float, 1, 8, 64, 1>);
   if (done) return e;
   return c->field_kind == 0 ? launch_scan_t<float, 0, 8, 4, 1>(c, a, w.n_chunks, false, &c->r_slab)
                             : launch_scan_t<float, 1, 8, 8, 1>(c, a, w.n_chunks, false, &c->r_slab);
