@@ -589,6 +589,12 @@ __device__ __forceinline__ void take_block(const ScanArgs& a, const float2* node
 #pragma unroll
         for (int j = 1; j <= B; ++j) take(j, true);
       }
+    } else if (nb == B) {
+#pragma unroll
+      for (int j = 1; j <= B; ++j) {
+        take(j, live);
+        live = live && !inside_r0(pr.px, pr.py, r0sq);
+      }
     } else {
       for (int j = 1; j <= B; ++j) {
         take(j, j <= nb && live);
