@@ -152,7 +152,7 @@ void rkn_destroy(rkn_ctx* c) {
                     &c->out_best_i, &c->out_best_e, &c->trace_buf, &c->seeds_buf, &c->perm_buf,
                     &c->wire_wx, &c->wire_wy, &c->hits_wire, &c->hough_acc, &c->hough_max,
                     &c->hough_cand_n, &c->hough_cand, &c->hough_slots, &c->hough_nsel, &c->hits_orig, &c->hits_phi, &c->layer_ext,
-                    &c->sel_seg, &c->sel_win, &c->sel_idx, &c->sel_sc, &c->sel_seed, &c->cl_seeds,
+                    &c->sel_seg, &c->sel_win, &c->sel_idx, &c->sel_sc, &c->sel_seed, &c->sel_parts, &c->cl_seeds,
                     &c->cl_perm, &c->cl_segs, &c->cl_evc, &c->cl_resid, &c->cl_argmin, &c->cl_phi, &c->cl_mask,
                     &c->cl_count, &c->work_counts};
   for (DevBuf* b : bufs) b->release();
@@ -327,6 +327,8 @@ rkn_status rkn_upload_hits(rkn_ctx* c, int32_t n_events, const int32_t* ev_off, 
   if (e == hipSuccess) e = c->hits_phi.ensure(sizeof(float) * (size_t)std::max<int64_t>(H, 1));
   if (e == hipSuccess)
     e = c->layer_ext.ensure(sizeof(float2) * (size_t)std::max(n_events, 1) * (size_t)std::max(c->n_layers, 1));
+  // here, because a selection from device scores to device outputs allocates nothing
+  if (e == hipSuccess) e = c->sel_parts.ensure(rkn::topk_scratch_bytes(n_events));
   if (e == hipSuccess) {
     c->n_events = n_events;
     e = rkn::launch_prep_hits(c, d_wid.as<int32_t>(), d_drift.as<float>());

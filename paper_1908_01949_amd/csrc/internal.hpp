@@ -182,7 +182,7 @@ struct rkn_ctx {
   // per-call work buffers
   rkn::DevBuf windows, segs, ev_chunk, parts, counter, mscratch, out_score, out_nin, out_best_i,
       out_best_e, trace_buf, seeds_buf, perm_buf;
-  rkn::DevBuf sel_seg, sel_win, sel_idx, sel_sc, sel_seed;   // per-event top-k selection
+  rkn::DevBuf sel_seg, sel_win, sel_idx, sel_sc, sel_seed, sel_parts;   // per-event top-k selection
   rkn::DevBuf work_counts;                                   // rkn_scan_work_counts
   rkn::DevBuf cl_seeds, cl_perm, cl_segs, cl_evc, cl_resid, cl_argmin, cl_phi, cl_mask, cl_count;   // classification
   std::vector<rkn::DevBuf> extra;
@@ -313,6 +313,7 @@ void batch_release(rkn_ctx* c);
 // are d_score[d_seg_off[e] .. d_seg_off[e+1]) and come from windows
 // d_win_off[e] .. (e + 1 < n_seg ? d_win_off[e+1] : *d_win_total), in order.
 // d_seed / d_step (optional): each pick's seed and the grid step of its window.
+size_t topk_scratch_bytes(int n_events);   // of ctx.sel_parts
 hipError_t launch_topk(rkn_ctx* c, const double* d_score, const long long* d_seg_off, const WindowDev* d_windows,
                        const int32_t* d_win_off, int n_seg, const int32_t* d_win_total, int k, int64_t* d_idx,
                        double* d_sc, double* d_seed, double* d_step = nullptr);

@@ -16,18 +16,15 @@ __device__ __forceinline__ bool key_less(double a, long long ia, double b, long 
   return a < b || (a == b && ia < ib);
 }
 
-// One workgroup per event. Each thread keeps a sorted list of its kTopMax best
-// (score, index) pairs over a strided pass of the event's seeds; k rounds of a
-// workgroup argmin over the list heads then merge them. Order: score, then index
-// (NaN scores are never selected). Seeds are decoded from the event's windows, whose
-// seeds are contiguous from seg_off[e] in window order.
-__global__ void __launch_bounds__(256)
-topk_kernel(const double* __restrict__ score, const long long* __restrict__ seg_off,
-            const WindowDev* __restrict__ windows, const int32_t* __restrict__ win_off, int n_seg,
-            const int32_t* __restrict__ win_total, int k, int64_t* __restrict__ out_idx,
-            double* __restrict__ out_score, double* __restrict__ out_seed, double* __restrict__ out_step) {
-  const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const long long lo = seg_off[e], hi = seg_off[e + 1];
+// The k lowest (score, index) pairs of a workgroup's candidates, ascending; NaN scores are
+// never selected. `get(j, s, i)` reads candidate j of n. Each thread keeps a sorted list
+// of its kTopMax best over a strided pass; k rounds of a workgroup argmin over the list
+// heads then merge them into s_sc, s_sel (index -1 and infinity past the last candidate).
+template <class GET>
+__device__ __forceinline__ void block_topk(long long n, int k, double* s_sc, long long* s_sel, const GET& get) {
+  __shared__ double s_e[4];
+  __shared__ long long s_i[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double bs[kTopMax];
   long long bi[kTopMax];
 #pragma unroll
@@ -35,10 +32,11 @@ topk_kernel(const double* __restrict__ score, const long long* __restrict__ seg_
     bs[j] = INFINITY;
     bi[j] = 0x7fffffffffffffffLL;
   }
-  for (long long g = lo + tid; g < hi; g += 256) {
-    double s = score[g];
-    long long i = g;
-    if (!(s == s)) continue;
+  for (long long g = tid; g < n; g += 256) {
+    double s;
+    long long i;
+    get(g, s, i);
+    if (!(s == s) || i < 0) continue;
 #pragma unroll
     for (int j = 0; j < kTopMax; ++j) {
       const bool lt = key_less(s, i, bs[j], bi[j]);
@@ -50,10 +48,6 @@ topk_kernel(const double* __restrict__ score, const long long* __restrict__ seg_
       i = ti;
     }
   }
-  __shared__ double s_e[4];
-  __shared__ long long s_i[4];
-  __shared__ long long s_sel[kTopMax];
-  __shared__ double s_sc[kTopMax];
   for (int r = 0; r < k; ++r) {
     double be = bs[0];
     long long bx = bi[0];
@@ -95,6 +89,55 @@ topk_kernel(const double* __restrict__ score, const long long* __restrict__ seg_
     }
     __syncthreads();
   }
+}
+
+// Candidates of one slice of an event's seeds: its k lowest to part_s, part_i. An event
+// whose seeds one workgroup reads alone is bound by that CU's loads and its 16 compares a
+// seed (16^5 seeds: 3.7 ms); see topk_slices for the split.
+__global__ void __launch_bounds__(256)
+topk_slice_kernel(const double* __restrict__ score, const long long* __restrict__ seg_off, int k,
+                  double* __restrict__ part_s, long long* __restrict__ part_i) {
+  __shared__ long long s_sel[kTopMax];
+  __shared__ double s_sc[kTopMax];
+  const int e = blockIdx.y, n_sl = gridDim.x;
+  const long long n = seg_off[e + 1] - seg_off[e], per = (n + n_sl - 1) / n_sl;
+  const long long j0 = min(n, per * blockIdx.x), j1 = min(n, j0 + per), lo = seg_off[e] + j0;
+  block_topk(j1 - j0, k, s_sc, s_sel, [&](long long j, double& s, long long& i) {
+    i = lo + j;
+    s = score[i];
+  });
+  if ((int)threadIdx.x < k) {
+    const size_t o = ((size_t)e * n_sl + blockIdx.x) * k + threadIdx.x;
+    part_s[o] = s_sc[threadIdx.x];
+    part_i[o] = s_sel[threadIdx.x];
+  }
+}
+
+// One workgroup per event: the k lowest of its scores (n_sl = 1) or of its slices'
+// candidates. Seeds are decoded from the event's windows, whose seeds are contiguous from
+// seg_off[e] in window order.
+__global__ void __launch_bounds__(256)
+topk_kernel(const double* __restrict__ score, const long long* __restrict__ seg_off,
+            const double* __restrict__ part_s, const long long* __restrict__ part_i, int n_sl,
+            const WindowDev* __restrict__ windows, const int32_t* __restrict__ win_off, int n_seg,
+            const int32_t* __restrict__ win_total, int k, int64_t* __restrict__ out_idx,
+            double* __restrict__ out_score, double* __restrict__ out_seed, double* __restrict__ out_step) {
+  __shared__ long long s_sel[kTopMax];
+  __shared__ double s_sc[kTopMax];
+  const int e = blockIdx.x, tid = threadIdx.x;
+  const long long lo = seg_off[e], hi = seg_off[e + 1];
+  if (n_sl > 1) {
+    const size_t o = (size_t)e * n_sl * k;
+    block_topk((long long)n_sl * k, k, s_sc, s_sel, [&](long long j, double& s, long long& i) {
+      s = part_s[o + j];
+      i = part_i[o + j];
+    });
+  } else {
+    block_topk(hi - lo, k, s_sc, s_sel, [&](long long j, double& s, long long& i) {
+      i = lo + j;
+      s = score[i];
+    });
+  }
   if (tid < k) {
     const long long g = s_sel[tid];
     const size_t o = (size_t)e * k + tid;
@@ -126,13 +169,31 @@ topk_kernel(const double* __restrict__ score, const long long* __restrict__ seg_
   }
 }
 
+// Slices per event: enough workgroups for two on each of 256 CUs, at most 256 (their
+// candidates are merged by one workgroup). The rule knows the events only, the seeds of a
+// batch are counted on the device. One event of 16^5 seeds: 3.73 ms -> 47 us in 256
+// slices; 64 events of 4 x 10^4 seeds in 8: 77 us; 3 x 8 windows: 40 us.
+static int topk_slices(int n_events) { return std::min(256, (512 + n_events - 1) / n_events); }
+
+static size_t topk_part_rows(int n_events) { return (size_t)topk_slices(n_events) * n_events * kTopMax; }
+
+size_t topk_scratch_bytes(int n_events) {
+  return n_events > 0 ? topk_part_rows(n_events) * (sizeof(double) + sizeof(long long)) : 0;
+}
+
 hipError_t launch_topk(rkn_ctx* c, const double* d_score, const long long* d_seg_off, const WindowDev* d_windows,
                        const int32_t* d_win_off, int n_seg, const int32_t* d_win_total, int k, int64_t* d_idx,
                        double* d_sc, double* d_seed, double* d_step) {
   if (n_seg <= 0) return hipSuccess;
   if (k < 1 || k > kTopMax) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(topk_kernel, dim3(n_seg), dim3(256), 0, c->stream, d_score, d_seg_off, d_windows, d_win_off,
-                     n_seg, d_win_total, k, d_idx, d_sc, d_seed, d_step);
+  const int n_sl = topk_slices(n_seg);
+  double* part_s = c->sel_parts.as<double>();
+  long long* part_i = (long long*)(part_s + topk_part_rows(n_seg));
+  if (n_sl > 1)
+    hipLaunchKernelGGL(topk_slice_kernel, dim3(n_sl, n_seg), dim3(256), 0, c->stream, d_score, d_seg_off, k, part_s,
+                       part_i);
+  hipLaunchKernelGGL(topk_kernel, dim3(n_seg), dim3(256), 0, c->stream, d_score, d_seg_off, part_s, part_i, n_sl,
+                     d_windows, d_win_off, n_seg, d_win_total, k, d_idx, d_sc, d_seed, d_step);
   return hipGetLastError();
 }
 
