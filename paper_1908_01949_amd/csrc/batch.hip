@@ -19,7 +19,7 @@ namespace rkn {
 // Single workgroup: per-event sizes, a serial exclusive scan over events, then every
 // event writes its windows and segments. counts[0] = windows.
 __global__ void __launch_bounds__(256)
-batch_expand_kernel(const WinSlot* __restrict__ slots, const int32_t* __restrict__ nsel, int n_events,
+batch_expand_kernel(const WinSlot* __restrict__ slots, const int32_t* __restrict__ nsel, int n_events, int max_cand,
                     int32_t* __restrict__ ev_nw, long long* __restrict__ ev_nc, long long* __restrict__ ev_ns,
                     WindowDev* __restrict__ windows, Seg* __restrict__ segs, int64_t* __restrict__ ev_chunk,
                     long long* __restrict__ ev_seed, int32_t* __restrict__ counts) {
@@ -28,7 +28,7 @@ batch_expand_kernel(const WinSlot* __restrict__ slots, const int32_t* __restrict
     int nw = 0;
     long long nc = 0, ns = 0;
     for (int j = 0; j < nsel[e]; ++j) {
-      const WinSlot& s = slots[(size_t)e * kMaxCand + j];
+      const WinSlot& s = slots[(size_t)e * max_cand + j];
       if (!s.valid) continue;
       long long size = 1;
       for (int q = 0; q < 5; ++q) size *= s.w.count[q];
@@ -64,7 +64,7 @@ batch_expand_kernel(const WinSlot* __restrict__ slots, const int32_t* __restrict
     int w = ev_nw[e];
     long long g = ev_seed[e], ch = ev_chunk[e];
     for (int j = 0; j < nsel[e]; ++j) {
-      const WinSlot& s = slots[(size_t)e * kMaxCand + j];
+      const WinSlot& s = slots[(size_t)e * max_cand + j];
       if (!s.valid) continue;
       long long size = 1;
       for (int q = 0; q < 5; ++q) size *= s.w.count[q];
@@ -218,7 +218,7 @@ rkn_status rkn_batch_plan(rkn_ctx* c, const rkn_hough_params* hp, const rkn_scan
   hipError_t eq = queue_hough_all(c, h);
   if (eq == hipSuccess) {
     hipLaunchKernelGGL(batch_expand_kernel, dim3(1), dim3(256), 0, c->stream, c->hough_slots.as<WinSlot>(),
-                       c->hough_nsel.as<int32_t>(), ne, ev_nw, ev_nc, ev_ns, c->b_windows.as<WindowDev>(),
+                       c->hough_nsel.as<int32_t>(), ne, h.max_cand, ev_nw, ev_nc, ev_ns, c->b_windows.as<WindowDev>(),
                        c->b_segs.as<Seg>(), c->b_ev_chunk.as<int64_t>(), c->b_ev_seed.as<long long>(),
                        c->b_counts.as<int32_t>());
     eq = hipGetLastError();

@@ -177,7 +177,7 @@ struct rkn_ctx {
   rkn::DevBuf hits_orig;             // int32 original index within its event, per layer-ordered hit
   rkn::DevBuf hits_phi;              // float twisted azimuth psi of the wire centre, per layer-ordered hit
   rkn::DevBuf layer_ext;             // float2 [n_events][n_layers] (dphi/dz of the layer's wires, psi deviation)
-  rkn::DevBuf hough_acc, hough_max, hough_cand_n, hough_cand, hough_slots, hough_nsel;
+  rkn::DevBuf hough_acc, hough_max, hough_cand_n, hough_cand, hough_slots, hough_nsel, hough_public;
 
   // per-call work buffers
   rkn::DevBuf windows, segs, ev_chunk, parts, counter, mscratch, out_score, out_nin, out_best_i,
