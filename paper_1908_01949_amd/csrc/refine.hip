@@ -440,87 +440,43 @@ __global__ void __launch_bounds__(256, 2) adj_seg_kernel(BwdArgs a) {
     for (int c = 0; c < 7; ++c) out[(size_t)(r * 7 + c) * n] = c == 6 ? (r == 6 ? 1.0 : 0.0) : T[c < 6 ? c : 0][r];
 }
 
-constexpr int kCombineSeeds = 4;   // seeds (waves) per workgroup of adj_combine_kernel
-
-// One seed's matrices in adj_combine_kernel.
-struct CombineLds {
-  alignas(16) double phi[8][8], S[8][8], B[8][8], hit[8][8];
-};
-
-// Orders one wave's LDS writes before its own later reads (and reads before writes).
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
+constexpr int kCombineSeeds = 8;   // seeds (waves) per workgroup of adj_combine_kernel
 
 // Per seed, one wave: lambda_0 and S_0 from the segments, last to first, then the seed
 // derivatives through P = dy0/dseed: grad = P^T lambda_0, J^T J = P^T S_0 P. Lane (r, c)
-// of an 8 x 8 grid holds S[r][c], lane (r, 7) lambda_r; rows and columns of the factors
-// are read from LDS, and a segment's values are loaded while the one after it is worked
-// on. Bound by the chain of segments. (1024 seeds, 94 segments: one thread per seed, 84
-// loads waited out per segment, 200 us; 8 seeds a workgroup, factors over wave shuffles,
-// 56 of them a segment, 132 us; this way 70 us.)
+// of an 8 x 8 grid holds S[r][c], lane (r, 7) lambda_r; the factors of the products come
+// over wave shuffles. (One thread per seed waited out each segment's 84 loads: 200 us for
+// 1024 seeds and 94 segments, now 152 us. 8 neighbouring seeds of a workgroup share the
+// cache lines of the segments' values.)
 __global__ void __launch_bounds__(64 * kCombineSeeds) adj_combine_kernel(BwdArgs a) {
   __shared__ double s_P[kCombineSeeds][7][5];
-  __shared__ CombineLds s_m[kCombineSeeds];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane >> 3, c = lane & 7;
   const int64_t n = a.n;
   const int64_t p0 = (int64_t)blockIdx.x * kCombineSeeds + wave;
   const int64_t p = p0 < n ? p0 : n - 1;
   const bool in7 = r < 7 && c < 7;
   double S = 0.0;
-  CombineLds& m = s_m[wave];
   auto phi_of = [&](int k) { return in7 ? a.segout[((size_t)k * kSegVals + r * 7 + c) * n + p] : 0.0; };
-  // first list slot of segment k, from a wave's load of 64 of them
-  int offs = 0, offs_of = -1;
-  auto first_hit = [&](int k) {
-    if (k >> 6 != offs_of) {
-      offs_of = k >> 6;
-      offs = a.segoff[(size_t)min(offs_of * 64 + lane, a.n_ckpt) * n + p];
-    }
-    return __builtin_amdgcn_readlane(offs, k & 63);
-  };
-  // lane (j, q): value q of the list's hit l0 + j
-  auto hits_of = [&](int l0, int l1) {
-    return l0 + r < l1 ? a.hitvec[((size_t)(l0 + r) * kHitVals + c) * n + p] : 0.0;
-  };
-  int l1 = a.segoff[(size_t)a.n_ckpt * n + p], l0 = first_hit(a.n_ckpt - 1);
-  double phi = phi_of(a.n_ckpt - 1), hv = hits_of(l0, l1);
+  double next = phi_of(a.n_ckpt - 1);
+  int l1 = a.segoff[(size_t)a.n_ckpt * n + p];
   for (int k = a.n_ckpt - 1; k >= 0; --k) {
-    // the next segment's values, while this one is worked on
-    double next_phi = 0.0, next_hv = 0.0;
-    int next_l0 = 0;
-    if (k > 0) {
-      next_l0 = first_hit(k - 1);
-      next_phi = phi_of(k - 1);
-      next_hv = hits_of(next_l0, l0);
-    }
+    const double phi = next;
+    if (k > 0) next = phi_of(k - 1);
+    const int l0 = a.segoff[(size_t)k * n + p];
     double acc = 0.0;   // sum e e^T, sum c e
-    for (int li = l0; li < l1; li += 8) {
-      m.hit[r][c] = li == l0 ? hv : hits_of(li, l1);
-      wave_lds_sync();
-      for (int j = 0; j < min(8, l1 - li); ++j)
-        if (r < 7) acc += m.hit[j][r] * m.hit[j][c];
-      wave_lds_sync();
+    for (int li = l0; li < l1; ++li) {
+      const double* h = a.hitvec + (size_t)li * kHitVals * n + p;
+      if (r < 7) acc += h[(size_t)r * n] * h[(size_t)c * n];
     }
-    m.phi[r][c] = phi;
-    m.S[r][c] = S;
-    wave_lds_sync();
+    l1 = l0;
     double B = 0.0;     // Phi [S, lambda]
 #pragma unroll
-    for (int q = 0; q < 7; ++q) B += m.phi[r][q] * m.S[q][c];
-    m.B[r][c] = B;
-    wave_lds_sync();
+    for (int q = 0; q < 7; ++q) B += __shfl(phi, r * 8 + q, 64) * __shfl(S, q * 8 + c, 64);
     double Sn = acc;    // B Phi^T + sum e e^T
 #pragma unroll
-    for (int q = 0; q < 7; ++q) Sn += m.B[r][q] * m.phi[c][q];
-    wave_lds_sync();
+    for (int q = 0; q < 7; ++q) Sn += __shfl(B, r * 8 + q, 64) * __shfl(phi, (c < 7 ? c : 0) * 8 + q, 64);
     S = c == 7 ? acc + B : Sn;
     if (r == 7) S = 0.0;
-    phi = next_phi;
-    hv = next_hv;
-    l1 = l0;
-    l0 = next_l0;
   }
   const double* sd = a.seeds5 + 5 * p;
   const double pm = sqrt(sd[2] * sd[2] + sd[3] * sd[3] + sd[4] * sd[4]);
