@@ -9,16 +9,14 @@
 // minimum over chords; at its minimising chord n with parameters (s*, t*) and unit
 // closest-approach vector w, dD/dx_n = (1 - s*) w and dD/dx_{n+1} = s* w.
 //
-// State y = (x, T, Lambda) in R^7; M_n = dy_{n+1}/dy_n. The adjoint obeys, for
+// State y = (x, T, Lambda) in R^7; M_n = dy_{n+1}/dy_n. The backward sweep runs, for
 // n = N-1 .. 0, with e_i = [(1 - s*) w; 0] + M_n^T [s* w; 0] for the hits whose
 // minimum is on chord n:
 //   lambda_n = M_n^T lambda_{n+1} + sum c_i e_i        (gradient, c_i = dF/dr_i)
 //   S_n      = M_n^T S_{n+1} M_n + sum e_i e_i^T       (Gauss-Newton matrix)
 // so that with P = dy_0/ds: grad = P^T lambda_0, J^T J = P^T S_0 P, and with
-// c_i = 2 r_i, J^T r = grad / 2. The path is cut into segments at the checkpoints that
-// the forward pass writes every `ckpt` steps: each is stepped again from its checkpoint,
-// carrying its transfer matrix and each hit's e to the segment's start, and the segments
-// are then chained from the last to the first. Transfer matrices, lambda and S are
+// c_i = 2 r_i, J^T r = grad / 2. States are recomputed segment by segment from the
+// checkpoints written by the forward pass every `ckpt` steps. lambda and S are
 // accumulated in FP64; M_n comes from forward-mode tangents through the FP32 step.
 #include <math.h>
 
@@ -241,89 +239,59 @@ struct BwdArgs {
   const int32_t* argmin;      // [n][max_hits] chord index, -1 outside the inlier set
   const float* cgrad;         // [n][max_hits] upstream dF/dr, or NULL: c = 2 r
   int max_hits;
+  float* segbuf;              // [n_ckpt][ckpt+1][6][n] recomputed (x, T) per step
   int32_t* segoff;            // [n_ckpt+1][n] list offsets of each segment's hits
-  int2* list;                 // [max_hits][n] (chord, hit) in chord order
-  double* hitvec;             // [max_hits][kHitVals][n] per list slot
-  double* segout;             // [n_ckpt][kSegVals][n] per segment: the transfer matrix
+  int2* list;                 // [max_hits][n] (chord, hit) grouped by segment
+  double* segout;             // [n_ckpt][kSegVals][n] per segment: Phi, a, A
   double* grad;               // [n][5]
   double* jtj;                // [n][25] or NULL
 };
 
-// Per segment: the transfer matrix dy(end)/dy(start), transposed (49 values).
-constexpr int kSegVals = 49;
-constexpr int kHitVals = 8;   // per inlier hit: e at its segment's start (7), upstream c
-constexpr int kPrepSeeds = 4; // seeds (waves) per workgroup of adj_prep_kernel
+// Per segment: the transfer matrix Phi (7x7, row-major), the accumulated adjoint
+// source a (7) and the Gauss-Newton source A (7x7 symmetric, 28 upper entries).
+constexpr int kSegVals = 49 + 7 + 28;
 
-// Order each seed's inlier hits by (chord, hit), one wave per seed: rank by counting over
-// the keys in LDS; segoff[k] = the first list slot of segment k. (One thread per seed
-// walked its row of argmin chords three times through global counters: 190 us for 1024
-// seeds, now 22 us.)
-__global__ void __launch_bounds__(64 * kPrepSeeds) adj_prep_kernel(BwdArgs a) {
-  __shared__ int64_t s_key[kPrepSeeds][RKN_MAX_HITS_PER_EVENT];
-  __shared__ int s_chord[kPrepSeeds][RKN_MAX_HITS_PER_EVENT];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t p = (int64_t)blockIdx.x * kPrepSeeds + wave, n = a.n;
-  int nh = 0, found = 0;
-  if (p < n) {
-    const int e = a.seed_event[p];
-    nh = a.ev_off[e + 1] - a.ev_off[e];
-  }
-  for (int o = lane; o < nh; o += 64) {
-    const int st = a.argmin[p * a.max_hits + o];
-    s_key[wave][o] = st >= 0 ? ((int64_t)st << 10) | o : INT64_MAX;
-  }
-  __syncthreads();
-  for (int o = lane; o < nh; o += 64) {
-    const int64_t key = s_key[wave][o];
-    if (key == INT64_MAX) continue;
-    int rank = 0;
-    for (int j = 0; j < nh; ++j) rank += s_key[wave][j] < key;
-    s_chord[wave][rank] = (int)(key >> 10);
-    a.list[(size_t)rank * n + p] = make_int2((int)(key >> 10), o);
-    ++found;
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) found += __shfl_xor(found, o, 64);
-  __syncthreads();
-  if (p >= n) return;
-  for (int k = lane; k <= a.n_ckpt; k += 64) {
-    const int64_t first = (int64_t)k * a.ckpt;   // hits on earlier chords come before
-    int lo = 0, hi = found;
-    while (lo < hi) {
-      const int mid = (lo + hi) / 2;
-      if (s_chord[wave][mid] < first)
-        lo = mid + 1;
-      else
-        hi = mid;
-    }
-    a.segoff[(size_t)k * n + p] = lo;
-  }
+__device__ __forceinline__ int upper_index(int r, int c) {   // r <= c
+  return r * 7 - r * (r - 1) / 2 + (c - r);
 }
 
-// One (segment, seed) work item, one lane: from the segment's checkpoint the track is
-// stepped again and the transfer matrix T_n = dy_n/dy_start carried along, T <- M_n T.
-// A hit whose minimum lies on chord n contributes e = T_n^T ([(1 - s*) w; 0] + M_n^T
-// [s* w; 0]) at the segment's start, written out with its upstream gradient c; so
-//   lambda(start) = T_end^T lambda(end) + sum c e,
-//   S(start) = T_end^T S(end) T_end + sum e e^T.
-// The bottom row of T and M is that of the identity (Lambda is constant).
-//
-// Bound by FP64 and FP32 VALU work: per step about 1300 FP32 operations for M_n (tangents
-// through the stages) and 258 FP64 multiply-adds for T. Walking backwards it carried
-// M^T A M as well (930) and kept every recomputed state in memory: 0.80 ms for 1024 seeds
-// and 94 segments, 2.07 ms for 4096 seeds. This way 0.48 and 1.58 ms, and with two waves
-// on a SIMD (256 registers instead of 270, 11 of them spilled) 0.39 and 1.15 ms. The field
-// map is staged in LDS.
-template <int FIELD>
-__global__ void __launch_bounds__(256, 2) adj_seg_kernel(BwdArgs a) {
-  extern __shared__ float2 s_nodes[];
-  FieldDev f = a.field;
-  if constexpr (FIELD == 1) {
-    const int nn = (int)padded_field_nodes(f.nr, f.nz);
-    for (int i = threadIdx.x; i < nn; i += blockDim.x) s_nodes[i] = a.field.nodes[i];
-    f.nodes = s_nodes;
-    __syncthreads();
+// Group each seed's inlier hits by the segment of their minimising chord (counting
+// sort over segments; the order within a segment does not matter).
+__global__ void __launch_bounds__(64) adj_prep_kernel(BwdArgs a) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= a.n) return;
+  const int64_t n = a.n;
+  const int e = a.seed_event[p];
+  const int nh = a.ev_off[e + 1] - a.ev_off[e];
+  for (int k = 0; k <= a.n_ckpt; ++k) a.segoff[(size_t)k * n + p] = 0;
+  for (int o = 0; o < nh; ++o) {
+    const int st = a.argmin[p * a.max_hits + o];
+    if (st >= 0) a.segoff[(size_t)(st / a.ckpt + 1) * n + p] += 1;
   }
+  int acc = 0;
+  for (int k = 0; k <= a.n_ckpt; ++k) {
+    acc += a.segoff[(size_t)k * n + p];
+    a.segoff[(size_t)k * n + p] = acc;     // segoff[k] = first list slot of segment k
+  }
+  for (int o = 0; o < nh; ++o) {
+    const int st = a.argmin[p * a.max_hits + o];
+    if (st < 0) continue;
+    const size_t cs = (size_t)(st / a.ckpt) * n + p;
+    const int pos = a.segoff[cs];
+    a.segoff[cs] = pos + 1;
+    a.list[(size_t)pos * n + p] = make_int2(st, o);
+  }
+  // the scatter advanced each offset to the next segment's start: shift back
+  for (int k = a.n_ckpt; k >= 1; --k) a.segoff[(size_t)k * n + p] = a.segoff[(size_t)(k - 1) * n + p];
+  a.segoff[p] = 0;
+}
+
+// One (segment, seed) work item: recompute the segment's states from its checkpoint,
+// then walk its steps backwards from lambda = 0, S = 0 at the segment end:
+//   Phi <- M_n^T Phi,  a <- M_n^T a + sum c e,  A <- M_n^T A M_n + sum e e^T,
+// so that lambda(start) = Phi lambda(end) + a and S(start) = Phi S(end) Phi^T + A.
+template <int FIELD, bool WANT_S>
+__global__ void __launch_bounds__(64) adj_seg_kernel(BwdArgs a) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t n = a.n;
   if (idx >= n * a.n_ckpt) return;
@@ -331,69 +299,158 @@ __global__ void __launch_bounds__(256, 2) adj_seg_kernel(BwdArgs a) {
   const int64_t p = idx - (int64_t)k * n;
   const int n0 = k * a.ckpt;
   const int n1 = min(n0 + a.ckpt, a.n_steps);
+  float* sb = a.segbuf + (size_t)k * (a.ckpt + 1) * 6 * n + p;
   State<float> s = load_state(a.tape + (size_t)k * 13 * n + p, n);
+  const float lam = s.lam;
+  auto put = [&](int j, const State<float>& q) {
+    float* b = sb + (size_t)j * 6 * n;
+    b[0] = q.x;
+    b[n] = q.y;
+    b[2 * n] = q.z;
+    b[3 * n] = q.tx;
+    b[4 * n] = q.ty;
+    b[5 * n] = q.tz;
+  };
+  auto get = [&](int j) {
+    const float* b = sb + (size_t)j * 6 * n;
+    State<float> q{};
+    q.x = b[0];
+    q.y = b[n];
+    q.z = b[2 * n];
+    q.tx = b[3 * n];
+    q.ty = b[4 * n];
+    q.tz = b[5 * n];
+    q.lam = lam;
+    return q;
+  };
   // The forward pass's propagation: block-relative sums folded at the ends of its
   // kRefineBlock-step blocks (and at the last step) when the track was live at the
   // block's start; the checkpoint is taken right after a fold. With the
   // turn-partition stop the forward pass took a step only while every earlier step
   // ended outside r < R0 (the seed itself is not tested) and froze the state after
-  // that; later steps leave the state as it is (M = I).
+  // that; steps from first_frozen on leave the state as it is (M = I).
   const float r0sq = (float)(a.R0 * a.R0);
   bool live = !(a.turn_stop && k > 0 && inside_r0(s.x, s.y, r0sq));
   bool live_blk = live;
+  int first_frozen = live ? n1 : n0;
   Prop<float, FIELD> pr;
   pr.start(s);
-  pr.init_field(s, f, f.nodes);
+  pr.init_field(s, a.field, a.field.nodes);
+  auto cur = [&]() {
+    State<float> q = s;
+    q.x = pr.px;
+    q.y = pr.py;
+    q.z = pr.pz;
+    q.tx = pr.tx;
+    q.ty = pr.ty;
+    q.tz = pr.tz;
+    return q;
+  };
+  put(0, cur());
+  for (int j = 1; j <= n1 - n0; ++j) {
+    if (live) {
+      pr.step(s, a.field, a.field.nodes, a.h);
+      if (a.turn_stop && inside_r0(pr.px, pr.py, r0sq)) {
+        live = false;
+        first_frozen = n0 + j;
+      }
+    }
+    if ((n0 + j) % kRefineBlock == 0 || n0 + j == a.n_steps) {
+      if (live_blk) pr.fold(s);
+      live_blk = live;
+    }
+    put(j, cur());
+  }
   const int e = a.seed_event[p];
   const int hb = a.ev_off[e];
-  int li = a.segoff[(size_t)k * n + p];
-  const int l1 = a.segoff[(size_t)(k + 1) * n + p];
-  int2 hit = li < l1 ? a.list[(size_t)li * n + p] : make_int2(-1, 0);
-  double T[6][7];
+  const int l0 = a.segoff[(size_t)k * n + p], l1 = a.segoff[(size_t)(k + 1) * n + p];
+  double Phi[7][7], av[7], A[28];
 #pragma unroll
-  for (int r = 0; r < 6; ++r)
+  for (int r = 0; r < 7; ++r) {
+    av[r] = 0.0;
 #pragma unroll
-    for (int c = 0; c < 7; ++c) T[r][c] = r == c ? 1.0 : 0.0;
-  for (int st = n0; st < n1; ++st) {
-    State<float> sn = s;
-    sn.x = pr.px;
-    sn.y = pr.py;
-    sn.z = pr.pz;
-    sn.tx = pr.tx;
-    sn.ty = pr.ty;
-    sn.tz = pr.tz;
-    // a copy of its own, so that the derivative's sums do not share subexpressions with
-    // the step's below and are formed alike wherever step_jacobian is inlined
-    asm volatile("" : "+v"(sn.x), "+v"(sn.y), "+v"(sn.z), "+v"(sn.tx), "+v"(sn.ty), "+v"(sn.tz), "+v"(sn.lam));
-    const bool taken = live;
+    for (int c = 0; c < 7; ++c) Phi[r][c] = r == c ? 1.0 : 0.0;
+  }
+#pragma unroll
+  for (int q = 0; q < 28; ++q) A[q] = 0.0;
+  for (int st = n1 - 1; st >= n0; --st) {
+    const State<float> sn = get(st - n0);
+    const bool frozen = st >= first_frozen;
     float M[7][7];
-    if (taken) {
-      step_jacobian<FIELD>(sn, f, a.h, M);
-    } else {
+    if (frozen) {
 #pragma unroll
       for (int r = 0; r < 7; ++r)
 #pragma unroll
         for (int c = 0; c < 7; ++c) M[r][c] = r == c ? 1.0f : 0.0f;
+    } else {
+      step_jacobian<FIELD>(sn, a.field, a.h, M);
     }
-    if (taken) {
-      pr.step(s, f, f.nodes, a.h);
-      live = !(a.turn_stop && inside_r0(pr.px, pr.py, r0sq));
+    // Phi <- M^T Phi, a <- M^T a (column by column, in place); nothing when frozen
+    if (!frozen) {
+#pragma unroll
+      for (int c = 0; c < 7; ++c) {
+        double col[7];
+#pragma unroll
+        for (int r = 0; r < 7; ++r) {
+          double acc = 0.0;
+#pragma unroll
+          for (int q = 0; q < 7; ++q) acc += (double)M[q][r] * Phi[q][c];
+          col[r] = acc;
+        }
+#pragma unroll
+        for (int r = 0; r < 7; ++r) Phi[r][c] = col[r];
+      }
+      {
+        double col[7];
+#pragma unroll
+        for (int r = 0; r < 7; ++r) {
+          double acc = 0.0;
+#pragma unroll
+          for (int q = 0; q < 7; ++q) acc += (double)M[q][r] * av[q];
+          col[r] = acc;
+        }
+#pragma unroll
+        for (int r = 0; r < 7; ++r) av[r] = col[r];
+      }
+      if constexpr (WANT_S) {
+        // A <- M^T A M over the upper triangle: B = A M by columns, then (M^T B)
+        double nA[28];
+#pragma unroll
+        for (int c = 0; c < 7; ++c) {
+          double b[7];
+#pragma unroll
+          for (int r = 0; r < 7; ++r) {
+            double acc = 0.0;
+#pragma unroll
+            for (int q = 0; q < 7; ++q) acc += A[r <= q ? upper_index(r, q) : upper_index(q, r)] * (double)M[q][c];
+            b[r] = acc;
+          }
+#pragma unroll
+          for (int r = 0; r <= c; ++r) {
+            double acc = 0.0;
+#pragma unroll
+            for (int q = 0; q < 7; ++q) acc += (double)M[q][r] * b[q];
+            nA[upper_index(r, c)] = acc;
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 28; ++q) A[q] = nA[q];
+      }
     }
-    if ((st + 1) % kRefineBlock == 0 || st + 1 == a.n_steps) {
-      if (live_blk) pr.fold(s);
-      live_blk = live;
-    }
-    // hits whose minimum lies on this chord
-    while (hit.x == st) {
-      const int o = hit.y;
+    // sources of the hits whose minimum lies on chord st
+    for (int li = l0; li < l1; ++li) {
+      const int2 it = a.list[(size_t)li * n + p];
+      if (it.x != st) continue;
+      const int o = it.y;
+      const State<float> sn1 = get(st - n0 + 1);
       const HitRec<float> w = a.wire32[a.hits_wire[hb + o]];
-      float p0[3] = {sn.x, sn.y, sn.z}, p1[3] = {pr.px, pr.py, pr.pz};
-      asm volatile("" : "+v"(p0[0]), "+v"(p0[1]), "+v"(p0[2]), "+v"(p1[0]), "+v"(p1[1]), "+v"(p1[2]));
+      const float p0[3] = {sn.x, sn.y, sn.z}, p1[3] = {sn1.x, sn1.y, sn1.z};
       const float m[3] = {w.mx, w.my, w.mz}, u[3] = {w.ux, w.uy, w.uz};
       float sstar, v[3];
       const float d2 = seg_wire_closest(p0, p1, m, u, w.L, sstar, v);
       const float D = sqrtf(d2);
-      const float iv = D > 0.0f ? 1.0f / D : 0.0f;   // D = 0: the derivative is taken as 0
+      if (!(D > 0.0f)) continue;   // D = 0: the derivative is taken as 0
+      const float iv = 1.0f / D;
       const float aa[3] = {(1.0f - sstar) * v[0] * iv, (1.0f - sstar) * v[1] * iv, (1.0f - sstar) * v[2] * iv};
       const float bb[3] = {sstar * v[0] * iv, sstar * v[1] * iv, sstar * v[2] * iv};
       double ev[7];
@@ -404,32 +461,15 @@ __global__ void __launch_bounds__(256, 2) adj_seg_kernel(BwdArgs a) {
         for (int q = 0; q < 3; ++q) acc += (double)M[q][c] * (double)bb[q];
         ev[c] = acc;
       }
-      double* out = a.hitvec + (size_t)li * kHitVals * n + p;
-#pragma unroll
-      for (int c = 0; c < 7; ++c) {
-        double acc = c == 6 ? ev[6] : 0.0;
-#pragma unroll
-        for (int q = 0; q < 6; ++q) acc += T[q][c] * ev[q];
-        out[(size_t)c * n] = acc;
-      }
       const float r = a.resid[p * a.max_hits + o];
-      out[(size_t)7 * n] = a.cgrad ? (double)a.cgrad[p * a.max_hits + o] : 2.0 * (double)r;
-      ++li;
-      hit = li < l1 ? a.list[(size_t)li * n + p] : make_int2(-1, 0);
-    }
-    if (taken) {
+      const double cg = a.cgrad ? (double)a.cgrad[p * a.max_hits + o] : 2.0 * (double)r;
 #pragma unroll
-      for (int c = 0; c < 7; ++c) {
-        double col[6];
+      for (int c = 0; c < 7; ++c) av[c] += cg * ev[c];
+      if constexpr (WANT_S) {
 #pragma unroll
-        for (int r = 0; r < 6; ++r) {
-          double acc = c == 6 ? (double)M[r][6] : 0.0;
+        for (int r2 = 0; r2 < 7; ++r2)
 #pragma unroll
-          for (int q = 0; q < 6; ++q) acc += (double)M[r][q] * T[q][c];
-          col[r] = acc;
-        }
-#pragma unroll
-        for (int r = 0; r < 6; ++r) T[r][c] = col[r];
+          for (int c = r2; c < 7; ++c) A[upper_index(r2, c)] += ev[r2] * ev[c];
       }
     }
   }
@@ -437,77 +477,107 @@ __global__ void __launch_bounds__(256, 2) adj_seg_kernel(BwdArgs a) {
 #pragma unroll
   for (int r = 0; r < 7; ++r)
 #pragma unroll
-    for (int c = 0; c < 7; ++c) out[(size_t)(r * 7 + c) * n] = c == 6 ? (r == 6 ? 1.0 : 0.0) : T[c < 6 ? c : 0][r];
+    for (int c = 0; c < 7; ++c) out[(size_t)(r * 7 + c) * n] = Phi[r][c];
+#pragma unroll
+  for (int r = 0; r < 7; ++r) out[(size_t)(49 + r) * n] = av[r];
+  if constexpr (WANT_S) {
+#pragma unroll
+    for (int q = 0; q < 28; ++q) out[(size_t)(56 + q) * n] = A[q];
+  }
 }
 
-constexpr int kCombineSeeds = 8;   // seeds (waves) per workgroup of adj_combine_kernel
-
-// Per seed, one wave: lambda_0 and S_0 from the segments, last to first, then the seed
-// derivatives through P = dy0/dseed: grad = P^T lambda_0, J^T J = P^T S_0 P. Lane (r, c)
-// of an 8 x 8 grid holds S[r][c], lane (r, 7) lambda_r; the factors of the products come
-// over wave shuffles. (One thread per seed waited out each segment's 84 loads: 200 us for
-// 1024 seeds and 94 segments, now 152 us. 8 neighbouring seeds of a workgroup share the
-// cache lines of the segments' values.)
-__global__ void __launch_bounds__(64 * kCombineSeeds) adj_combine_kernel(BwdArgs a) {
-  __shared__ double s_P[kCombineSeeds][7][5];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane >> 3, c = lane & 7;
+// Per seed: lambda_0 and S_0 from the segments, last to first, then the seed
+// derivatives through P = dy0/dseed: grad = P^T lambda_0, J^T J = P^T S_0 P.
+template <bool WANT_S>
+__global__ void __launch_bounds__(64) adj_combine_kernel(BwdArgs a) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= a.n) return;
   const int64_t n = a.n;
-  const int64_t p0 = (int64_t)blockIdx.x * kCombineSeeds + wave;
-  const int64_t p = p0 < n ? p0 : n - 1;
-  const bool in7 = r < 7 && c < 7;
-  double S = 0.0;
-  auto phi_of = [&](int k) { return in7 ? a.segout[((size_t)k * kSegVals + r * 7 + c) * n + p] : 0.0; };
-  double next = phi_of(a.n_ckpt - 1);
-  int l1 = a.segoff[(size_t)a.n_ckpt * n + p];
+  double lam[7] = {0, 0, 0, 0, 0, 0, 0};
+  double S[28];
+#pragma unroll
+  for (int q = 0; q < 28; ++q) S[q] = 0.0;
   for (int k = a.n_ckpt - 1; k >= 0; --k) {
-    const double phi = next;
-    if (k > 0) next = phi_of(k - 1);
-    const int l0 = a.segoff[(size_t)k * n + p];
-    double acc = 0.0;   // sum e e^T, sum c e
-    for (int li = l0; li < l1; ++li) {
-      const double* h = a.hitvec + (size_t)li * kHitVals * n + p;
-      if (r < 7) acc += h[(size_t)r * n] * h[(size_t)c * n];
+    const double* in = a.segout + (size_t)k * kSegVals * n + p;
+    double Phi[7][7];
+#pragma unroll
+    for (int r = 0; r < 7; ++r)
+#pragma unroll
+      for (int c = 0; c < 7; ++c) Phi[r][c] = in[(size_t)(r * 7 + c) * n];
+    double nl[7];
+#pragma unroll
+    for (int r = 0; r < 7; ++r) {
+      double acc = in[(size_t)(49 + r) * n];
+#pragma unroll
+      for (int c = 0; c < 7; ++c) acc += Phi[r][c] * lam[c];
+      nl[r] = acc;
     }
-    l1 = l0;
-    double B = 0.0;     // Phi [S, lambda]
 #pragma unroll
-    for (int q = 0; q < 7; ++q) B += __shfl(phi, r * 8 + q, 64) * __shfl(S, q * 8 + c, 64);
-    double Sn = acc;    // B Phi^T + sum e e^T
+    for (int r = 0; r < 7; ++r) lam[r] = nl[r];
+    if constexpr (WANT_S) {
+      // S <- Phi S Phi^T + A
+      double B[7][7];   // B = Phi S
 #pragma unroll
-    for (int q = 0; q < 7; ++q) Sn += __shfl(B, r * 8 + q, 64) * __shfl(phi, (c < 7 ? c : 0) * 8 + q, 64);
-    S = c == 7 ? acc + B : Sn;
-    if (r == 7) S = 0.0;
+      for (int r = 0; r < 7; ++r)
+#pragma unroll
+        for (int c = 0; c < 7; ++c) {
+          double acc = 0.0;
+#pragma unroll
+          for (int q = 0; q < 7; ++q) acc += Phi[r][q] * S[q <= c ? upper_index(q, c) : upper_index(c, q)];
+          B[r][c] = acc;
+        }
+#pragma unroll
+      for (int r = 0; r < 7; ++r)
+#pragma unroll
+        for (int c = r; c < 7; ++c) {
+          double acc = in[(size_t)(56 + upper_index(r, c)) * n];
+#pragma unroll
+          for (int q = 0; q < 7; ++q) acc += B[r][q] * Phi[c][q];
+          S[upper_index(r, c)] = acc;
+        }
+    }
   }
   const double* sd = a.seeds5 + 5 * p;
   const double pm = sqrt(sd[2] * sd[2] + sd[3] * sd[3] + sd[4] * sd[4]);
-  if (lane < 35) {
-    const int i = lane / 5, j = lane - 5 * i;
-    double v = 0.0;
-    if (pm >= 1e-3) {
-      const double lam0 = kKappa * a.charge / pm;   // dLambda/dp_j = -Lambda T_j / |p|
-      if (i == 0 && j == 0) v = -a.R0 * sin(sd[0]);
-      if (i == 1 && j == 0) v = a.R0 * cos(sd[0]);
-      if (i == 2 && j == 1) v = 1.0;
-      if (i >= 3 && i < 6 && j >= 2) v = ((i - 3 == j - 2 ? 1.0 : 0.0) - sd[i - 1] / pm * (sd[j] / pm)) / pm;
-      if (i == 6 && j >= 2) v = -lam0 * (sd[j] / pm) / pm;
+  double P[7][5];
+#pragma unroll
+  for (int i = 0; i < 7; ++i)
+#pragma unroll
+    for (int j = 0; j < 5; ++j) P[i][j] = 0.0;
+  if (pm >= 1e-3) {
+    const double T0[3] = {sd[2] / pm, sd[3] / pm, sd[4] / pm};
+    P[0][0] = -a.R0 * sin(sd[0]);
+    P[1][0] = a.R0 * cos(sd[0]);
+    P[2][1] = 1.0;
+    for (int c = 0; c < 3; ++c)
+      for (int q = 0; q < 3; ++q) P[3 + c][2 + q] = ((c == q ? 1.0 : 0.0) - T0[c] * T0[q]) / pm;
+    const double lam0 = kKappa * a.charge / pm;   // dLambda/dp_j = -Lambda T_j / |p|
+    for (int q = 0; q < 3; ++q) P[6][2 + q] = -lam0 * T0[q] / pm;
+  }
+#pragma unroll
+  for (int j = 0; j < 5; ++j) {
+    double acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < 7; ++i) acc += P[i][j] * lam[i];
+    a.grad[p * 5 + j] = acc;
+  }
+  if constexpr (WANT_S) {
+    if (a.jtj) {
+#pragma unroll
+      for (int r = 0; r < 5; ++r)
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          double acc = 0.0;
+#pragma unroll
+          for (int i = 0; i < 7; ++i) {
+            double sp = 0.0;
+#pragma unroll
+            for (int j = 0; j < 7; ++j) sp += S[i <= j ? upper_index(i, j) : upper_index(j, i)] * P[j][c];
+            acc += P[i][r] * sp;
+          }
+          a.jtj[p * 25 + r * 5 + c] = acc;
+        }
     }
-    s_P[wave][i][j] = v;
-  }
-  __syncthreads();
-  // lane (i, j), j < 5: (S P)[i][j]; then lane (i, j), i, j < 5: (P^T (S P))[i][j]
-  double sp = 0.0;
-#pragma unroll
-  for (int q = 0; q < 7; ++q) sp += __shfl(S, r * 8 + q, 64) * s_P[wave][q][c < 5 ? c : 0];
-  double g = 0.0, jj = 0.0;
-#pragma unroll
-  for (int q = 0; q < 7; ++q) {
-    const double pr = s_P[wave][q][r < 5 ? r : 0];
-    jj += pr * __shfl(sp, q * 8 + c, 64);
-    g += pr * __shfl(S, q * 8 + 7, 64);
-  }
-  if (p0 < n && r < 5) {
-    if (c == 7) a.grad[p * 5 + r] = g;
-    if (c < 5 && a.jtj) a.jtj[p * 25 + r * 5 + c] = jj;
   }
 }
 
@@ -567,46 +637,29 @@ __global__ void gn_solve_kernel(int64_t n, const double* __restrict__ jtj, const
   }
 }
 
-// Take the first trial (alpha = 1, 1/2, ...) that lowers Phi: its seed and Phi become the
-// current ones; pick[p] is its place among the trials, -1 if none does.
-__global__ void gn_accept_kernel(int64_t n, const double* __restrict__ trials, const double* __restrict__ phi_trial,
-                                 double* __restrict__ seeds, double* __restrict__ phi_cur,
-                                 int64_t* __restrict__ pick) {
+// Take the first trial (alpha = 1, 1/2, ...) that lowers Phi; its forward outputs
+// (checkpoints, residuals, argmin chords) become the current ones, so the next
+// iteration's adjoint needs no forward pass of its own.
+__global__ void gn_accept_kernel(int64_t n, int n_ckpt, int max_hits, const double* __restrict__ trials,
+                                 const double* __restrict__ phi_trial, const float* __restrict__ tape6,
+                                 const float* __restrict__ resid6, const int32_t* __restrict__ argmin6,
+                                 double* __restrict__ seeds, double* __restrict__ phi_cur, float* __restrict__ tape,
+                                 float* __restrict__ resid, int32_t* __restrict__ argmin) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n) return;
-  int64_t took = -1;
-  for (int k = 0; k < 6 && took < 0; ++k) {
+  for (int k = 0; k < 6; ++k) {
     const int64_t g = p * 6 + k;   // trials of a seed are adjacent
-    if (phi_trial[g] < phi_cur[p]) {
-      phi_cur[p] = phi_trial[g];
+    const double ph = phi_trial[g];
+    if (ph < phi_cur[p]) {
+      phi_cur[p] = ph;
       for (int d = 0; d < 5; ++d) seeds[p * 5 + d] = trials[g * 5 + d];
-      took = g;
-    }
-  }
-  pick[p] = took;
-}
-
-// The accepted trials' forward outputs (checkpoints, residuals, argmin chords) become the
-// current ones, so the next iteration's adjoint needs no forward pass of its own. Blocks
-// y < rows copy one checkpoint field of every seed, the others one hit each. (One thread
-// per seed took 360 us for 1024 seeds, now 13 us with the pick.)
-__global__ void __launch_bounds__(256)
-gn_take_kernel(int64_t n, int rows, int max_hits, const int64_t* __restrict__ pick, const float* __restrict__ tape6,
-               const float* __restrict__ resid6, const int32_t* __restrict__ argmin6, float* __restrict__ tape,
-               float* __restrict__ resid, int32_t* __restrict__ argmin) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int y = blockIdx.y; y < rows + max_hits; y += gridDim.y) {
-    if (y < rows) {
-      if (i < n && pick[i] >= 0) tape[(size_t)y * n + i] = tape6[(size_t)y * 6 * n + pick[i]];
-    } else {
-      // the hits as one flat range, in slices of n values
-      const int64_t f = (int64_t)(y - rows) * n + i;
-      const int64_t p = f / max_hits;
-      if (i < n && pick[p] >= 0) {
-        const int64_t o = f - p * max_hits;
-        resid[f] = resid6[pick[p] * max_hits + o];
-        argmin[f] = argmin6[pick[p] * max_hits + o];
+      for (int c = 0; c < n_ckpt; ++c)
+        for (int q = 0; q < 13; ++q) tape[((size_t)c * 13 + q) * n + p] = tape6[((size_t)c * 13 + q) * 6 * n + g];
+      for (int o = 0; o < max_hits; ++o) {
+        resid[p * max_hits + o] = resid6[g * max_hits + o];
+        argmin[p * max_hits + o] = argmin6[g * max_hits + o];
       }
+      break;
     }
   }
 }
@@ -650,6 +703,7 @@ hipError_t refine_ckpt_buffers(rkn_ctx* c, int ckpt) {
   hipError_t e;
   if ((e = c->r_tape.ensure(sizeof(float) * 13 * n * nk)) != hipSuccess ||
       (e = c->r_tape6.ensure(sizeof(float) * 13 * 6 * n * nk)) != hipSuccess ||
+      (e = c->r_segbuf.ensure(sizeof(float) * 6 * n * (size_t)(ckpt + 1) * nk)) != hipSuccess ||
       (e = c->r_segoff.ensure(sizeof(int32_t) * n * (nk + 1))) != hipSuccess ||
       (e = c->r_segout.ensure(sizeof(double) * kSegVals * n * nk)) != hipSuccess)
     return e;
@@ -698,21 +752,29 @@ hipError_t refine_backward(rkn_ctx* c, const float* cgrad, bool want_S) {
   b.argmin = c->r_argmin.as<int32_t>();
   b.cgrad = cgrad;
   b.max_hits = c->max_hits_event > 0 ? c->max_hits_event : 1;
-  b.hitvec = c->r_hitvec.as<double>();
+  b.segbuf = c->r_segbuf.as<float>();
   b.segoff = c->r_segoff.as<int32_t>();
   b.list = c->r_list.as<int2>();
   b.segout = c->r_segout.as<double>();
   b.grad = c->r_grad.as<double>();
   b.jtj = want_S ? c->r_jtj.as<double>() : nullptr;
-  const size_t smem = c->field_kind == 1 ? padded_field_nodes(c->nr, c->nz) * sizeof(float2) : 0;
-  auto seg = c->field_kind == 0 ? adj_seg_kernel<0> : adj_seg_kernel<1>;
-  const hipError_t e = hipFuncSetAttribute((const void*)seg, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(adj_prep_kernel, dim3((unsigned)((b.n + kPrepSeeds - 1) / kPrepSeeds)), dim3(64 * kPrepSeeds), 0,
-                     c->stream, b);
-  hipLaunchKernelGGL(seg, dim3((unsigned)((b.n * b.n_ckpt + 255) / 256)), dim3(256), smem, c->stream, b);
-  hipLaunchKernelGGL(adj_combine_kernel, dim3((unsigned)((b.n + kCombineSeeds - 1) / kCombineSeeds)),
-                     dim3(64 * kCombineSeeds), 0, c->stream, b);
+  const dim3 blk(64);
+  const dim3 g1((unsigned)((b.n + 63) / 64));
+  const dim3 gs((unsigned)((b.n * b.n_ckpt + 63) / 64));
+  hipLaunchKernelGGL(adj_prep_kernel, g1, blk, 0, c->stream, b);
+  if (want_S) {
+    if (c->field_kind == 0)
+      hipLaunchKernelGGL((adj_seg_kernel<0, true>), gs, blk, 0, c->stream, b);
+    else
+      hipLaunchKernelGGL((adj_seg_kernel<1, true>), gs, blk, 0, c->stream, b);
+    hipLaunchKernelGGL(adj_combine_kernel<true>, g1, blk, 0, c->stream, b);
+  } else {
+    if (c->field_kind == 0)
+      hipLaunchKernelGGL((adj_seg_kernel<0, false>), gs, blk, 0, c->stream, b);
+    else
+      hipLaunchKernelGGL((adj_seg_kernel<1, false>), gs, blk, 0, c->stream, b);
+    hipLaunchKernelGGL(adj_combine_kernel<false>, g1, blk, 0, c->stream, b);
+  }
   return hipGetLastError();
 }
 
@@ -796,8 +858,6 @@ rkn_status rkn_refine_setup(rkn_ctx* c, const rkn_scan_params* p, int64_t n_seed
       (e = c->r_phi6.ensure(sizeof(double) * 6 * n)) != hipSuccess ||
       (e = c->r_phicur.ensure(sizeof(double) * n)) != hipSuccess ||
       (e = c->r_list.ensure(sizeof(int2) * n * H)) != hipSuccess ||
-      (e = c->r_hitvec.ensure(sizeof(double) * kHitVals * n * H)) != hipSuccess ||
-      (e = c->r_pick.ensure(sizeof(int64_t) * n)) != hipSuccess ||
       (e = c->r_grad.ensure(sizeof(double) * 5 * n)) != hipSuccess ||
       (e = c->r_jtj.ensure(sizeof(double) * 25 * n)) != hipSuccess ||
       (e = c->r_cgrad.ensure(sizeof(float) * n * H)) != hipSuccess)
@@ -977,13 +1037,10 @@ rkn_status rkn_gn_refine(rkn_ctx* c, int32_t iters, const double* scale, double*
     }
     if (e == hipSuccess) e = refine_forward(c, true, 0, true);
     if (e == hipSuccess) {
-      hipLaunchKernelGGL(gn_accept_kernel, g1, b1, 0, c->stream, n, c->r_trials.as<double>(), c->r_phi6.as<double>(),
-                         c->r_seeds.as<double>(), c->r_phicur.as<double>(), c->r_pick.as<int64_t>());
-      const int rows = c->r_nckpt * 13;
-      hipLaunchKernelGGL(gn_take_kernel, dim3(g1.x, (unsigned)std::min(rows + H, 65535)), b1, 0, c->stream, n, rows, H,
-                         c->r_pick.as<int64_t>(), c->r_tape6.as<float>(), c->r_resid6.as<float>(),
-                         c->r_argmin6.as<int32_t>(), c->r_tape.as<float>(), c->r_resid.as<float>(),
-                         c->r_argmin.as<int32_t>());
+      hipLaunchKernelGGL(gn_accept_kernel, g1, b1, 0, c->stream, n, c->r_nckpt, H, c->r_trials.as<double>(),
+                         c->r_phi6.as<double>(), c->r_tape6.as<float>(), c->r_resid6.as<float>(),
+                         c->r_argmin6.as<int32_t>(), c->r_seeds.as<double>(), c->r_phicur.as<double>(),
+                         c->r_tape.as<float>(), c->r_resid.as<float>(), c->r_argmin.as<int32_t>());
       e = hipGetLastError();
     }
   }
