@@ -1,4 +1,4 @@
-// Batched seed scan of every uploaded event: Hough windows -> seed tiles -> one
+// Batched seed scan of every uploaded event: Hough windows -> seed chunks -> one
 // persistent scan launch -> per-event argmin, captured once as HIP graphs and
 // replayed per batch (section 2.1 seeding and section 2.2 scan, many events).
 //

@@ -220,12 +220,12 @@ struct rkn_ctx {
   float r_tune_ms[4] = {0, 0, 0, 0};   // adjoint sweep times of the checkpoint tuner
   rkn::DevBuf r_seeds, r_seeds0, r_trials, r_event, r_segs, r_segs6, r_evc, r_evc6, r_ident, r_base6, r_mask, r_resid,
       r_argmin, r_resid6, r_argmin6, r_phi, r_phi6, r_phicur, r_tape, r_segbuf, r_list, r_grad, r_jtj, r_cgrad,
-      r_slab, r_counter, r_tape6, r_segoff, r_segout, r_accept;
+      r_slab, r_counter, r_tape6, r_segoff, r_segout, r_pick;
 
   rkn::DevBuf* refine_buffers_[30] = {&r_seeds,  &r_seeds0, &r_trials, &r_event,  &r_segs,   &r_segs6,  &r_evc,   &r_evc6, &r_ident,
                                       &r_base6,  &r_mask,   &r_resid,  &r_argmin, &r_resid6, &r_argmin6, &r_phi,
                                       &r_phi6,   &r_phicur, &r_tape,   &r_segbuf, &r_list,   &r_grad,   &r_jtj,
-                                      &r_cgrad,  &r_slab,   &r_counter, &r_tape6, &r_segoff, &r_segout, &r_accept};
+                                      &r_cgrad,  &r_slab,   &r_counter, &r_tape6, &r_segoff, &r_segout, &r_pick};
   void refine_release() {
     for (rkn::DevBuf* b : refine_buffers_) b->release();
     r_ready = r_at_setup = false;
