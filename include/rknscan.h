@@ -191,7 +191,7 @@ rkn_status rkn_scan_windows(rkn_ctx *ctx, const rkn_scan_params *p, int32_t n_wi
  * running minima) is one 256 MiB array per GPU, held from the library's load until
  * the process ends and shared by every call on that GPU: calls on one context's
  * stream are ordered, calls that overlap on one GPU from other streams race. The
- * call allocates nothing. RKN_E_CAPACITY when the windows, their tiles and the
+ * call allocates nothing. RKN_E_CAPACITY when the windows, their chunks and the
  * running minima of one workgroup do not fit the array; when the minima of a full
  * persistent grid do not fit, fewer workgroups run. */
 rkn_status rkn_scan_windows_noalloc(rkn_ctx *ctx, const rkn_scan_params *p, int32_t n_windows,
