@@ -257,15 +257,18 @@ __device__ __forceinline__ int upper_index(int r, int c) {   // r <= c
 
 constexpr int kPrepSeeds = 4;   // seeds (waves) per workgroup of adj_prep_kernel
 
-// Group each seed's inlier hits by the segment of their argmin chord, in hit order within
-// one, one wave per seed: rank by counting over the keys in LDS; segoff[k] = the first list
-// slot of segment k. (One thread per seed walked its row of argmin chords three times
+// Group each seed's inlier hits by the segment of their argmin chord, in the order in which
+// the backward sweep meets them (last chord first, a chord's hits in hit order), one wave
+// per seed: rank by counting over the keys in LDS; segoff[k] = the first list slot of
+// segment k. (One thread per seed walked its row of argmin chords three times
 // through global counters: 190 us for 1024 seeds, now 22 us.)
 __global__ void __launch_bounds__(64 * kPrepSeeds) adj_prep_kernel(BwdArgs a) {
   __shared__ int64_t s_key[kPrepSeeds][RKN_MAX_HITS_PER_EVENT];
   __shared__ int s_seg[kPrepSeeds][RKN_MAX_HITS_PER_EVENT];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t p = (int64_t)blockIdx.x * kPrepSeeds + wave, n = a.n;
+  // a chord's number with the chords of its segment in reverse (its own inverse)
+  auto mirrored = [&](int64_t st) { return 2 * (st / a.ckpt) * a.ckpt + a.ckpt - 1 - st; };
   int nh = 0, found = 0;
   if (p < n) {
     const int e = a.seed_event[p];
@@ -273,7 +276,7 @@ __global__ void __launch_bounds__(64 * kPrepSeeds) adj_prep_kernel(BwdArgs a) {
   }
   for (int o = lane; o < nh; o += 64) {
     const int st = a.argmin[p * a.max_hits + o];
-    s_key[wave][o] = st >= 0 ? ((int64_t)(st / a.ckpt) << 10) | o : INT64_MAX;
+    s_key[wave][o] = st >= 0 ? (mirrored(st) << 10) | o : INT64_MAX;
   }
   __syncthreads();
   for (int o = lane; o < nh; o += 64) {
@@ -281,8 +284,8 @@ __global__ void __launch_bounds__(64 * kPrepSeeds) adj_prep_kernel(BwdArgs a) {
     if (key == INT64_MAX) continue;
     int rank = 0;
     for (int j = 0; j < nh; ++j) rank += s_key[wave][j] < key;
-    s_seg[wave][rank] = (int)(key >> 10);
-    a.list[(size_t)rank * n + p] = make_int2(a.argmin[p * a.max_hits + o], o);
+    s_seg[wave][rank] = (int)((key >> 10) / a.ckpt);
+    a.list[(size_t)rank * n + p] = make_int2((int)mirrored(key >> 10), o);
     ++found;
   }
 #pragma unroll
@@ -306,8 +309,22 @@ __global__ void __launch_bounds__(64 * kPrepSeeds) adj_prep_kernel(BwdArgs a) {
 // then walk its steps backwards from lambda = 0, S = 0 at the segment end:
 //   Phi <- M_n^T Phi,  a <- M_n^T a + sum c e,  A <- M_n^T A M_n + sum e e^T,
 // so that lambda(start) = Phi lambda(end) + a and S(start) = Phi S(end) Phi^T + A.
+//
+// Bound by FP64 and FP32 VALU work on one wave per SIMD with S (362 registers), two
+// without (256), and by what such a wave waits for: so the field map is staged in LDS,
+// and the hits come in the order of the walk, one list entry held at a time. (Gradient of
+// 4096 seeds, 94 segments, map from memory, the segment's whole list read at every step
+// and one wave per SIMD: 2.07 ms; this way 1.37. With S, 1024 seeds: 0.80 and 0.73.)
 template <int FIELD, bool WANT_S>
-__global__ void __launch_bounds__(64) adj_seg_kernel(BwdArgs a) {
+__global__ void __launch_bounds__(256, WANT_S ? 1 : 2) adj_seg_kernel(BwdArgs a) {
+  extern __shared__ float2 s_nodes[];
+  FieldDev f = a.field;
+  if constexpr (FIELD == 1) {
+    const int nn = (int)padded_field_nodes(f.nr, f.nz);
+    for (int i = threadIdx.x; i < nn; i += blockDim.x) s_nodes[i] = a.field.nodes[i];
+    f.nodes = s_nodes;
+    __syncthreads();
+  }
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t n = a.n;
   if (idx >= n * a.n_ckpt) return;
@@ -351,7 +368,7 @@ __global__ void __launch_bounds__(64) adj_seg_kernel(BwdArgs a) {
   int first_frozen = live ? n1 : n0;
   Prop<float, FIELD> pr;
   pr.start(s);
-  pr.init_field(s, a.field, a.field.nodes);
+  pr.init_field(s, f, f.nodes);
   auto cur = [&]() {
     State<float> q = s;
     q.x = pr.px;
@@ -365,7 +382,7 @@ __global__ void __launch_bounds__(64) adj_seg_kernel(BwdArgs a) {
   put(0, cur());
   for (int j = 1; j <= n1 - n0; ++j) {
     if (live) {
-      pr.step(s, a.field, a.field.nodes, a.h);
+      pr.step(s, f, f.nodes, a.h);
       if (a.turn_stop && inside_r0(pr.px, pr.py, r0sq)) {
         live = false;
         first_frozen = n0 + j;
@@ -379,7 +396,9 @@ __global__ void __launch_bounds__(64) adj_seg_kernel(BwdArgs a) {
   }
   const int e = a.seed_event[p];
   const int hb = a.ev_off[e];
-  const int l0 = a.segoff[(size_t)k * n + p], l1 = a.segoff[(size_t)(k + 1) * n + p];
+  int li = a.segoff[(size_t)k * n + p];
+  const int l1 = a.segoff[(size_t)(k + 1) * n + p];
+  int2 it = li < l1 ? a.list[(size_t)li * n + p] : make_int2(-1, 0);
   double Phi[7][7], av[7], A[28];
 #pragma unroll
   for (int r = 0; r < 7; ++r) {
@@ -399,7 +418,7 @@ __global__ void __launch_bounds__(64) adj_seg_kernel(BwdArgs a) {
 #pragma unroll
         for (int c = 0; c < 7; ++c) M[r][c] = r == c ? 1.0f : 0.0f;
     } else {
-      step_jacobian<FIELD>(sn, a.field, a.h, M);
+      step_jacobian<FIELD>(sn, f, a.h, M);
     }
     // Phi <- M^T Phi, a <- M^T a (column by column, in place); nothing when frozen
     if (!frozen) {
@@ -454,10 +473,10 @@ __global__ void __launch_bounds__(64) adj_seg_kernel(BwdArgs a) {
       }
     }
     // sources of the hits whose minimum lies on chord st
-    for (int li = l0; li < l1; ++li) {
-      const int2 it = a.list[(size_t)li * n + p];
-      if (it.x != st) continue;
+    while (it.x == st) {
       const int o = it.y;
+      ++li;
+      it = li < l1 ? a.list[(size_t)li * n + p] : make_int2(-1, 0);
       const State<float> sn1 = get(st - n0 + 1);
       const HitRec<float> w = a.wire32[a.hits_wire[hb + o]];
       const float p0[3] = {sn.x, sn.y, sn.z}, p1[3] = {sn1.x, sn1.y, sn1.z};
@@ -793,22 +812,15 @@ hipError_t refine_backward(rkn_ctx* c, const float* cgrad, bool want_S) {
   b.jtj = want_S ? c->r_jtj.as<double>() : nullptr;
   const dim3 blk(64);
   const dim3 g1((unsigned)((b.n + 63) / 64));
-  const dim3 gs((unsigned)((b.n * b.n_ckpt + 63) / 64));
+  const size_t smem = c->field_kind == 1 ? padded_field_nodes(c->nr, c->nz) * sizeof(float2) : 0;
+  auto seg = want_S ? (c->field_kind == 0 ? adj_seg_kernel<0, true> : adj_seg_kernel<1, true>)
+                    : (c->field_kind == 0 ? adj_seg_kernel<0, false> : adj_seg_kernel<1, false>);
+  const hipError_t e = hipFuncSetAttribute((const void*)seg, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(adj_prep_kernel, dim3((unsigned)((b.n + kPrepSeeds - 1) / kPrepSeeds)), dim3(64 * kPrepSeeds), 0,
                      c->stream, b);
-  if (want_S) {
-    if (c->field_kind == 0)
-      hipLaunchKernelGGL((adj_seg_kernel<0, true>), gs, blk, 0, c->stream, b);
-    else
-      hipLaunchKernelGGL((adj_seg_kernel<1, true>), gs, blk, 0, c->stream, b);
-    hipLaunchKernelGGL(adj_combine_kernel<true>, g1, blk, 0, c->stream, b);
-  } else {
-    if (c->field_kind == 0)
-      hipLaunchKernelGGL((adj_seg_kernel<0, false>), gs, blk, 0, c->stream, b);
-    else
-      hipLaunchKernelGGL((adj_seg_kernel<1, false>), gs, blk, 0, c->stream, b);
-    hipLaunchKernelGGL(adj_combine_kernel<false>, g1, blk, 0, c->stream, b);
-  }
+  hipLaunchKernelGGL(seg, dim3((unsigned)((b.n * b.n_ckpt + 255) / 256)), dim3(256), smem, c->stream, b);
+  hipLaunchKernelGGL(want_S ? adj_combine_kernel<true> : adj_combine_kernel<false>, g1, blk, 0, c->stream, b);
   return hipGetLastError();
 }
 
