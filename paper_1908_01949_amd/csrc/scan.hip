@@ -72,7 +72,7 @@ struct ScanArgs {
   int n_seg;
   const int32_t* n_seg_dev;   // if set, the segment count is read here (captured launches)
   const int64_t* ev_chunk;    // first chunk of each event [n_events + 1]
-  int walk;                   // 1: windows walked in scan order, lanes out of reach in z not culled
+  int walk;                   // 1: windows walked in scan order, lanes out of reach in z not culled; -1: not decided
   int64_t chunk0, n_chunks;   // the chunks to scan: [chunk0, chunk0 + n_chunks)
   const int64_t* n_chunks_dev;   // if set, n_chunks is read here
   const WindowDev* windows;
@@ -1486,7 +1486,8 @@ static int scan_waves(const rkn_ctx* c, int precision, int B) {
 // gains nothing from either (10 windows of 8^5..12^5 seeds: 0.97-1.02) and keeps the
 // grid's order, in which the wave's lists, and with them the rounding of each distance,
 // are those of the seeds' own neighbours; so do explicit seeds, whose order is the
-// caller's.
+// caller's. Decided once for a scan: the parts of one that runs in several launches share
+// the windows' chunks, which mean other seeds in the other order.
 static int walks(const ScanArgs& a, bool longer) {
   return longer || (!a.seeds5 && (a.n_seg_dev || a.n_seg > 1)) ? 1 : 0;
 }
@@ -1511,7 +1512,7 @@ static hipError_t launch_scan_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, boo
   const int per_cu = resident_per_cu(c, (const void*)kern, TILE, smem);
   if (per_cu < 1) return hipErrorInvalidConfiguration;
   int64_t grid = (int64_t)per_cu * c->n_cu;
-  a.walk = walks(a, max_chunks > grid * WAVES);
+  if (a.walk < 0) a.walk = walks(a, max_chunks > grid * WAVES);
   if (grid > max_chunks) grid = max_chunks;
   if (grid < 1) grid = 1;
   a.slab_stride = (int64_t)(c->max_hits_event > 0 ? c->max_hits_event : 1) * TILE;
@@ -1589,7 +1590,6 @@ static bool launch_pipe_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, bool allo
   a.hits_bytes = (int)hits_lds_bytes(c, sizeof(R));
   a.sect_bytes = (int)sect_table_bytes(c);
   a.touch_words = touch_words(c);
-  a.walk = walks(a, false);
   a.n_pairs = n;
   a.n_con = con;
   a.pair_bytes = (int)pair;
@@ -1602,6 +1602,7 @@ static bool launch_pipe_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, bool allo
     if ((*err = slab_buf->ensure(bytes)) != hipSuccess) return true;
     a.mscratch = slab_buf->p;
   }
+  if (a.walk < 0) a.walk = walks(a, false);
   if (alloc_only) return true;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), smem, c->stream, a);
   *err = hipGetLastError();
@@ -1685,6 +1686,7 @@ static ScanArgs base_args(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& 
   a.chunk0 = w.chunk0;
   a.n_chunks = w.n_chunks;
   a.n_chunks_dev = w.n_chunks_dev;
+  a.walk = -1;
   a.windows = w.windows;
   a.seeds5 = w.seeds5;
   a.perm = w.perm;
@@ -1791,12 +1793,21 @@ hipError_t launch_scan_dev(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs&
 hipError_t launch_scan_raw(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& w, double* d_score, int32_t* d_nin,
                            int64_t* d_best_i, double* d_best_e, ArgminPart* d_parts, int64_t max_parts,
                            unsigned long long* d_queue, void* d_slab, size_t slab_bytes) {
-  // as many launches as the argmin partials need; each lowers the events' best
+  // as many launches as the argmin partials need; each lowers the events' best, and all
+  // walk the windows as one launch of the whole scan would
+  int walk = -1;
+  if (w.n_chunks > max_parts) {
+    ScanArgs whole = scan_args(c, p, w, d_score, d_nin, d_parts, d_queue);
+    const hipError_t e = dispatch_scan(c, p, whole, w.n_chunks, true, nullptr, d_slab, slab_bytes);
+    if (e != hipSuccess) return e;
+    walk = whole.walk;
+  }
   for (int64_t c0 = 0; c0 < w.n_chunks || c0 == 0; c0 += max_parts) {
     ScanSegs part = w;
     part.chunk0 = c0;
     part.n_chunks = std::min(max_parts, w.n_chunks - c0);
     ScanArgs a = scan_args(c, p, part, d_score, d_nin, d_parts, d_queue);
+    a.walk = walk;
     if (part.n_chunks > 0) {
       const hipError_t e = dispatch_scan(c, p, a, part.n_chunks, false, nullptr, d_slab, slab_bytes);
       if (e != hipSuccess) return e;
