@@ -557,6 +557,18 @@ __device__ __forceinline__ int find_seg(const Seg* segs, int n_seg, int64_t ch) 
   return lo;
 }
 
+// The same from segment lo on, which starts at or before ch: by doubling steps, since the
+// next chunk of a part lies in the same or the next segment, and one from the queue
+// anywhere in the event (an event may have 10^5 one-point windows).
+__device__ __forceinline__ int find_seg_from(const Seg* segs, int n_seg, int lo, int64_t ch) {
+  int step = 1;
+  while (lo + step < n_seg && segs[lo + step].chunk0 <= ch) {
+    lo += step;
+    step *= 2;
+  }
+  return lo + find_seg(segs + lo, min(step, n_seg - lo), ch);
+}
+
 // One block of fixed steps of a wave's lanes: the points into the lanes' columns, the
 // radial range of the block (r2min, r2max), and the block's increments into the origin
 // (the folded position, within an ulp of the last one, ends the block's last chord and
@@ -1011,11 +1023,8 @@ __global__ void __launch_bounds__(64 * WAVES) scan_kernel(ScanArgs a) {
     for (;;) {
       if (lane == 0) {
         const int64_t ch = next_chunk(a, sh);
-        int sg = sh.seg;
-        if (ch >= 0)
-          while (a.segs[sg + 1].chunk0 <= ch) ++sg;
         s_chunk[wave] = ch;
-        s_seg[wave] = sg;
+        s_seg[wave] = ch < 0 ? 0 : find_seg_from(a.segs, a.n_seg_dev ? *a.n_seg_dev : a.n_seg, sh.seg, ch);
       }
       wave_sync();
       if (s_chunk[wave] < 0) break;
