@@ -1562,6 +1562,9 @@ template <typename R, int FIELD, int B, int COLS, int MODE, bool QUAD = false>
 static bool launch_pipe_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, bool alloc_only, DevBuf* slab_buf,
                           void* raw_slab, size_t raw_bytes, hipError_t* err) {
   if (a.work || a.h_max > 0 || max_chunks < 1) return false;
+  // what scan_kernel's narrowest shape has no room for is refused for any number of seeds
+  if (scan_lds_bytes(c, sizeof(R), FIELD, B, sizeof(R) == 8 || FIELD == 0 ? 4 : 8) + 256 > (size_t)c->max_lds_block)
+    return false;
   auto kern = a.turn_stop ? pipe_kernel<R, FIELD, B, COLS, MODE, 1, QUAD> : pipe_kernel<R, FIELD, B, COLS, MODE, 0, QUAD>;
   constexpr int prod = QUAD ? COLS / 16 : 1;   // producers of a pair
   const size_t field = field_lds_bytes(c, FIELD), room = (size_t)c->max_lds_block - 512;
