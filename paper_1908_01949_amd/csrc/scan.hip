@@ -964,12 +964,24 @@ __device__ __forceinline__ S slab_empty() {
   }
 }
 
+// Waves per SIMD that scan_kernel's registers must leave room for. The FP32 instances in the
+// uniform field come out at 125 to 130 registers; 128 hold a fourth workgroup on a CU
+// wherever the LDS does (8 layers, 40 hits, 12^5 seeds: 1.30 ms past 128, 1.16 within;
+// adaptive steps, 18 layers, 300 events of 5^5 seeds: 2.63 and 2.21 ms). The others: what a
+// workgroup needs.
+template <typename R, int FIELD, int B, int WAVES, int MODE, int VAR, bool COUNT>
+constexpr int waves_per_simd() {
+  const bool four = sizeof(R) == 4 && FIELD == 0 && MODE == 0 && !COUNT && (VAR != 2 || B == 4);
+  return four ? 4 : (WAVES + 3) / 4;
+}
+
 // VAR 0: fixed steps over the whole path; 1: fixed steps, the track ends with its
 // turn partition; 2: adaptive step size (scan mode only), turn_stop as given.
 // COUNT: the instance that also counts its work (seed-steps, sphere tests, chord
 // distances) into a.work; the timed instances leave it out.
 template <typename R, int FIELD, int B, int WAVES, int MODE, int VAR, bool COUNT = false>
-__global__ void __launch_bounds__(64 * WAVES) scan_kernel(ScanArgs a) {
+__global__ void __launch_bounds__(64 * WAVES, (waves_per_simd<R, FIELD, B, WAVES, MODE, VAR, COUNT>()))
+scan_kernel(ScanArgs a) {
   constexpr int TILE = 64 * WAVES;
   // MODE 0: the scan (score E). MODE 1: the refinement forward pass (FP32 only):
   // argmin chords, checkpoints and inlier residuals.
