@@ -187,7 +187,7 @@ rkn_status rkn_scan_windows(rkn_ctx *ctx, const rkn_scan_params *p, int32_t n_wi
  * memory (code under stream capture, tight serving loops, harnesses that forbid it):
  * the same scan and outputs, which must be device pointers (p->ptr_flags has
  * RKN_PTR_DEVICE; best_index and best_score are required, score and n_in may be
- * NULL). Its work memory (device windows, seed chunks, argmin partials, chunk queue,
+ * NULL). Its work memory (device windows, seed chunks, argmin partials, division of the chunks,
  * running minima) is one 256 MiB array per GPU, held from the library's load until
  * the process ends and shared by every call on that GPU: calls on one context's
  * stream are ordered, calls that overlap on one GPU from other streams race. The

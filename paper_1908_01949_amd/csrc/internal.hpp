@@ -318,7 +318,7 @@ hipError_t launch_topk(rkn_ctx* c, const double* d_score, const long long* d_seg
                        const int32_t* d_win_off, int n_seg, const int32_t* d_win_total, int k, int64_t* d_idx,
                        double* d_sc, double* d_seed, double* d_step = nullptr);
 
-// Scratch of one user of launch_scan_dev: argmin partials, chunk queue, slab.
+// Scratch of one user of launch_scan_dev: argmin partials, division of the chunks, slab.
 struct ScanScratch {
   DevBuf* parts;
   DevBuf* counter;
@@ -332,13 +332,15 @@ hipError_t launch_scan_dev(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs&
                            int64_t* d_best_i, double* d_best_e, bool alloc_only, const ScanScratch* scratch = nullptr);
 
 // Scan whose work memory the caller provides (no allocation): max_parts >= 1 argmin
-// partials (chunks per launch), the chunk queue, and slab_bytes of slab memory for the
-// running minima (the persistent grid is capped to the workgroup slabs that fit;
-// hipErrorInvalidValue when not even one fits). Segments and windows already on the
-// device.
+// partials (chunks per launch), scan_plan_bytes for the division of the chunks, and
+// slab_bytes of slab memory for the running minima (the persistent grid is capped to the
+// workgroup slabs that fit; hipErrorInvalidValue when not even one fits). Segments and
+// windows already on the device.
 hipError_t launch_scan_raw(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& w, double* d_score, int32_t* d_nin,
                            int64_t* d_best_i, double* d_best_e, ArgminPart* d_parts, int64_t max_parts,
-                           unsigned long long* d_queue, void* d_slab, size_t slab_bytes);
+                           void* d_plan, void* d_slab, size_t slab_bytes);
+// Bytes of the division of a launch's chunks (a few words per event).
+size_t scan_plan_bytes(const rkn_ctx* c);
 // Slab bytes one scan workgroup needs for these parameters (block size resolved).
 size_t scan_slab_bytes_per_workgroup(const rkn_ctx* c, const rkn_scan_params* p);
 

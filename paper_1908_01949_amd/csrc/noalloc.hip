@@ -1,7 +1,7 @@
 // rkn_scan_windows_noalloc: the window scan of rkn_scan_windows for callers that
 // cannot allocate device memory (code under stream capture, tight serving loops,
 // harnesses that forbid hipMalloc). Its work memory -- the device windows, their
-// segments, the per-event chunk offsets, the argmin partials, the chunk queue and the
+// segments, the per-event chunk offsets, the argmin partials, the division of the chunks and the
 // slab of running minima -- lives in one file-scope device array per GPU, held from
 // the library's load until the process ends. Nothing in the call allocates.
 //
@@ -85,8 +85,8 @@ rkn_status rkn_scan_windows_noalloc(rkn_ctx* c, const rkn_scan_params* p, int32_
   const size_t o_win = 0;
   const size_t o_segs = o_win + align256(sizeof(WindowDev) * wins.size());
   const size_t o_evc = o_segs + align256(sizeof(Seg) * n_seg);
-  const size_t o_queue = o_evc + align256(sizeof(int64_t) * list.ev_chunk.size());
-  const size_t o_parts = o_queue + 256;
+  const size_t o_plan = o_evc + align256(sizeof(int64_t) * list.ev_chunk.size());
+  const size_t o_parts = o_plan + align256(scan_plan_bytes(c));
   const size_t per_wg = scan_slab_bytes_per_workgroup(c, &q);
   // the limit that callers know: 48 bytes for every workgroup's worth of seeds beside
   // the windows and one workgroup's minima
@@ -122,7 +122,7 @@ rkn_status rkn_scan_windows_noalloc(rkn_ctx* c, const rkn_scan_params* p, int32_
   segs.windows = reinterpret_cast<const WindowDev*>(base + o_win);
   e = launch_scan_raw(c, &q, segs, score, n_in, best_index, best_score,
                       reinterpret_cast<ArgminPart*>(base + o_parts), max_parts,
-                      reinterpret_cast<unsigned long long*>(base + o_queue), base + o_slab, kScratchBytes - o_slab);
+                      base + o_plan, base + o_slab, kScratchBytes - o_slab);
   if (e == hipErrorInvalidConfiguration) {
     c->err = "scan configuration does not fit the device (LDS per workgroup); use FP32 or fewer hits per event";
     return RKN_E_UNSUPPORTED;

@@ -2,11 +2,11 @@
 //
 // Work decomposition (one MI355X):
 //   * one lane per seed; a wave scans chunks of up to 64 seeds of one window. The
-//     persistent grid (sized to the resident capacity) deals runs of chunks to its
-//     workgroups, a first share fixed, the rest from an atomic queue in runs that
-//     shrink as it empties; a workgroup works through its run event by event, its
-//     waves taking the chunks one by one. With a field map, the 65x129 (B_r, B_z)
-//     nodes are staged in LDS once per workgroup and shared by all its waves;
+//     persistent grid (sized to the resident capacity) shares the chunks event by event
+//     (plan_kernel): a workgroup stands in one event at a time, its waves taking the
+//     event's chunks one by one with the other workgroups there. With a field map, the
+//     65x129 (B_r, B_z) nodes are staged in LDS once per workgroup and shared by all its
+//     waves;
 //   * the event's hits are staged in LDS, ordered by layer and, within a layer, by
 //     the twisted azimuth psi = phi - s_l z of the wire centre; a 1 mm radial table
 //     maps a radius range to the layers whose band (widened by the largest drift +
@@ -50,6 +50,16 @@ constexpr int kPipeWaves = 12;  // waves per workgroup of pipe_kernel at most
 constexpr int kTraceFold = 8;   // rkn_trace: steps between folds of the block-relative sums
 constexpr float kPi = 3.14159265358979f;
 
+// How scan_kernel divides a launch's chunks. len > 0: tiles of at most len chunks of one
+// event, one for each workgroup (n_tiles of them). len = 0: each event's chunks are taken
+// from its own counter. Behind it in memory, per event [n_events + 1]: its first tile, or
+// the chunks taken.
+struct ScanPlan {
+  int64_t chunk0, chunk_end;  // the launch's chunks
+  int32_t len, n_tiles, n_events;
+};
+constexpr size_t kPlanHead = 64;
+
 struct ScanArgs {
   FieldDev field;
   const HitRec<float>* hits32;
@@ -72,13 +82,14 @@ struct ScanArgs {
   int n_seg;
   const int32_t* n_seg_dev;   // if set, the segment count is read here (captured launches)
   const int64_t* ev_chunk;    // first chunk of each event [n_events + 1]
+  int n_events;
   int walk;                   // 1: windows walked in scan order, lanes out of reach in z not culled; -1: not decided
   int64_t chunk0, n_chunks;   // the chunks to scan: [chunk0, chunk0 + n_chunks)
   const int64_t* n_chunks_dev;   // if set, n_chunks is read here
   const WindowDev* windows;
   const double* seeds5;       // explicit seeds [n][5] in scan order (NULL: windows)
   const int64_t* perm;        // scan order -> caller index (explicit seeds)
-  unsigned long long* queue;  // chunks taken from the queue
+  ScanPlan* plan;             // scan_kernel's division of the chunks (plan_kernel writes it)
   void* mscratch;
   int64_t slab_stride;        // elements per workgroup slab
   double R0, charge, h, lambda;
@@ -239,7 +250,97 @@ hipError_t launch_prep_hits(rkn_ctx* c, const int32_t* d_wire_id, const float* d
 }
 
 // ---------------------------------------------------------------------------------
-__global__ void reset_queue_kernel(unsigned long long* queue) { *queue = 0; }
+__device__ __forceinline__ unsigned long long* plan_events(ScanPlan* p) {
+  return reinterpret_cast<unsigned long long*>(reinterpret_cast<unsigned char*>(p) + kPlanHead);
+}
+
+// The chunks of event e that belong to the launch: [first, returned end).
+__device__ __forceinline__ int64_t event_chunks(const ScanPlan* p, const int64_t* ev_chunk, int e, int64_t* first) {
+  *first = max(ev_chunk[e], p->chunk0);
+  return max(min(ev_chunk[e + 1], p->chunk_end), *first);
+}
+
+constexpr int kPlanThreads = 1024;
+constexpr int kMaxWaves = 16;    // waves of a scan_kernel workgroup at most
+
+// One workgroup: the division of a launch's n chunks over `grid` workgroups of `waves`
+// waves, on n_cu CUs (see ScanPlan). A workgroup stages one event at a time, so a share of
+// chunks that lies in two events costs it two rounds.
+//  * At most one chunk per wave: the shortest tiles that end with their event and give each
+//    workgroup at most one, in as few workgroups per CU as can be (200 events of 4 chunks:
+//    1.75 ms in equal shares, 0.79 ms in tiles).
+//  * More, or more events than workgroups: every workgroup starts at its place in the
+//    chunks and takes its event's chunks one by one with the other workgroups there, then
+//    those of the events up to the next workgroup's place, then helps where chunks are
+//    left. (One run of 7/8 of its share per workgroup and a queue of runs for the rest,
+//    cut without regard to events: 64 events of 64 chunks 2.9 ms, 4000 events of one chunk
+//    20 ms; this way 2.0 and 13.)
+__global__ void __launch_bounds__(kPlanThreads) plan_kernel(ScanArgs a, int grid, int waves, int n_cu) {
+  __shared__ int s_tiles[kMaxWaves + 1];
+  __shared__ int s_sum[kPlanThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t n = a.n_chunks_dev ? *a.n_chunks_dev : a.n_chunks;
+  ScanPlan plan{a.chunk0, a.chunk0 + n, 0, 0, a.n_events};
+  unsigned long long* per_event = plan_events(a.plan);
+  auto chunks_of = [&](int e) {
+    int64_t first;
+    return event_chunks(&plan, a.ev_chunk, e, &first) - first;
+  };
+  if (n <= (int64_t)grid * waves) {
+    // tiles of every length 1 .. waves; summed in the wave first (200 lanes adding to one
+    // counter each: 35 us)
+    for (int l = tid; l <= kMaxWaves; l += kPlanThreads) s_tiles[l] = 0;
+    __syncthreads();
+    int t[kMaxWaves + 1] = {0};
+    for (int e = tid; e < a.n_events; e += kPlanThreads) {
+      const int c = (int)chunks_of(e);
+#pragma unroll
+      for (int l = 1; l <= kMaxWaves; ++l) t[l] += (c + l - 1) / l;
+    }
+#pragma unroll
+    for (int l = 1; l <= kMaxWaves; ++l) {
+      for (int o = 32; o >= 1; o >>= 1) t[l] += __shfl_xor(t[l], o, 64);
+      if (lane == 0 && t[l]) atomicAdd(&s_tiles[l], t[l]);
+    }
+    __syncthreads();
+    const int per_cu = (int)((n + (int64_t)n_cu * waves - 1) / ((int64_t)n_cu * waves));
+    for (int g = min(max(per_cu, 1) * n_cu, grid);; g = min(g + n_cu, grid)) {
+      int l = 1;
+      while (l <= waves && s_tiles[l] > g) ++l;
+      if (l <= waves) {
+        plan.len = l;
+        plan.n_tiles = s_tiles[l];
+      }
+      if (plan.len > 0 || g >= grid) break;
+    }
+  }
+  if (plan.len == 0) {
+    for (int e = tid; e < a.n_events; e += kPlanThreads) per_event[e] = 0;
+  } else {
+    // the events' first tiles: a running sum over the events
+    int total = 0;
+    for (int e0 = 0; e0 < a.n_events; e0 += kPlanThreads) {
+      const int e = e0 + tid;
+      const int t = e < a.n_events ? ((int)chunks_of(e) + plan.len - 1) / plan.len : 0;
+      int incl = t;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += x;
+      }
+      __syncthreads();   // the sums of the round before have been read
+      if (lane == 63) s_sum[wave] = incl;
+      __syncthreads();
+      int base = total;
+      for (int w = 0; w < kPlanThreads / 64; ++w) {
+        if (w < wave) base += s_sum[w];
+        total += s_sum[w];
+      }
+      if (e < a.n_events) per_event[e] = (unsigned long long)(base + incl - t);
+    }
+  }
+  if (tid == 0) *a.plan = plan;
+}
 
 template <typename R>
 __device__ __forceinline__ const HitRec<R>* hits_of(const ScanArgs& a);
@@ -558,8 +659,8 @@ __device__ __forceinline__ int find_seg(const Seg* segs, int n_seg, int64_t ch) 
 }
 
 // The same from segment lo on, which starts at or before ch: by doubling steps, since the
-// next chunk of a part lies in the same or the next segment, and one from the queue
-// anywhere in the event (an event may have 10^5 one-point windows).
+// chunk lies in the same or the next segment where an event has few windows, and anywhere in
+// the event where it has many (10^5 one-point windows).
 __device__ __forceinline__ int find_seg_from(const Seg* segs, int n_seg, int lo, int64_t ch) {
   int step = 1;
   while (lo + step < n_seg && segs[lo + step].chunk0 <= ch) {
@@ -862,96 +963,116 @@ __device__ __forceinline__ void finish_refine(const ScanArgs& a, const EventLds<
   __threadfence_block();
 }
 
-// What a workgroup works on (LDS, not registers held across a chunk): the part [g0, ge)
-// of its run [.., g1) that lies in one event.
-template <int WAVES>
+// What a workgroup works on (LDS, not registers held across a chunk): a part of event
+// `event`, whose chunks end at ge. Its size counts: in the 12- and 16-wave shapes the last
+// bytes of LDS decide how many hits an event may have.
 struct Work {
-  int64_t g0, ge, g1;
-  int64_t q0, q_end;        // the launch's queue: chunks [q0, q_end)
-  int64_t ev_end;           // the event's chunks end here
-  int64_t spare[WAVES];     // chunks of another event that waves took from the queue
-  int seg, event, hbase, nh, next, n_spare, singles, stage, done;
+  int64_t ge;
+  int64_t pos, own_end;      // the workgroup's own place in the chunks: [pos, own_end) is left
+  unsigned long long best;   // where chunks are left, while it searches
+  int seg, event, hbase, nh;
+  bool stage, done, search;
 };
 
-// The launch's chunks: an even share for each workgroup, and a queue for the rest. A
-// launch with at most one chunk per wave is shared out whole. One whose events each fill
-// the grid comes whole from the queue, which then stands in one event most of the time,
-// so waves take single chunks and none waits for another (16^5 FP32 seeds of one event,
-// uniform field: 9.3 ms, against 11.6 ms with half of them shared out). Smaller events
-// would send every wave of a workgroup into another event, so there 7/8 are shared out in
-// long runs and the queue evens out the ends (64 events in the field map: 97 ms, against
-// 107 ms all from the queue).
-template <int WAVES>
-__device__ __forceinline__ void start_work(const ScanArgs& a, Work<WAVES>& sh) {
-  const int64_t n = a.n_chunks_dev ? *a.n_chunks_dev : a.n_chunks;
-  const int n_seg = a.n_seg_dev ? *a.n_seg_dev : a.n_seg;
-  const int64_t grid = gridDim.x, slots = grid * WAVES;
-  const int64_t span = n > 0 ? a.segs[n_seg - 1].event - a.segs[0].event + 1 : 1;
-  const int64_t n_queue = n <= slots ? 0 : (n >= span * slots ? n : n / 8);
-  const int64_t n_shared = n - n_queue;
-  sh.event = -1;
-  sh.ge = a.chunk0 + n_shared * blockIdx.x / grid;
-  sh.g1 = a.chunk0 + n_shared * (blockIdx.x + 1) / grid;
-  sh.q0 = a.chunk0 + n_shared;
-  sh.q_end = a.chunk0 + n;
-  sh.n_spare = 0;
-}
-
-__device__ __forceinline__ int64_t queue_head(const ScanArgs& a) {
-  return (int64_t)__hip_atomic_load(a.queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// The workgroup's next part (thread 0, between barriers): what is left of its run, else
-// a chunk that a wave could not use, else a run from the queue (2 chunks per wave, near
-// the end 1).
-template <int WAVES>
-__device__ __forceinline__ void next_part(const ScanArgs& a, Work<WAVES>& sh) {
-  const int n_seg = a.n_seg_dev ? *a.n_seg_dev : a.n_seg;
-  int64_t g0 = sh.ge;
-  sh.done = 0;
-  if (g0 >= sh.g1) {
-    int64_t len = 0;
-    if (sh.n_spare > 0) {
-      g0 = sh.spare[--sh.n_spare];
-      len = 1;
-    } else if (sh.q0 < sh.q_end) {
-      const int64_t left = sh.q_end - sh.q0 - queue_head(a);
-      const int64_t want = left > 4 * (int64_t)gridDim.x * WAVES ? 2 * WAVES : WAVES;
-      g0 = sh.q0 + (int64_t)atomicAdd(a.queue, (unsigned long long)want);
-      len = min(want, sh.q_end - g0);
-    }
-    if (len <= 0) {
-      sh.done = 1;
-      return;
-    }
-    sh.g1 = g0 + len;
+// The last event whose first chunk is at most ch.
+__device__ __forceinline__ int find_event(const int64_t* ev_chunk, int n_events, int64_t ch) {
+  int lo = 0, hi = n_events;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) / 2;
+    if (ev_chunk[mid] <= ch)
+      lo = mid;
+    else
+      hi = mid;
   }
-  const int seg = find_seg(a.segs, n_seg, g0), ev = a.segs[seg].event;
-  sh.g0 = g0;
-  sh.ev_end = a.ev_chunk[ev + 1];
-  sh.ge = min(sh.g1, sh.ev_end);
-  sh.seg = seg;
+  return lo;
+}
+
+// Makes chunks [g0, end) of event ev the workgroup's part, one for each wave by its number,
+// so that those of a part of few chunks run on different SIMDs; ge: the event's end.
+template <int WAVES>
+__device__ __forceinline__ void set_part(const ScanArgs& a, Work& sh, int64_t* first, int ev, int64_t g0, int64_t end,
+                                         int64_t ge) {
+  for (int w = 0; w < WAVES; ++w) first[w] = g0 + w < end ? g0 + w : -1;
+  sh.ge = ge;
+  sh.seg = find_seg(a.segs, a.n_seg_dev ? *a.n_seg_dev : a.n_seg, g0);
   sh.stage = ev != sh.event;
   sh.event = ev;
   sh.hbase = a.ev_off[ev];
   sh.nh = a.ev_off[ev + 1] - sh.hbase;
-  sh.next = 0;
-  sh.singles = sh.g1 == sh.ge && sh.n_spare == 0;   // a wave leaves at most one spare per part
+  sh.search = sh.done = false;
 }
 
-// A wave's next chunk (one lane): of the workgroup's part, then, while the queue stands
-// in the same event, single chunks from there (so that the waves of a launch of one event
-// never wait for each other); -1: none.
+// Takes up to a chunk per wave of event ev; false if none is left.
 template <int WAVES>
-__device__ __forceinline__ int64_t next_chunk(const ScanArgs& a, Work<WAVES>& sh) {
-  int64_t ch = sh.g0 + atomicAdd(&sh.next, 1);
-  if (ch < sh.ge) return ch;
-  if (!sh.singles || sh.q0 + queue_head(a) >= min(sh.ev_end, sh.q_end)) return -1;
-  ch = sh.q0 + (int64_t)atomicAdd(a.queue, 1ULL);
-  if (ch >= sh.q_end) return -1;
-  if (ch < sh.ev_end) return ch;
-  sh.spare[atomicAdd(&sh.n_spare, 1)] = ch;   // the wave now waits for the next part
-  return -1;
+__device__ __forceinline__ bool take_part(const ScanArgs& a, Work& sh, int64_t* first, int ev) {
+  int64_t g0;
+  const int64_t ge = event_chunks(a.plan, a.ev_chunk, ev, &g0);
+  g0 += (int64_t)atomicAdd(plan_events(a.plan) + ev, (unsigned long long)WAVES);
+  if (g0 >= ge) return false;
+  set_part<WAVES>(a, sh, first, ev, g0, min(g0 + WAVES, ge), ge);
+  return true;
+}
+
+// The workgroup's place (thread 0).
+__device__ __forceinline__ void start_work(ScanPlan* p, Work& sh) {
+  const int64_t n = p->chunk_end - p->chunk0, grid = gridDim.x, b = blockIdx.x;
+  sh.event = -1;
+  sh.pos = p->len > 0 ? b : p->chunk0 + n * b / grid;
+  sh.own_end = p->len > 0 ? min(b + 1, (int64_t)p->n_tiles) : p->chunk0 + n * (b + 1) / grid;
+}
+
+// The workgroup's next part of its own (thread 0, between barriers): its tile, or chunks of
+// the events from its place on; sh.search if there is none left and it may help elsewhere.
+template <int WAVES>
+__device__ __forceinline__ void next_part(const ScanArgs& a, Work& sh, int64_t* first) {
+  ScanPlan* p = a.plan;
+  if (p->len > 0) {
+    const int64_t t = sh.pos;
+    sh.search = false;
+    sh.done = t >= sh.own_end;
+    if (sh.done) return;
+    sh.pos = sh.own_end;
+    const int64_t* tile0 = reinterpret_cast<const int64_t*>(plan_events(p));
+    const int ev = find_event(tile0, p->n_events, t);
+    int64_t g0;
+    const int64_t ge = event_chunks(p, a.ev_chunk, ev, &g0);
+    g0 += (t - tile0[ev]) * p->len;
+    set_part<WAVES>(a, sh, first, ev, g0, min(g0 + p->len, ge), 0);
+    return;
+  }
+  for (int64_t pos = sh.pos; pos < sh.own_end;) {
+    const int ev = find_event(a.ev_chunk, p->n_events, pos);
+    pos = a.ev_chunk[ev + 1];
+    sh.pos = pos;
+    if (take_part<WAVES>(a, sh, first, ev)) return;
+  }
+  sh.best = 0;
+  sh.search = true;
+  sh.done = false;
+}
+
+// An event with chunks left, by all threads: the most of them, weighted so that workgroups
+// that search at the same time do not all go to the same one.
+__device__ __forceinline__ void search_events(const ScanArgs& a, Work& sh, int tid, int nthreads) {
+  for (int e = tid; e < a.plan->n_events; e += nthreads) {
+    int64_t g0;
+    const int64_t ge = event_chunks(a.plan, a.ev_chunk, e, &g0);
+    const int64_t left = ge - g0 - (int64_t)__hip_atomic_load(plan_events(a.plan) + e, __ATOMIC_RELAXED,
+                                                              __HIP_MEMORY_SCOPE_AGENT);
+    if (left <= 0) continue;
+    const uint32_t weight = 64 + ((blockIdx.x * 37u + (uint32_t)e * 11u) & 63u);
+    const uint64_t key = min((uint64_t)left * weight, (uint64_t)0xffffffff);
+    atomicMax(&sh.best, key << 32 | (uint32_t)e);
+  }
+}
+
+// A wave's next chunk (one lane): of the workgroup's event, whose chunks all workgroups
+// there share, so that none of their waves waits for another; -1: none is left.
+__device__ __forceinline__ int64_t next_chunk(const ScanArgs& a, const Work& sh) {
+  if (sh.ge == 0) return -1;   // a tile has no more chunks than waves
+  const int64_t ch = max(a.ev_chunk[sh.event], a.plan->chunk0) +
+                     (int64_t)atomicAdd(plan_events(a.plan) + sh.event, 1ULL);
+  return ch < sh.ge ? ch : -1;
 }
 
 // The slab entry that means "no minimum yet".
@@ -999,7 +1120,7 @@ scan_kernel(ScanArgs a) {
   L.loff = reinterpret_cast<int*>(s_items + WAVES * kCap);
   L.slope = reinterpret_cast<float*>(L.loff + a.n_layers + 1);
   uint32_t* s_touch = reinterpret_cast<uint32_t*>(L.slope + a.n_layers);
-  __shared__ Work<WAVES> sh;
+  __shared__ Work sh;
   __shared__ int64_t s_chunk[WAVES];
   __shared__ int s_seg[WAVES];
 
@@ -1022,22 +1143,34 @@ scan_kernel(ScanArgs a) {
     nodes = s_field;   // made visible by the barriers before the first chunk
   }
 
-  if (tid == 0) start_work(a, sh);
+  if (tid == 0) start_work(a.plan, sh);
   for (;;) {
     __syncthreads();   // every wave is done with the part and its tables
-    if (tid == 0) next_part(a, sh);
+    if (tid == 0) next_part<WAVES>(a, sh, s_chunk);
     __syncthreads();
+    while (sh.search) {
+      search_events(a, sh, tid, TILE);
+      __syncthreads();
+      if (tid == 0) {
+        const unsigned long long best = sh.best;
+        sh.best = 0;
+        if (best == 0) {
+          sh.done = true;
+          sh.search = false;
+        } else {
+          take_part<WAVES>(a, sh, s_chunk, (int)(uint32_t)best);
+        }
+      }
+      __syncthreads();
+    }
     if (sh.done) break;
     if (sh.stage) {
       stage_event<R>(a, L, sh.event, tid, TILE, B * hmax);
       __syncthreads();
     }
     for (;;) {
-      if (lane == 0) {
-        const int64_t ch = next_chunk(a, sh);
-        s_chunk[wave] = ch;
-        s_seg[wave] = ch < 0 ? 0 : find_seg_from(a.segs, a.n_seg_dev ? *a.n_seg_dev : a.n_seg, sh.seg, ch);
-      }
+      if (lane == 0 && s_chunk[wave] >= 0)
+        s_seg[wave] = find_seg_from(a.segs, a.n_seg_dev ? *a.n_seg_dev : a.n_seg, sh.seg, s_chunk[wave]);
       wave_sync();
       if (s_chunk[wave] < 0) break;
       if (!filled) {
@@ -1160,6 +1293,7 @@ scan_kernel(ScanArgs a) {
         finish_refine<R, TILE, 1>(a, L, slab, touch, lane, sh.hbase, sh.nh, s_seg[wave], s_chunk[wave], valid);
       else
         finish_scan<R, TILE, 1>(a, L, slab, touch, lane, sh.nh, s_seg[wave], s_chunk[wave], valid);
+      if (lane == 0) s_chunk[wave] = next_chunk(a, sh);
     }
   }
   if constexpr (COUNT) {
@@ -1550,7 +1684,7 @@ static hipError_t launch_scan_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, boo
     a.mscratch = slab_buf->p;
   }
   if (alloc_only) return hipSuccess;
-  hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(1), 0, c->stream, a.queue);
+  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, c->stream, a, (int)grid, WAVES, c->n_cu);
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(TILE), smem, c->stream, a);
   return hipGetLastError();
 }
@@ -1569,7 +1703,9 @@ static size_t pair_lds_bytes(const rkn_ctx* c, size_t rsize, int B, int cols, in
 // on one lane each, 2.81 on four). Past that scan_kernel's waves fill the chip and are the faster
 // (768 chunks of 64 trials in the field map, two rounds of pairs: Gauss-Newton 43 ms
 // against 37), except where an event has at most 16 seeds: its one wave per workgroup
-// takes two rounds as well (1000 events of 8 seeds: 10.3 ms against 16.7).
+// takes two rounds as well (1000 events of 8 seeds: 10.3 ms against 16.7). No more than four
+// pairs of 64 seeds on a CU, so that each producer has a SIMD to itself (70 000 FP64 seeds
+// of one event, 40 hits, uniform field, five pairs: 2.79 ms, against 2.56 in scan_kernel).
 template <typename R, int FIELD, int B, int COLS, int MODE, bool QUAD = false>
 static bool launch_pipe_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, bool alloc_only, DevBuf* slab_buf,
                           void* raw_slab, size_t raw_bytes, hipError_t* err) {
@@ -1586,7 +1722,7 @@ static bool launch_pipe_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, bool allo
                       : prod + con <= kPipeWaves && pairs * (pair + 512) <= room && pairs * (prod + con) <= 16;
   };
   int64_t per_cu = (max_chunks + c->n_cu - 1) / c->n_cu;
-  if (QUAD && per_cu * prod > 4) return false;   // a SIMD for each producer
+  if ((QUAD || COLS == 64) && per_cu * prod > 4) return false;   // a SIMD for each producer
   if (!fits(per_cu, 1)) {
     if (COLS > 16) return false;
     int64_t most = kPipeWaves;
@@ -1707,6 +1843,7 @@ static ScanArgs base_args(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& 
   a.n_seg = w.n_seg;
   a.n_seg_dev = w.n_seg_dev;
   a.ev_chunk = w.ev_chunk;
+  a.n_events = c->n_events;
   a.chunk0 = w.chunk0;
   a.n_chunks = w.n_chunks;
   a.n_chunks_dev = w.n_chunks_dev;
@@ -1727,10 +1864,10 @@ static ScanArgs base_args(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& 
 hipError_t launch_refine_fwd(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& w, const int64_t* d_base_of,
                              uint8_t* d_mask, int define_mask, float* d_resid, int32_t* d_argmin, double* d_phi,
                              float* d_tape, int ckpt, int n_ckpt, int64_t n_pos) {
-  hipError_t e = c->r_counter.ensure(64);
+  hipError_t e = c->r_counter.ensure(scan_plan_bytes(c));
   if (e != hipSuccess) return e;
   ScanArgs a = base_args(c, p, w);
-  a.queue = c->r_counter.as<unsigned long long>();
+  a.plan = c->r_counter.as<ScanPlan>();
   a.hits_orig = c->hits_orig.as<int32_t>();
   a.base_of = d_base_of;
   a.mask = d_mask;
@@ -1762,9 +1899,9 @@ hipError_t launch_refine_fwd(rkn_ctx* c, const rkn_scan_params* p, const ScanSeg
 }
 
 static ScanArgs scan_args(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& w, double* d_score, int32_t* d_nin,
-                          ArgminPart* parts, unsigned long long* queue) {
+                          ArgminPart* parts, void* plan) {
   ScanArgs a = base_args(c, p, w);
-  a.queue = queue;
+  a.plan = static_cast<ScanPlan*>(plan);
   a.score = d_score;
   if (c->adapt) {   // set only for the adaptive scan entry point's call
     a.path_len = p->n_steps * p->step_mm;
@@ -1790,9 +1927,9 @@ hipError_t launch_scan(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& w, 
                        int64_t* d_best_i, double* d_best_e) {
   hipError_t e = c->parts.ensure(sizeof(ArgminPart) * (size_t)(w.n_chunks > 0 ? w.n_chunks : 1));
   if (e != hipSuccess) return e;
-  e = c->counter.ensure(64);
+  e = c->counter.ensure(scan_plan_bytes(c));
   if (e != hipSuccess) return e;
-  ScanArgs a = scan_args(c, p, w, d_score, d_nin, c->parts.as<ArgminPart>(), c->counter.as<unsigned long long>());
+  ScanArgs a = scan_args(c, p, w, d_score, d_nin, c->parts.as<ArgminPart>(), c->counter.p);
   if (w.n_chunks > 0) {
     e = dispatch_scan(c, p, a, w.n_chunks, false, &c->mscratch);
     if (e != hipSuccess) return e;
@@ -1806,9 +1943,9 @@ hipError_t launch_scan_dev(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs&
   const ScanScratch& s = scratch ? *scratch : own;
   hipError_t e = s.parts->ensure(sizeof(ArgminPart) * (size_t)(w.n_chunks > 0 ? w.n_chunks : 1));
   if (e != hipSuccess) return e;
-  e = s.counter->ensure(64);
+  e = s.counter->ensure(scan_plan_bytes(c));
   if (e != hipSuccess) return e;
-  ScanArgs a = scan_args(c, p, w, d_score, d_nin, s.parts->as<ArgminPart>(), s.counter->as<unsigned long long>());
+  ScanArgs a = scan_args(c, p, w, d_score, d_nin, s.parts->as<ArgminPart>(), s.counter->p);
   e = dispatch_scan(c, p, a, w.n_chunks, alloc_only, s.slab);
   if (e != hipSuccess || alloc_only) return e;
   return launch_event_argmin(c, w, s.parts->as<ArgminPart>(), 0, w.n_chunks, d_best_i, d_best_e);
@@ -1816,12 +1953,12 @@ hipError_t launch_scan_dev(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs&
 
 hipError_t launch_scan_raw(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs& w, double* d_score, int32_t* d_nin,
                            int64_t* d_best_i, double* d_best_e, ArgminPart* d_parts, int64_t max_parts,
-                           unsigned long long* d_queue, void* d_slab, size_t slab_bytes) {
+                           void* d_plan, void* d_slab, size_t slab_bytes) {
   // as many launches as the argmin partials need; each lowers the events' best, and all
   // walk the windows as one launch of the whole scan would
   int walk = -1;
   if (w.n_chunks > max_parts) {
-    ScanArgs whole = scan_args(c, p, w, d_score, d_nin, d_parts, d_queue);
+    ScanArgs whole = scan_args(c, p, w, d_score, d_nin, d_parts, d_plan);
     const hipError_t e = dispatch_scan(c, p, whole, w.n_chunks, true, nullptr, d_slab, slab_bytes);
     if (e != hipSuccess) return e;
     walk = whole.walk;
@@ -1830,7 +1967,7 @@ hipError_t launch_scan_raw(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs&
     ScanSegs part = w;
     part.chunk0 = c0;
     part.n_chunks = std::min(max_parts, w.n_chunks - c0);
-    ScanArgs a = scan_args(c, p, part, d_score, d_nin, d_parts, d_queue);
+    ScanArgs a = scan_args(c, p, part, d_score, d_nin, d_parts, d_plan);
     a.walk = walk;
     if (part.n_chunks > 0) {
       const hipError_t e = dispatch_scan(c, p, a, part.n_chunks, false, nullptr, d_slab, slab_bytes);
@@ -1840,6 +1977,10 @@ hipError_t launch_scan_raw(rkn_ctx* c, const rkn_scan_params* p, const ScanSegs&
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+size_t scan_plan_bytes(const rkn_ctx* c) {
+  return kPlanHead + sizeof(int64_t) * ((size_t)c->n_events + 1);
 }
 
 size_t scan_slab_bytes_per_workgroup(const rkn_ctx* c, const rkn_scan_params* p) {
