@@ -973,6 +973,10 @@ struct Work {
   int seg, event, hbase, nh;
   bool stage, done, search;
 };
+// With each wave's chunk and segment: what the shapes' limits leave for it (18 layers: 12
+// waves up to 314 hits; 128 bytes more cost four of them).
+static_assert(sizeof(Work) + 12 * (sizeof(int64_t) + sizeof(int)) <= 256, "12-wave shape");
+static_assert(sizeof(Work) + 16 * (sizeof(int64_t) + sizeof(int)) <= 272, "16-wave shape");
 
 // The last event whose first chunk is at most ch.
 __device__ __forceinline__ int find_event(const int64_t* ev_chunk, int n_events, int64_t ch) {

@@ -1,9 +1,10 @@
-"""Which scans the LDS admits: the limits do not depend on how many seeds a call has.
+"""Which scans the LDS admits, and in which shape: the limits do not depend on how many
+seeds a call has, and the bookkeeping of a workgroup's chunks does not narrow them.
 
 LDS of a workgroup of W waves with B-step blocks (FP32, field map nr x nz, L layers, h hits
 in the largest event), bytes: 8 (nr + 1)(nz + 1) and 32 h, each rounded up to 64; 2048;
 512 L; W (B + 1) 768; 704 W; 4 (2 L + 1); 4 W ceil(h / 32). A shape is taken when 256 more
-fit the 160 KiB.
+fit the 160 KiB (272 more for 16 waves).
 """
 import numpy as np
 import pytest
@@ -24,6 +25,15 @@ def _hits(geo, h):
     rng = np.random.default_rng(h)
     return (np.array([0, h], np.int32), np.sort(rng.choice(geo.mx.size, h, replace=False)).astype(np.int32),
             rng.uniform(0, 8, h).astype(np.float32))
+
+
+@pytest.mark.parametrize("block_steps,hits,lanes", [(6, 314, 768), (6, 315, 512), (4, 316, 1024), (4, 317, 512)])
+def test_widest_shape_up_to_its_limit(rk, geo, sfield, block_steps, hits, lanes):
+    """The 18-layer chamber: 12 waves up to 314 hits, 16 waves up to 316."""
+    c = rk.Context(0)
+    c.upload_geometry(geo); c.upload_field(sfield); c.upload_hits(*_hits(geo, hits))
+    assert rk.rkn_scan_shape(c.ctx, rk.make_scan_params(precision=32, block_steps=block_steps)) == (block_steps, lanes)
+    c.close()
 
 
 @pytest.mark.parametrize("precision,nr,scans,refines", [(32, 80, True, True), (32, 84, True, False),
