@@ -904,6 +904,14 @@ __device__ __forceinline__ void finish_scan(const ScanArgs& a, const EventLds<R>
   }
 }
 
+// sum + r^2 with the square rounded first, whatever the code around it: Phi of a seed then
+// does not depend on the kernel that ran it, and Gauss-Newton compares the Phi of its trials
+// with one that another launch may have formed.
+__device__ __forceinline__ double add_square(double sum, double r) {
+#pragma clang fp contract(off)
+  return sum + r * r;
+}
+
 // MODE 1: inlier residuals (original hit order) and argmin chords.
 template <typename R, int TILE, int U, typename S>
 __device__ __forceinline__ void finish_refine(const ScanArgs& a, const EventLds<R>& L, S* slab, const uint32_t* touch,
@@ -947,7 +955,7 @@ __device__ __forceinline__ void finish_refine(const ScanArgs& a, const EventLds<
         }
         rrow[o[u]] = in ? (float)r : NAN;
         arow[o[u]] = (in && key[u] != 0xffffffffffffffffULL) ? (int32_t)(unsigned)(key[u] & 0xffffffffu) : -1;
-        if (in) ph += r * r;
+        if (in) ph = add_square(ph, r);
       }
     }
     for (int i = nh; i < a.max_hits; ++i) {
