@@ -201,6 +201,25 @@ __device__ __forceinline__ void advance(State<R>& st, R dx, R dy, R dz) {
   }
 }
 
+// c + a b and a b - c d: in FP32 as the fused forms that QuadProp writes too, so that a
+// trajectory has the same bits in every kernel that forms or recomputes it.
+template <typename R>
+__device__ __forceinline__ R add_mul(R c, R a, R b) {
+  if constexpr (sizeof(R) == 4) {
+    return __builtin_fmaf(a, b, c);
+  } else {
+    return c + a * b;
+  }
+}
+template <typename R>
+__device__ __forceinline__ R cross_term(R a, R b, R c, R d) {
+  if constexpr (sizeof(R) == 4) {
+    return __builtin_fmaf(a, b, -(c * d));
+  } else {
+    return a * b - c * d;
+  }
+}
+
 // One RKN4 step (Nystrom formula for x'' = lam x' x B(x), three field evaluations:
 // start, middle, end) as increments: from the position p and unit direction t, the
 // changes d[0..2] of the position and d[3..5] of the direction over a step h.
@@ -241,34 +260,34 @@ __device__ __forceinline__ void rkn_delta(const FieldDev& f, const float2* nodes
     } else {
       field_rz_r2(f, nodes, px, py, pz, r2, lam, bx, by, bz);
     }
-    const R k1x = ty * bz - tz * by;
-    const R k1y = tz * bx - tx * bz;
-    const R k1z = tx * by - ty * bx;
+    const R k1x = cross_term(ty, bz, tz, by);
+    const R k1y = cross_term(tz, bx, tx, bz);
+    const R k1z = cross_term(tx, by, ty, bx);
     const R hh8 = h * h * (R)0.125;
     {
-      const R qx = px + h2 * tx + hh8 * k1x, qy = py + h2 * ty + hh8 * k1y;
-      field_rz_r2(f, nodes, qx, qy, pz + h2 * tz + hh8 * k1z, radius2(qx, qy), lam, bx, by, bz);
+      const R qx = add_mul(add_mul(px, h2, tx), hh8, k1x), qy = add_mul(add_mul(py, h2, ty), hh8, k1y);
+      field_rz_r2(f, nodes, qx, qy, add_mul(add_mul(pz, h2, tz), hh8, k1z), radius2(qx, qy), lam, bx, by, bz);
     }
     // stages 2 and 3 share the middle field
-    const R t2x = tx + h2 * k1x, t2y = ty + h2 * k1y, t2z = tz + h2 * k1z;
-    const R k2x = t2y * bz - t2z * by;
-    const R k2y = t2z * bx - t2x * bz;
-    const R k2z = t2x * by - t2y * bx;
-    const R t3x = tx + h2 * k2x, t3y = ty + h2 * k2y, t3z = tz + h2 * k2z;
-    const R k3x = t3y * bz - t3z * by;
-    const R k3y = t3z * bx - t3x * bz;
-    const R k3z = t3x * by - t3y * bx;
+    const R t2x = add_mul(tx, h2, k1x), t2y = add_mul(ty, h2, k1y), t2z = add_mul(tz, h2, k1z);
+    const R k2x = cross_term(t2y, bz, t2z, by);
+    const R k2y = cross_term(t2z, bx, t2x, bz);
+    const R k2z = cross_term(t2x, by, t2y, bx);
+    const R t3x = add_mul(tx, h2, k2x), t3y = add_mul(ty, h2, k2y), t3z = add_mul(tz, h2, k2z);
+    const R k3x = cross_term(t3y, bz, t3z, by);
+    const R k3y = cross_term(t3z, bx, t3x, bz);
+    const R k3z = cross_term(t3x, by, t3y, bx);
     const R hh2 = h * h * (R)0.5;
     {
-      const R qx = px + h * tx + hh2 * k3x, qy = py + h * ty + hh2 * k3y;
+      const R qx = add_mul(add_mul(px, h, tx), hh2, k3x), qy = add_mul(add_mul(py, h, ty), hh2, k3y);
       const R r2e = radius2(qx, qy);
-      field_rz_r2(f, nodes, qx, qy, pz + h * tz + hh2 * k3z, r2e, lam, bx, by, bz);
+      field_rz_r2(f, nodes, qx, qy, add_mul(add_mul(pz, h, tz), hh2, k3z), r2e, lam, bx, by, bz);
       if (r2_4) *r2_4 = r2e;
     }
-    const R t4x = tx + h * k3x, t4y = ty + h * k3y, t4z = tz + h * k3z;
-    const R k4x = t4y * bz - t4z * by;
-    const R k4y = t4z * bx - t4x * bz;
-    const R k4z = t4x * by - t4y * bx;
+    const R t4x = add_mul(tx, h, k3x), t4y = add_mul(ty, h, k3y), t4z = add_mul(tz, h, k3z);
+    const R k4x = cross_term(t4y, bz, t4z, by);
+    const R k4y = cross_term(t4z, bx, t4x, bz);
+    const R k4z = cross_term(t4x, by, t4y, bx);
     if (b4) {
       b4[0] = bx;
       b4[1] = by;
@@ -280,9 +299,9 @@ __device__ __forceinline__ void rkn_delta(const FieldDev& f, const float2* nodes
       d[0] = k1x + sx;
       d[1] = k1y + sy;
       d[2] = k1z + sz;
-      d[3] = k1x + (R)2 * sx + k4x;
-      d[4] = k1y + (R)2 * sy + k4y;
-      d[5] = k1z + (R)2 * sz + k4z;
+      d[3] = add_mul(k1x, (R)2, sx) + k4x;
+      d[4] = add_mul(k1y, (R)2, sy) + k4y;
+      d[5] = add_mul(k1z, (R)2, sz) + k4z;
     } else if constexpr (sizeof(R) == 4) {
       const R sx = k2x + k3x, sy = k2y + k3y, sz = k2z + k3z;
       d[0] = h * tx + hh6 * (k1x + sx);
@@ -422,9 +441,8 @@ struct Prop {
 // holds component c (0 x, 1 y, 2 z; lane 3 mirrors z). Vector operations then take one
 // instruction instead of three, neighbouring components coming over quad permutes; only
 // the cell lookup is done by all four. A step is 90 instructions instead of 138, which is
-// what counts for a wave that has its SIMD to itself. The sums are written as the fused
-// multiply-adds the compiler forms in rkn_delta, so the trajectories are the same bit for
-// bit.
+// what counts for a wave that has its SIMD to itself. The sums are the fused multiply-adds
+// that rkn_delta writes, so the trajectories are the same bit for bit.
 template <int CTRL>
 __device__ __forceinline__ float quad_perm(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
