@@ -187,13 +187,20 @@ rkn_status rkn_scan_windows(rkn_ctx *ctx, const rkn_scan_params *p, int32_t n_wi
  * memory (code under stream capture, tight serving loops, harnesses that forbid it):
  * the same scan and outputs, which must be device pointers (p->ptr_flags has
  * RKN_PTR_DEVICE; best_index and best_score are required, score and n_in may be
- * NULL). Its work memory (device windows, seed chunks, argmin partials, division of the chunks,
- * running minima) is one 256 MiB array per GPU, held from the library's load until
- * the process ends and shared by every call on that GPU: calls on one context's
- * stream are ordered, calls that overlap on one GPU from other streams race. The
- * call allocates nothing. RKN_E_CAPACITY when the windows, their chunks and the
- * running minima of one workgroup do not fit the array; when the minima of a full
- * persistent grid do not fit, fewer workgroups run. */
+ * NULL). Its work memory (device windows and their segments, per-event offsets and
+ * counters, argmin partials, running minima) is one 256 MiB array per GPU, held from
+ * the library's load until the process ends and shared by every call on that GPU:
+ * calls on one context's stream are ordered, calls that overlap on one GPU from other
+ * streams race. The call allocates nothing.
+ *
+ * RKN_E_CAPACITY past a fixed limit, which does not follow the layout: 104 bytes per
+ * window, 48 bytes per workgroup's worth of a window's seeds (seeds_per_tile of
+ * rkn_scan_shape; a last, partial one counts), 4 bytes per event and the running minima
+ * of one workgroup come to 256 MiB at most. (Past some 10^7 events, the 16 bytes that
+ * offset and counter of each take in the array set it.) Within it, a scan of more chunks
+ * than the array has room for argmin partials runs in several launches, with the same
+ * results, and when the minima of a full persistent grid do not fit, fewer workgroups
+ * run. */
 rkn_status rkn_scan_windows_noalloc(rkn_ctx *ctx, const rkn_scan_params *p, int32_t n_windows,
                                     const rkn_window *w, double *score, int32_t *n_in,
                                     int64_t *best_index, double *best_score);
@@ -284,7 +291,9 @@ rkn_status rkn_trace(rkn_ctx *ctx, const rkn_scan_params *p, int64_t n_seeds, co
 /* Validate the parameters, size every buffer for the worst case
  * (n_events x max_cand windows of at most min(max_seeds_window, count_max^5)
  * seeds) and capture the graphs. sp->ptr_flags chooses host or device outputs of
- * rkn_batch_launch. hp and sp must have the same charge and R0 (else RKN_E_ARG). */
+ * rkn_batch_launch. hp and sp must have the same charge and R0 (else RKN_E_ARG).
+ * RKN_E_CAPACITY when the worst case is more than 2^40 seeds or 2^31 workgroups' worths
+ * of a window's seeds (seeds_per_tile of rkn_scan_shape). */
 rkn_status rkn_batch_plan(rkn_ctx *ctx, const rkn_hough_params *hp, const rkn_scan_params *sp);
 
 /* Autotuner of the batched path: plans the batch with each block size of

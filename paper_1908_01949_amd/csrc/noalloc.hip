@@ -1,9 +1,9 @@
 // rkn_scan_windows_noalloc: the window scan of rkn_scan_windows for callers that
 // cannot allocate device memory (code under stream capture, tight serving loops,
 // harnesses that forbid hipMalloc). Its work memory -- the device windows, their
-// segments, the per-event chunk offsets, the argmin partials, the division of the chunks and the
-// slab of running minima -- lives in one file-scope device array per GPU, held from
-// the library's load until the process ends. Nothing in the call allocates.
+// segments, the per-event chunk offsets, the division of the chunks, the argmin partials
+// and the slab of running minima -- lives in one file-scope device array per GPU, held
+// from the library's load until the process ends. Nothing in the call allocates.
 //
 // Host code never passes the array's name to a kernel or a copy: `scratch` in host
 // code is a stand-in symbol, not a device address. Its address on each device is
@@ -88,8 +88,10 @@ rkn_status rkn_scan_windows_noalloc(rkn_ctx* c, const rkn_scan_params* p, int32_
   const size_t o_plan = o_evc + align256(sizeof(int64_t) * list.ev_chunk.size());
   const size_t o_parts = o_plan + align256(scan_plan_bytes(c));
   const size_t per_wg = scan_slab_bytes_per_workgroup(c, &q);
-  // the limit that callers know: 48 bytes for every workgroup's worth of seeds beside
-  // the windows and one workgroup's minima
+  // The limit that rknscan.h states: 48 bytes for every workgroup's worth of seeds beside
+  // the windows, 4 bytes an event and one workgroup's minima. It is a contract, not the
+  // layout below, which needs less but for very many events: what was refused stays
+  // refused when the layout changes.
   const size_t T = (size_t)scan_tile(c, &q);
   size_t need = o_win + align256(sizeof(WindowDev) * wins.size()) + align256(sizeof(int32_t) * list.ev_chunk.size()) +
                 256 + per_wg;

@@ -207,12 +207,10 @@ rkn_status rkn_rescan_refine(rkn_ctx* c, const rkn_scan_params* p, const rkn_res
   const int ne = c->n_events, k = rp->k, G = rp->grid;
   rkn_scan_params q = *p;
   q.block_steps = resolve_block_steps(c, &q);
-  const int tile = scan_tile(c, &q);
   const long long per_window = (long long)G * G * G * G * G;
   const long long max_seeds = (long long)ne * k * per_window;
-  const long long max_tiles = (long long)ne * k * ((per_window + tile - 1) / tile);
   const long long max_chunks = (long long)ne * k * ((per_window + kChunk - 1) / kChunk);
-  if (max_seeds > (1LL << 32) || max_tiles > (1LL << 31)) {
+  if (max_seeds > (1LL << 32)) {
     c->err = "rescan: a round could scan more than 2^32 seeds; lower k or grid";
     return RKN_E_CAPACITY;
   }
