@@ -22,6 +22,7 @@
 
 #include <algorithm>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "internal.hpp"
@@ -315,11 +316,16 @@ __global__ void __launch_bounds__(64 * kPrepSeeds) adj_prep_kernel(BwdArgs a) {
 // and the hits come in the order of the walk, one list entry held at a time. (Gradient of
 // 4096 seeds, 94 segments, map from memory, the segment's whole list read at every step
 // and one wave per SIMD: 2.07 ms; this way 1.37. With S, 1024 seeds: 0.80 and 0.73.)
-template <int FIELD, bool WANT_S>
-__global__ void __launch_bounds__(256, WANT_S ? 1 : 2) adj_seg_kernel(BwdArgs a) {
+//
+// STOP, with the turn-partition stop: most segments lie past their track's end and cost
+// next to nothing, so a wave is a workgroup of its own, which gives its place to the next
+// at once, and reads the map from memory (a turn loop of 128 events: sweeps of 0.43 ms, of
+// 0.80 in workgroups of four waves that stage the map and wait for their longest one).
+template <int FIELD, bool WANT_S, bool STOP>
+__global__ void __launch_bounds__(STOP ? 64 : 256, WANT_S ? 1 : 2) adj_seg_kernel(BwdArgs a) {
   extern __shared__ float2 s_nodes[];
   FieldDev f = a.field;
-  if constexpr (FIELD == 1) {
+  if constexpr (FIELD == 1 && !STOP) {
     const int nn = (int)padded_field_nodes(f.nr, f.nz);
     for (int i = threadIdx.x; i < nn; i += blockDim.x) s_nodes[i] = a.field.nodes[i];
     f.nodes = s_nodes;
@@ -812,14 +818,21 @@ hipError_t refine_backward(rkn_ctx* c, const float* cgrad, bool want_S) {
   b.jtj = want_S ? c->r_jtj.as<double>() : nullptr;
   const dim3 blk(64);
   const dim3 g1((unsigned)((b.n + 63) / 64));
-  const size_t smem = c->field_kind == 1 ? padded_field_nodes(c->nr, c->nz) * sizeof(float2) : 0;
-  auto seg = want_S ? (c->field_kind == 0 ? adj_seg_kernel<0, true> : adj_seg_kernel<1, true>)
-                    : (c->field_kind == 0 ? adj_seg_kernel<0, false> : adj_seg_kernel<1, false>);
+  const bool stop = b.turn_stop != 0;
+  const int threads = stop ? 64 : 256;
+  const size_t smem = c->field_kind == 1 && !stop ? padded_field_nodes(c->nr, c->nz) * sizeof(float2) : 0;
+  auto pick = [&](auto s) {
+    constexpr bool S = decltype(s)::value;
+    if (c->field_kind == 0) return stop ? adj_seg_kernel<0, S, true> : adj_seg_kernel<0, S, false>;
+    return stop ? adj_seg_kernel<1, S, true> : adj_seg_kernel<1, S, false>;
+  };
+  auto seg = want_S ? pick(std::true_type{}) : pick(std::false_type{});
   const hipError_t e = hipFuncSetAttribute((const void*)seg, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(adj_prep_kernel, dim3((unsigned)((b.n + kPrepSeeds - 1) / kPrepSeeds)), dim3(64 * kPrepSeeds), 0,
                      c->stream, b);
-  hipLaunchKernelGGL(seg, dim3((unsigned)((b.n * b.n_ckpt + 255) / 256)), dim3(256), smem, c->stream, b);
+  hipLaunchKernelGGL(seg, dim3((unsigned)((b.n * b.n_ckpt + threads - 1) / threads)), dim3(threads), smem, c->stream,
+                     b);
   hipLaunchKernelGGL(want_S ? adj_combine_kernel<true> : adj_combine_kernel<false>, g1, blk, 0, c->stream, b);
   return hipGetLastError();
 }
