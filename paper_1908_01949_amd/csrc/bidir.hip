@@ -102,7 +102,8 @@ rkn_status classify(rkn_ctx* c, const rkn_scan_params* q, int64_t n, const int32
   if (e == hipSuccess)
     e = hipMemcpyAsync(c->cl_perm.p, order.data(), sizeof(int64_t) * (size_t)n, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(c->cl_segs.p, list.segs.data(), sizeof(Seg) * list.segs.size(), hipMemcpyHostToDevice, c->stream);
+    e = hipMemcpyAsync(c->cl_segs.p, list.segs.data(), sizeof(Seg) * list.segs.size(), hipMemcpyHostToDevice,
+                       c->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(c->cl_evc.p, list.ev_chunk.data(), sizeof(int64_t) * list.ev_chunk.size(), hipMemcpyHostToDevice,
                        c->stream);

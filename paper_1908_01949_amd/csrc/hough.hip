@@ -465,7 +465,8 @@ static hipError_t run_hough_chunk(rkn_ctx* c, const HoughDev& h, int ev0, int n,
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!windows) return hipSuccess;
   hipLaunchKernelGGL(hough_peaks_kernel, dim3(vote_blocks(h), n), dim3(256), 0,
-                     c->stream, h, acc.as<unsigned short>(), c->hough_max.as<uint32_t>(), ev0, c->hough_cand_n.as<uint32_t>(),
+                     c->stream, h, acc.as<unsigned short>(), c->hough_max.as<uint32_t>(), ev0,
+                     c->hough_cand_n.as<uint32_t>(),
                      c->hough_cand.as<uint2>());
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(hough_select_kernel, dim3(n), dim3(256), 0, c->stream, h, acc.as<unsigned short>(),

@@ -90,8 +90,9 @@ __device__ __forceinline__ void window_seed(const WindowDev& W, int64_t k, doubl
 // that differ only in z0 and pz run on nearly one circle, so the lanes of a wave then cross
 // the same layers at the same steps, and leave the chamber's z range together. Measured
 // against the grid's own order (theta, z0, px, py, pz), with the blocks outside that range
-// skipped in both: 64 events in the field map 113.5 -> 109.3 ms, 16^5 FP32 seeds in the
-// uniform field 13.2 -> 10.7 ms; pz slower than px and py: 110.2 and 10.8 ms.
+// skipped in both and workgroup-wide tiles of seeds in place of chunks: 64 events in the
+// field map 113.5 -> 109.3 ms, 16^5 FP32 seeds in the uniform field 13.2 -> 10.7 ms; pz
+// slower than px and py: 110.2 and 10.8 ms.
 //
 // Position k of that walk: returns the seed's index in the grid's own order and, with v not
 // NULL, its coordinates.
@@ -222,10 +223,11 @@ struct rkn_ctx {
       r_argmin, r_resid6, r_argmin6, r_phi, r_phi6, r_phicur, r_tape, r_segbuf, r_list, r_grad, r_jtj, r_cgrad,
       r_slab, r_counter, r_tape6, r_segoff, r_segout, r_pick;
 
-  rkn::DevBuf* refine_buffers_[30] = {&r_seeds,  &r_seeds0, &r_trials, &r_event,  &r_segs,   &r_segs6,  &r_evc,   &r_evc6, &r_ident,
-                                      &r_base6,  &r_mask,   &r_resid,  &r_argmin, &r_resid6, &r_argmin6, &r_phi,
-                                      &r_phi6,   &r_phicur, &r_tape,   &r_segbuf, &r_list,   &r_grad,   &r_jtj,
-                                      &r_cgrad,  &r_slab,   &r_counter, &r_tape6, &r_segoff, &r_segout, &r_pick};
+  rkn::DevBuf* refine_buffers_[30] = {&r_seeds, &r_seeds0, &r_trials, &r_event, &r_segs, &r_segs6, &r_evc,
+                                      &r_evc6, &r_ident, &r_base6, &r_mask, &r_resid, &r_argmin, &r_resid6,
+                                      &r_argmin6, &r_phi, &r_phi6, &r_phicur, &r_tape, &r_segbuf, &r_list,
+                                      &r_grad, &r_jtj, &r_cgrad, &r_slab, &r_counter, &r_tape6, &r_segoff,
+                                      &r_segout, &r_pick};
   void refine_release() {
     for (rkn::DevBuf* b : refine_buffers_) b->release();
     r_ready = r_at_setup = false;

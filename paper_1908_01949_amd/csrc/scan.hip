@@ -639,8 +639,9 @@ __device__ __forceinline__ LaneSlot load_seed(const ScanArgs& a, int seg, int64_
 template <typename R>
 __device__ __forceinline__ void write_tape(const ScanArgs& a, int step, int64_t gidx, const State<R>& st) {
   float* tp = a.tape + (size_t)(step / a.ckpt) * 13 * a.n_pos + gidx;
-  const float v13[13] = {(float)st.x,  (float)st.y,  (float)st.z,   (float)st.cx,  (float)st.cy, (float)st.cz, (float)st.tx,
-                         (float)st.ty, (float)st.tz, (float)st.ctx, (float)st.cty, (float)st.ctz, (float)st.lam};
+  const float v13[13] = {(float)st.x,   (float)st.y,   (float)st.z,   (float)st.cx, (float)st.cy, (float)st.cz,
+                         (float)st.tx,  (float)st.ty,  (float)st.tz,  (float)st.ctx, (float)st.cty, (float)st.ctz,
+                         (float)st.lam};
 #pragma unroll
   for (int q = 0; q < 13; ++q) tp[(size_t)q * a.n_pos] = v13[q];
 }
@@ -777,9 +778,9 @@ __device__ __forceinline__ bool steady_lane(const ScanArgs& a, R lam) {
 // them have no block).
 //
 // With z_skip, a block whose middle point lies outside [z_lo, z_hi] is out of every wire's
-// reach along z (a quarter of the blocks of the 6000-step paths) and has no candidates.
-// Only the scan drops it: the refinement's inliers count wherever they are, and the counting instance
-// counts the pairs of the radial and sphere rules.
+// reach along z and has no candidates (it would hold 16 % of the 512-event batch's
+// distances). Only the scan drops it: the refinement's inliers count wherever they are, and
+// the counting instance counts the pairs of the radial and sphere rules.
 //
 // Per layer whose band meets the block's radial range, the candidates are the run of
 // hits that can reach the azimuth sector of the block's middle point. Each lane walks
@@ -789,8 +790,8 @@ __device__ __forceinline__ bool steady_lane(const ScanArgs& a, R lam) {
 template <typename R, int B, int TILE, int COLS, int MODE, bool Y_FIRST, bool COUNT, typename S>
 __device__ __forceinline__ void cull_block(const EventLds<R>& L, const R* pts, uint32_t* items, S* slab,
                                            uint32_t* touch, int lane, bool on, int nb, int step0, R r2min, R r2max,
-                                           float half_h, bool z_skip, float z_lo, float z_hi, R Kcull, R sqrt_lam, unsigned long long& w_tests,
-                                           unsigned long long& w_chords) {
+                                           float half_h, bool z_skip, float z_lo, float z_hi, R Kcull, R sqrt_lam,
+                                           unsigned long long& w_tests, unsigned long long& w_chords) {
   const int jc = nb / 2;
   // the block's middle point, from this lane's own column
   const R cx = pts[(jc * 3 + 0) * COLS + lane], cy = pts[(jc * 3 + 1) * COLS + lane],
@@ -829,11 +830,12 @@ __device__ __forceinline__ void cull_block(const EventLds<R>& L, const R* pts, u
       if (act) items[n_items + n_stage + lane_rank(m)] = first + (uint32_t)off;
       n_stage += (int)__popcll(m);
       if (n_items + n_stage > kCap - 64) {
-        n_items = test_staged<R, COLS, COUNT>(items, n_items, n_items + n_stage, pts, L.hits, jc, Kcull, lane, nb, w_tests,
-                                        w_chords);
+        n_items = test_staged<R, COLS, COUNT>(items, n_items, n_items + n_stage, pts, L.hits, jc, Kcull, lane, nb,
+                                              w_tests, w_chords);
         n_stage = 0;
         if (n_items > kCap - 64) {
-          flush_items<R, B, TILE, COLS, MODE, Y_FIRST>(items, n_items, pts, L.hits, slab, touch, lane, nb, step0, sqrt_lam);
+          flush_items<R, B, TILE, COLS, MODE, Y_FIRST>(items, n_items, pts, L.hits, slab, touch, lane, nb, step0,
+                                                       sqrt_lam);
           n_items = 0;
         }
       }
@@ -841,8 +843,9 @@ __device__ __forceinline__ void cull_block(const EventLds<R>& L, const R* pts, u
   }
   if (n_stage)
     n_items = test_staged<R, COLS, COUNT>(items, n_items, n_items + n_stage, pts, L.hits, jc, Kcull, lane, nb, w_tests,
-                                    w_chords);
-  if (n_items) flush_items<R, B, TILE, COLS, MODE, Y_FIRST>(items, n_items, pts, L.hits, slab, touch, lane, nb, step0, sqrt_lam);
+                                          w_chords);
+  if (n_items)
+    flush_items<R, B, TILE, COLS, MODE, Y_FIRST>(items, n_items, pts, L.hits, slab, touch, lane, nb, step0, sqrt_lam);
 }
 
 // Results of a chunk's lanes from their slab column, read and reset at the marked rows.
@@ -862,7 +865,8 @@ __device__ __forceinline__ void finish_scan(const ScanArgs& a, const EventLds<R>
       const int i = i0 + u;
       m2[u] = (R)INFINITY;
       // rows without a mark were not written in this chunk: +inf, nothing to reset
-      if (i < nh && (U > 1 || ((touch[i >> 5] >> (i & 31)) & 1u))) m2[u] = load_coherent(slab + (size_t)i * TILE + lane);
+      if (i < nh && (U > 1 || ((touch[i >> 5] >> (i & 31)) & 1u)))
+        m2[u] = load_coherent(slab + (size_t)i * TILE + lane);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -1289,9 +1293,10 @@ scan_kernel(ScanArgs a) {
         } else {
           take_block<R, FIELD, B, 64, VAR>(a, nodes, st, pr, pts, lane, nb, h, r0sq, far2, steady, live, r2min, r2max);
         }
-        cull_block<R, B, TILE, 64, MODE, VAR == 2, COUNT>(L, pts, items, slab, touch, lane, valid && (!STOP || live0),
-                                                      nb, blk * B, r2min, r2max, 0.5f * (float)hmax, a.walk, z_lo, z_hi, Kcull,
-                                                      sqrt_lam, w_tests, w_chords);
+        cull_block<R, B, TILE, 64, MODE, VAR == 2, COUNT>(L, pts, items, slab, touch, lane,
+                                                          valid && (!STOP || live0), nb, blk * B, r2min, r2max,
+                                                          0.5f * (float)hmax, a.walk, z_lo, z_hi, Kcull, sqrt_lam,
+                                                          w_tests, w_chords);
         if constexpr (COUNT) w_steps += (valid && (!STOP || live0)) ? nb : 0;
       }
       // The minima of a seed were folded by lanes of its own wave, and the slab is this
@@ -1725,7 +1730,8 @@ static bool launch_pipe_t(rkn_ctx* c, ScanArgs& a, int64_t max_chunks, bool allo
   // what scan_kernel's narrowest shape has no room for is refused for any number of seeds
   if (scan_lds_bytes(c, sizeof(R), FIELD, B, sizeof(R) == 8 || FIELD == 0 ? 4 : 8) + 256 > (size_t)c->max_lds_block)
     return false;
-  auto kern = a.turn_stop ? pipe_kernel<R, FIELD, B, COLS, MODE, 1, QUAD> : pipe_kernel<R, FIELD, B, COLS, MODE, 0, QUAD>;
+  auto kern =
+      a.turn_stop ? pipe_kernel<R, FIELD, B, COLS, MODE, 1, QUAD> : pipe_kernel<R, FIELD, B, COLS, MODE, 0, QUAD>;
   constexpr int prod = QUAD ? COLS / 16 : 1;   // producers of a pair
   const size_t field = field_lds_bytes(c, FIELD), room = (size_t)c->max_lds_block - 512;
   auto fits = [&](int64_t pairs, int con) {   // that many pairs of con consumers on one CU
@@ -2024,7 +2030,7 @@ trace_kernel(FieldDev f, double R0, double charge, double hstep, int turn_stop, 
   st.tz = (R)(v[4] / pm);
   st.lam = (R)(kKappa * charge / pm);
   st.cx = st.cy = st.cz = (R)0;
-      st.ctx = st.cty = st.ctz = (R)0;
+  st.ctx = st.cty = st.ctz = (R)0;
   const R h = (R)hstep;
   const R r0sq = (R)(R0 * R0);
   int n = 0;
