@@ -356,8 +356,9 @@ def other_workloads(geo, reps=3):
         dt = (time.perf_counter() - t) / reps
         out[name] = dict(seeds=n, steps=wl["n_steps"], ms_scan=round(dt * 1e3, 3),
                          seed_steps_per_s=n * wl["n_steps"] / dt, hough_ms=round(t_hough * 1e3, 3) or None)
-        # roofline of this scan: the kernel's own count of chord distances (untimed
-        # counting instance) in the same flop model, against the peak of its precision
+        # roofline of this scan: the rules' count of chord distances (untimed counting
+        # instance) in the same flop model, against the peak of its precision; the timed
+        # instance executes 5 % less of it in the uniform field (flops.py)
         k_steps, _, k_chords = rk.rkn_scan_work_counts(c.ctx, p, w)
         q = k_chords / k_steps
         f_alg = flops.per_seed_step(field.kind, q)
@@ -473,7 +474,8 @@ def main():
 
     windows, scores, _, ev_seed_off = rk.rkn_batch_results(ctx.ctx, ne)
     # untimed: the kernel's counting instance over the same windows gives the chord
-    # distances it evaluates per seed-step (the work the roofline credits)
+    # distances per seed-step that its radial and sphere rules keep (the work the roofline
+    # credits; the timed instance passes over those beyond the wires' z range, flops.py)
     k_steps, k_tests, k_chords = rk.rkn_scan_work_counts(ctx.ctx, sp, windows)
     q_kernel = k_chords / k_steps
     log(f"kernel work counts: {k_steps} seed-steps, {k_tests} sphere tests, {k_chords} chord distances "
@@ -491,6 +493,7 @@ def main():
     roof = dict(bound="alu", achieved=round(achieved, 3), peak=flops.PEAK_FP32_TFLOPS, unit="TFLOP/s",
                 frac=round(achieved / flops.PEAK_FP32_TFLOPS, 4), traffic=measured_traffic(),
                 frac_unpacked_fp32=round(achieved / flops.PEAK_FP32_UNPACKED_TFLOPS, 4),
+                frac_steps_only=round(achieved / f_alg * flops.F_RKN_GRID / flops.PEAK_FP32_TFLOPS, 4),
                 flops_per_seed_step=round(f_alg, 2), q_kernel=round(q_kernel, 5),
                 sphere_tests_per_seed_step=round(k_tests / k_steps, 5),
                 kernel=f"scan_kernel<float, rz field, {bsteps}-step blocks, {bwaves} waves>")
