@@ -1328,7 +1328,8 @@ scan_kernel(ScanArgs a) {
 // that share the field map; the producers come first, so that they sit on different SIMDs.
 // COLS: columns of the points (seeds of a chunk at most). QUAD: a seed on four lanes, 16
 // to a producer (QuadProp).
-// Same blocks, lists and arithmetic per chunk as scan_kernel: the same results.
+// Same blocks, lists and arithmetic per chunk as scan_kernel: the same results for a chunk
+// of the same seeds (seeds together in other chunks: the last bits, see seg_wire_d2).
 //
 // What bounds it is the producers' instruction stream: a wave alone on its SIMD issues a
 // VALU instruction every 5.6 to 8 cycles. A map step is 138 of them and took 930 cycles on
