@@ -319,7 +319,7 @@ __global__ void __launch_bounds__(64 * kPrepSeeds) adj_prep_kernel(BwdArgs a) {
 //
 // STOP, with the turn-partition stop: most segments lie past their track's end and cost
 // next to nothing, so a wave is a workgroup of its own, which gives its place to the next
-// at once, and reads the map from memory (a turn loop of 128 events: sweeps of 0.43 ms, of
+// at once, and reads the map from memory (a turn loop of 128 events: sweeps of 0.39 ms, of
 // 0.80 in workgroups of four waves that stage the map and wait for their longest one).
 template <int FIELD, bool WANT_S, bool STOP>
 __global__ void __launch_bounds__(STOP ? 64 : 256, WANT_S ? 1 : 2) adj_seg_kernel(BwdArgs a) {
